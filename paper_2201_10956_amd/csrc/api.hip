@@ -45,6 +45,7 @@ struct EncodeLayout {
   int32_t *pairs;
   double *lf64;
   float *lf32;
+  uint32_t *lfx;
   int32_t *list;
   int32_t *status;
   int64_t total;
@@ -74,6 +75,7 @@ EncodeLayout encode_layout(void *buf, int32_t M, int32_t n1, int32_t n0, int32_t
   L.pairs = c.take<int32_t>((int64_t)L.classes * L.Mp * L.Mp * 4);
   L.lf64 = c.take<double>((int64_t)N + 2);
   L.lf32 = c.take<float>((int64_t)N + 2);
+  L.lfx = c.take<uint32_t>((int64_t)N + 2);  // found again from lf32 (fx_table)
   L.list = c.take<int32_t>((int64_t)L.Wtot * 32);
   L.total = c.size();
   return L;
@@ -81,15 +83,13 @@ EncodeLayout encode_layout(void *buf, int32_t M, int32_t n1, int32_t n0, int32_t
 
 // Log factorials L[n] = sum_{b=1}^{n} log b, summed in increasing b (the
 // inner sums of Eq. 1), n = 0..nmax.
-void host_log_factorials(int64_t nmax, std::vector<double> &L64, std::vector<float> &L32) {
+void host_log_factorials(int64_t nmax, std::vector<double> &L64) {
   L64.assign(nmax + 1, 0.0);
-  L32.assign(nmax + 1, 0.f);
   double acc = 0.0;
   for (int64_t n = 1; n <= nmax; ++n) {
     acc = acc + log((double)n);
     L64[n] = acc;
   }
-  for (int64_t n = 0; n <= nmax; ++n) L32[n] = (float)L64[n];
 }
 
 // The tables are sequential sums, so the table up to a smaller n is a prefix
@@ -99,7 +99,6 @@ void host_log_factorials(int64_t nmax, std::vector<double> &L64, std::vector<flo
 // so a copy still reading one is never left without its source.
 struct LfTables {
   std::vector<double> L64;
-  std::vector<float> L32;
 };
 static const LfTables *log_factorial_tables(int64_t nmax) {
   static std::mutex m;
@@ -107,7 +106,7 @@ static const LfTables *log_factorial_tables(int64_t nmax) {
   std::lock_guard<std::mutex> g(m);
   if (built.empty() || (int64_t)built.back()->L64.size() < nmax + 1) {
     LfTables *t = new LfTables;
-    host_log_factorials(nmax, t->L64, t->L32);
+    host_log_factorials(nmax, t->L64);
     built.push_back(t);
   }
   return built.back();
@@ -426,6 +425,9 @@ Job make_job(const epi3_dataset &d, float *score, uint32_t *counts, int64_t *jpr
   J.N0 = d.n_controls;
   J.N1 = d.n_cases;
   J.P = P;
+  J.lfx = fx_table(d);
+  J.scale = fx_scale(d.n_samples);
+  J.lf_len = d.n_samples + 2;
   return J;
 }
 
@@ -623,8 +625,7 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
   const int32_t unit = fp4 ? 128 : 64;  // samples per 64-byte staged chunk
   const int n = (int)tasks.size();
   std::vector<int64_t> begin(n + 1, 0);
-  const float *lf32 = nullptr;
-  int32_t lf_len = 0;
+  int32_t lf_len = 0;  // longest table
   for (int x = 0; x < n; ++x) {
     const epi3_dataset &d = *tasks[x].d;
     PlainJob pj{};
@@ -644,15 +645,14 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
     pj.N0 = d.n_controls;
     pj.N1 = d.n_cases;
     pj.JB = JB;
+    pj.lfx = fx_table(d);
+    pj.scale = fx_scale(d.n_samples);
+    pj.lf_len = d.n_samples + 2;
     if (pj.Sb0 > pj.Sb || pj.Sb1 > pj.Sb) return EPI3_E_INVALID;
     HIP_OK(launch_write_plainjob(pj, W.pjobs + x, s));
     HIP_OK(launch_plain_prefix(W.pjobs + x, s));
     begin[x + 1] = begin[x] + pj.n_tiles;
-    // log factorials are prefix sums, so the longest table serves every set
-    if (d.n_samples + 2 > lf_len) {
-      lf_len = d.n_samples + 2;
-      lf32 = d.lf32;
-    }
+    lf_len = std::max(lf_len, pj.lf_len);
   }
   const int64_t tiles = begin[n];
   if (tiles == 0) return EPI3_OK;
@@ -688,8 +688,8 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
       out.stride = stride;
       out.sample_base = n0;
       rc = timed(3, s2, [&]() {
-        return launch_finish_plain(W.pjobs, W.job_begin, n, JB, buf[b], n0 * stride, nn, lf32,
-                                   lf_len, counts, out, s2) == hipSuccess
+        return launch_finish_plain(W.pjobs, W.job_begin, n, JB, buf[b], n0 * stride, nn, lf_len,
+                                   counts, out, s2) == hipSuccess
                    ? EPI3_OK
                    : EPI3_E_HIP;
       });
@@ -934,7 +934,7 @@ int epi3_encode(const uint8_t *geno_dev, int64_t ld, const uint8_t *pheno_host, 
   HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(L.status), 0u, 64, s));
   HIP_OK(hipMemcpyAsync(L.list, list.data(), list.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
   HIP_OK(hipMemcpyAsync(L.lf64, lt->L64.data(), n_lf * sizeof(double), hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(L.lf32, lt->L32.data(), n_lf * sizeof(float), hipMemcpyHostToDevice, s));
+  HIP_OK(launch_log_tables(L.lf64, L.lf32, L.lfx, (int64_t)n_lf, fx_shift(n_samples), s));
   HIP_OK(launch_encode(geno_dev, ld, L.list, n_snps, L.Mp, layout == EPI3_LAYOUT_SPLIT ? L.W0 : L.Wtot,
                        layout == EPI3_LAYOUT_SPLIT ? L.W1 : 0, L.planes, L.status, s));
   if (layout == EPI3_LAYOUT_MASKED)
@@ -1006,7 +1006,7 @@ static int enqueue_count(const epi3_dataset &d, int32_t variant, float *score, u
   HIP_OK(launch_tile_prefix(W.job, 1, s));
   HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 2, s));
   return timed(0, s, [&]() {
-    return launch_count_valu(W.job, 1, J.n_tiles, W.queue, d.lf32, d.n_samples + 2, P, P,
+    return launch_count_valu(W.job, 1, J.n_tiles, W.queue, d.n_samples + 2, P, P,
                              counts != nullptr, s) == hipSuccess
                ? EPI3_OK
                : EPI3_E_HIP;
@@ -1458,15 +1458,11 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
     });
     const int nv = (int)order.size();
     int P_lo = 8, P_hi = 4;
-    int32_t lf_len = 2;
-    const float *lf32 = nullptr;
+    int32_t lf_len = 2;  // longest table
     for (int x : order) {
       P_lo = std::min(P_lo, pick_P(*jobs[x].d));
       P_hi = std::max(P_hi, pick_P(*jobs[x].d));
-      if (jobs[x].d->n_samples + 2 > lf_len) {
-        lf_len = jobs[x].d->n_samples + 2;
-        lf32 = jobs[x].d->lf32;
-      }
+      lf_len = std::max(lf_len, jobs[x].d->n_samples + 2);
     }
     std::vector<Job> J(nv);
     int64_t begin = 0;
@@ -1475,7 +1471,8 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
       J[y] = make_job(*jobs[x].d, W.score[x], nullptr, W.jprefix[x], &W.st[x].kmin,
                       pick_P(*jobs[x].d));
       J[y].tile_begin = begin;
-      begin += J[y].n_tiles;
+      // a launch over several jobs draws four tiles of one job at a time
+      begin += nv > 1 ? (J[y].n_tiles + 3) / 4 * 4 : J[y].n_tiles;
     }
     if (nv > 0) {
       HIP_OK(launch_write_jobs(J.data(), nv, W.jobs, s));
@@ -1484,7 +1481,7 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
     }
     if (begin > 0) {
       const int rc = timed(0, s, [&]() {
-        return launch_count_valu(W.jobs, nv, begin, W.queue, lf32, lf_len, P_lo, P_hi, false, s) ==
+        return launch_count_valu(W.jobs, nv, begin, W.queue, lf_len, P_lo, P_hi, false, s) ==
                        hipSuccess
                    ? EPI3_OK
                    : EPI3_E_HIP;
@@ -1564,8 +1561,8 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
           HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 16, s));
           out.sample_base = 0;
           return timed(0, s, [&]() {
-            return launch_count_score_perm(W.pjobs + g, 0, n_all, stride, W.queue, fst, d.lf32,
-                                           d.n_samples + 2, out, s) == hipSuccess
+            return launch_count_score_perm(W.pjobs + g, 0, n_all, stride, W.queue, fst, fx_table(d),
+                                           d.n_samples + 2, fx_scale(d.n_samples), out, s) == hipSuccess
                        ? EPI3_OK
                        : EPI3_E_HIP;
           });
@@ -1590,8 +1587,8 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
           HIP_OK(hipStreamWaitEvent(s2, ev_cnt[b], 0));
           out.sample_base = n0;
           rc = timed(3, s2, [&]() {
-            return launch_finish_perm(pdev[b], n0 * stride, nn, stride, fst, d.lf32,
-                                      d.n_samples + 2, out, s2) == hipSuccess
+            return launch_finish_perm(pdev[b], n0 * stride, nn, stride, fst, fx_table(d),
+                                      d.n_samples + 2, fx_scale(d.n_samples), out, s2) == hipSuccess
                        ? EPI3_OK
                        : EPI3_E_HIP;
           });

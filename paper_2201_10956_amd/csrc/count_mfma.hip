@@ -258,6 +258,27 @@ struct PermAcc<true> {
   static __device__ __forceinline__ uint32_t get(const type &c, int v) { return (uint32_t)c[v]; }
 };
 
+// The 27 cells of one class as complete27, for callers that walk k with (i, j)
+// held: the full table fij[3a + b] of the pair (i, j), the {0, 1}^2 cells of
+// (i, k) and (j, k) and the per-SNP counts mk[c].
+__device__ __forceinline__ void complete_ij(const uint32_t n[8], const int fij[9], const int pik[4],
+                                            const int pjk[4], const int mk[2], int t[27]) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) t[9 * a + 3 * b + c] = (int)n[4 * a + 2 * b + c];
+      t[9 * a + 6 + c] = pik[2 * a + c] - t[9 * a + c] - t[9 * a + 3 + c];
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) t[18 + 3 * b + c] = pjk[2 * b + c] - t[3 * b + c] - t[9 + 3 * b + c];
+    t[24 + c] = (mk[c] - pik[c] - pik[2 + c]) - t[18 + c] - t[21 + c];
+  }
+#pragma unroll
+  for (int x = 0; x < 9; ++x) t[3 * x + 2] = fij[x] - t[3 * x] - t[3 * x + 1];
+}
+
 // x from quad lane TT in every lane of each quad (DPP quad_perm broadcast;
 // the compiler folds it into the AND that consumes it).
 template <int TT>
@@ -274,19 +295,19 @@ __device__ __forceinline__ v4i quad_bcast(v4i x) {
 // Completes and scores, in the count kernel, the 16 x 64 (triplet,
 // phenotype) case tables of one wave's pivot i of a tile (k = k0 .. k0 + 15,
 // lane = phenotype), as finish_perm_kernel does from the corner scratch: the
-// same cells, the same FP32 row order, the same outputs.  The accumulators
+// same cells, the same fixed-point sum, the same outputs.  The accumulators
 // hold, in lane (q, h), the case cells with genotype h at SNP k of phenotype
 // q mod 32 + 32 qb; one lane-half swap per register pair (qb = 0, 1) leaves
 // lane q with both genotypes of phenotype q.  Lanes 0..15 complete the
 // all-sample tables (cells from the tile's totals in LDS) and write, per k,
-// the 27 cells x 4 and their L[cell + 1] to the wave's part of the idle
-// staging buffer (`row`, 224 bytes per k), which every lane then reads as
-// broadcasts.  The log-factorial table sits at LDS address 0.
+// the 27 cells x 4 and the sum of their L[cell + 1] to the wave's part of the
+// idle staging buffer (`rows`, 112 bytes per k), which every lane then reads
+// as broadcasts.  The log-factorial table sits at LDS address 0.
 template <int FUSE>
 __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPermT][2],
                                             const uint4 *tot16, uint32_t *rows,
-                                            SelState *__restrict__ st, const PermOut &out, int i,
-                                            int j, int k0, int64_t slot, int wave, int lane,
+                                            SelState *__restrict__ st, const PermOut &out,
+                                            float scale, int i, int j, int k0, int64_t slot, int wave, int lane,
                                             uint32_t &kmin, uint32_t &kmax) {
   // the pivot is uniform over the wave: scalar row addresses below
   i = __builtin_amdgcn_readfirstlane(i);
@@ -322,12 +343,14 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
     const int mk[2] = {kk4.x << 2, kk4.w << 2};
     int t4[27];
     complete_table(tn, tij, tik, tjk, mi, mj, mk, pj.N << 2, t4);
-    uint32_t *row = rows + lane * 56;
+    uint32_t *row = rows + lane * 28;
+    uint32_t up = 0u;
 #pragma unroll
     for (int x = 0; x < 27; ++x) {
       row[x] = (uint32_t)t4[x];
-      row[28 + x] = __float_as_uint(lf_at_lds0(t4[x] + 4));
+      up += fx_at_lds0(t4[x] + 4);
     }
+    row[27] = up;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -344,6 +367,8 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
   const u2e cii = cp_row(i, i)[qc], cjj = cp_row(j, j)[qc];
   const int aij[4] = {lo4(cij.x), hi4(cij.x), lo4(cij.y), hi4(cij.y)};
   const int mi[2] = {lo4(cii.x), hi4(cii.y)}, mj[2] = {lo4(cjj.x), hi4(cjj.y)};
+  int fij[9];
+  pair_cells(aij, mi, mj, n1x4, fij);
   const int64_t base = lex_base(M, i, j) + k0;
   // rows k0 .. k0 + 15 lie below the padded stride Mp (k0 + 15 < M + 16):
   // loaded for every k, used for k in (j, M) only; one k ahead, through
@@ -378,25 +403,28 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
         const int aik[4] = {lo4(cik.x), hi4(cik.x), lo4(cik.y), hi4(cik.y)};
         const int ajk[4] = {lo4(cjk.x), hi4(cjk.x), lo4(cjk.y), hi4(cjk.y)};
         const int mk[2] = {lo4(ckk.x), hi4(ckk.y)};
-        complete_table(cn, aij, aik, ajk, mi, mj, mk, n1x4, c4);
+        complete_ij(cn, fij, aik, ajk, mk, c4);
       }
-      // cells x 4 in words 0..27, their L[cell + 1] in words 28..55 (same
-      // address in all lanes: broadcast reads), four rows at a time
-      const uint4 *rk = reinterpret_cast<const uint4 *>(rows + kk * 56);
-      float k2 = 0.f;  // rows in order: L[r + 1] - (L[r_0] + L[r_1]), r_1 = cases
+      // cells x 4 in words 0..26, the sum of their L[cell + 1] in word 27
+      // (same address in all lanes: broadcast reads), four rows at a time
+      const uint4 *rk = reinterpret_cast<const uint4 *>(rows + kk * 28);
+      uint32_t up = 0u, down = 0u;  // sums of L[r + 1] and of L[r_0] + L[r_1], r_1 = cases
 #pragma unroll
       for (int x4 = 0; x4 < 7; ++x4) {
-        const uint4 tv = rk[x4], lv = rk[7 + x4];
-        const uint32_t ta[4] = {tv.x, tv.y, tv.z, tv.w}, la[4] = {lv.x, lv.y, lv.z, lv.w};
+        const uint4 tv = rk[x4];
+        const uint32_t ta[4] = {tv.x, tv.y, tv.z, tv.w};
 #pragma unroll
         for (int y = 0; y < 4; ++y) {
           const int x = 4 * x4 + y;
           if (x < 27) {
             const int r0 = (int)ta[y] - c4[x];
-            k2 += __uint_as_float(la[y]) - (lf_at_lds0(r0) + lf_at_lds0(c4[x]));
+            down += fx_at_lds0(r0) + fx_at_lds0(c4[x]);
+          } else {
+            up = ta[y];
           }
         }
       }
+      const float k2 = fx_score(up - down, scale);
       const uint32_t key = f2key(k2);
       kmin = key < kmin ? key : kmin;
       kmax = key > kmax ? key : kmax;
@@ -423,16 +451,17 @@ template <bool FP4, int FUSE>
 __device__ __forceinline__ void count_perm_body(
     const PermJob *__restrict__ pjp, int64_t tile_begin, int64_t n_tiles, int64_t stride,
     unsigned long long *__restrict__ queue, SelState *__restrict__ st,
-    const float *__restrict__ lf32, int lf_len, const PermOut &out, unsigned char *stage,
+    const uint32_t *__restrict__ lfx, int lf_len, float scale, const PermOut &out,
+    unsigned char *stage,
     int64_t *sTile, float (*sTot)[64][4], uint4 (*sT16)[kPermKB], uint32_t (*sRange)[2],
-    float *sLf) {
+    uint32_t *sLf) {
   static_assert(FUSE == 0 || FP4, "fused scoring takes FP4 accumulators");
   typedef PermAcc<FP4> Acc;
   const PermJob pj = *pjp;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   if constexpr (FUSE != 0) {
-    for (int x = tid; x < lf_len; x += 256) sLf[x] = lf32[x];
+    for (int x = tid; x < lf_len; x += 256) sLf[x] = lfx[x];
     if (tid < 64) {
       sRange[tid][0] = 0xffffffffu;
       sRange[tid][1] = 0u;
@@ -711,7 +740,7 @@ __device__ __forceinline__ void count_perm_body(
       // the staging buffers are idle until the next tile's first store
       __builtin_amdgcn_s_setprio(0);
       fused_score<FUSE>(pj, acc, sT16[wave], reinterpret_cast<uint32_t *>(stage + wave * 4096), st,
-                        out, i, j, kbase, slot, wave, lane, kmin, kmax);
+                        out, scale, i, j, kbase, slot, wave, lane, kmin, kmax);
       continue;
     }
 
@@ -767,7 +796,8 @@ __global__ void __launch_bounds__(256, 2) count_mfma_perm_kernel(
   // second half, added by the waves of the first half
   __shared__ float sTot[2][64][4];
   const PermOut none{};
-  count_perm_body<FP4, 0>(pjp, tile_begin, n_tiles, stride, queue, nullptr, nullptr, 0, none, stage,
+  count_perm_body<FP4, 0>(pjp, tile_begin, n_tiles, stride, queue, nullptr, nullptr, 0, 1.f, none,
+                          stage,
                           sTile, sTot, nullptr, nullptr, nullptr);
 }
 
@@ -778,15 +808,15 @@ template <int FUSE>
 __global__ void __launch_bounds__(256, 2) count_score_perm_kernel(
     const PermJob *__restrict__ pjp, int64_t tile_begin, int64_t n_tiles, int64_t stride,
     unsigned long long *__restrict__ queue, SelState *__restrict__ st,
-    const float *__restrict__ lf32, int lf_len, PermOut out) {
+    const uint32_t *__restrict__ lfx, int lf_len, float scale, PermOut out) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   unsigned char *stage = lds + finish_perm_table_bytes(lf_len);
   int64_t *sTile = reinterpret_cast<int64_t *>(stage + 2 * kStageBytes);
   float(*sTot)[64][4] = reinterpret_cast<float(*)[64][4]>(sTile + 2);
   uint4(*sT16)[kPermKB] = reinterpret_cast<uint4(*)[kPermKB]>(sTot + 2);
   uint32_t(*sRange)[2] = reinterpret_cast<uint32_t(*)[2]>(sT16 + 4);
-  count_perm_body<true, FUSE>(pjp, tile_begin, n_tiles, stride, queue, st, lf32, lf_len, out, stage,
-                              sTile, sTot, sT16, sRange, reinterpret_cast<float *>(lds));
+  count_perm_body<true, FUSE>(pjp, tile_begin, n_tiles, stride, queue, st, lfx, lf_len, scale, out, stage,
+                              sTile, sTot, sT16, sRange, reinterpret_cast<uint32_t *>(lds));
 }
 
 // Completes the tables of one pass of tiles and scores them.  Workgroup per
@@ -794,7 +824,7 @@ __global__ void __launch_bounds__(256, 2) count_score_perm_kernel(
 // wave's lanes 0..15 complete the all-sample tables of the tile's 16 triplets
 // (one k each) and keep the cells in registers; then lane = phenotype q
 // loops over the 16 k, reading lane k's cells into scalar registers
-// (readlane) and their L[cell + 1] by scalar loads, and completes and scores
+// (readlane) and the sum of their L[cell + 1], and completes and scores
 // its case table.  Case cells are handled as 4 x count
 // (byte offsets into the table), so each lookup needs no index arithmetic.
 // Per-phenotype corner cells and case pair tables are contiguous 1 KB rows;
@@ -821,15 +851,13 @@ __global__ void __launch_bounds__(256) finish_perm_kernel(const PermJob *__restr
                                                           int64_t tile_begin, int64_t n_tiles,
                                                           int64_t stride,
                                                           SelState *__restrict__ st,
-                                                          const float *__restrict__ lf32,
-                                                          int lf_len, PermOut out) {
+                                                          const uint32_t *__restrict__ lfx,
+                                                          int lf_len, float scale, PermOut out) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const float *sL = lf32;
   FinishPermLds &sh = *reinterpret_cast<FinishPermLds *>(lds + (LDS ? finish_perm_table_bytes(lf_len) : 0));
   if (LDS) {
-    float *tab = reinterpret_cast<float *>(lds);
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) tab[x] = lf32[x];
-    sL = tab;
+    uint32_t *tab = reinterpret_cast<uint32_t *>(lds);
+    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) tab[x] = lfx[x];
   }
   if (threadIdx.x < 64) {
     sh.range[threadIdx.x][0] = 0xffffffffu;
@@ -884,10 +912,10 @@ __global__ void __launch_bounds__(256) finish_perm_kernel(const PermJob *__restr
     const int kk_lo = j + 1 - k0 > 0 ? j + 1 - k0 : 0;
     const int kk_hi = M - k0 < kPermKB ? M - k0 : kPermKB;
     // ---- all-sample tables, lane kk = triplet (i, j, k0 + kk) ----
-    // Kept in registers, two cell counts per register (16 bits each); the
-    // phenotype loop below reads lane kk's counts into scalar registers and
-    // fetches L[count + 1] by scalar loads, so neither LDS bandwidth nor
-    // vector instructions are spent broadcasting them.
+    // Kept in registers, two cell counts per register (16 bits each), with
+    // the sum of their L[count + 1]; the phenotype loop below reads lane kk's
+    // into scalar registers.
+    uint32_t lup = 0u;
     uint32_t pk[14];
 #pragma unroll
     for (int x = 0; x < 14; ++x) pk[x] = 0u;
@@ -907,13 +935,18 @@ __global__ void __launch_bounds__(256) finish_perm_kernel(const PermJob *__restr
       int t4[27];
       complete_table(tn, tij, tik, tjk, mi, mj, mk, pj.N << 2, t4);
 #pragma unroll
-      for (int x = 0; x < 27; ++x) pk[x >> 1] |= ((uint32_t)t4[x] >> 2) << (16 * (x & 1));
+      for (int x = 0; x < 27; ++x) {
+        pk[x >> 1] |= ((uint32_t)t4[x] >> 2) << (16 * (x & 1));
+        lup += LDS ? fx_at_lds0(t4[x] + 4) : fx_at(lfx, t4[x] + 4);
+      }
     }
     // ---- case tables and scores, lane = phenotype q ----
     const u2e cij = cp_row(i, j)[qc];
     const u2e cii = cp_row(i, i)[qc], cjj = cp_row(j, j)[qc];
     const int aij[4] = {lo4(cij.x), hi4(cij.x), lo4(cij.y), hi4(cij.y)};
     const int mi[2] = {lo4(cii.x), hi4(cii.y)}, mj[2] = {lo4(cjj.x), hi4(cjj.y)};
+    int fij[9];
+    pair_cells(aij, mi, mj, n1x4, fij);
     // loads of the next k are issued before the current k is scored; the
     // (uniform) row pointers advance by one k per step, each load being a
     // scalar base plus the lane's phenotype offset
@@ -946,23 +979,24 @@ __global__ void __launch_bounds__(256) finish_perm_kernel(const PermJob *__restr
         const int aik[4] = {lo4(cik.x), hi4(cik.x), lo4(cik.y), hi4(cik.y)};
         const int ajk[4] = {lo4(cjk.x), hi4(cjk.x), lo4(cjk.y), hi4(cjk.y)};
         const int mk[2] = {lo4(ckk.x), hi4(ckk.y)};
-        complete_table(cn, aij, aik, ajk, mi, mj, mk, n1x4, c4);
+        complete_ij(cn, fij, aik, ajk, mk, c4);
       }
       uint32_t spk[14];
 #pragma unroll
       for (int x = 0; x < 14; ++x) spk[x] = __builtin_amdgcn_readlane(pk[x], kk);
-      float k2 = 0.f;  // rows in order: L[r + 1] - (L[r_0] + L[r_1]), r_1 = cases
+      // sums of L[r + 1] (taken per triplet above) and of L[r_0] + L[r_1], r_1 = cases
+      const uint32_t up = __builtin_amdgcn_readlane(lup, kk);
+      uint32_t down = 0u;
 #pragma unroll
       for (int x = 0; x < 27; ++x) {
-        const uint32_t nall = (spk[x >> 1] >> (16 * (x & 1))) & 0xffffu;
-        const int tall = (int)(nall << 2);
-        const float l1 = lf32[nall + 1];  // uniform address: a scalar load
+        const int tall = (int)(((spk[x >> 1] >> (16 * (x & 1))) & 0xffffu) << 2);
         const int r0 = tall - c4[x];
         if (LDS)
-          k2 += l1 - (lf_at_lds0(r0) + lf_at_lds0(c4[x]));
+          down += fx_at_lds0(r0) + fx_at_lds0(c4[x]);
         else
-          k2 += l1 - (lf_at(sL, r0) + lf_at(sL, c4[x]));
+          down += fx_at(lfx, r0) + fx_at(lfx, c4[x]);
       }
+      const float k2 = fx_score(up - down, scale);
       const uint32_t key = f2key(k2);
       kmin = key < kmin ? key : kmin;
       kmax = key > kmax ? key : kmax;
@@ -1056,7 +1090,7 @@ int64_t host_perm_tiles(int64_t M) {
 template <bool FP4, int FUSE>
 static hipError_t launch_count_t(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
                                  int64_t stride, unsigned long long *queue, SelState *st,
-                                 const float *lf32, int32_t lf_len, const PermOut &out,
+                                 const uint32_t *lfx, int32_t lf_len, float scale, const PermOut &out,
                                  hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
   int dev = 0, n_cu = 0;
@@ -1084,7 +1118,7 @@ static hipError_t launch_count_t(const PermJob *pj_dev, int64_t tile_begin, int6
     int64_t blocks = (int64_t)n_cu * per_cu;
     if (blocks > n_tiles) blocks = n_tiles;
     hipLaunchKernelGGL(count_score_perm_kernel<FUSE>, dim3((unsigned)blocks), dim3(256), lds, s,
-                       pj_dev, tile_begin, n_tiles, stride, queue, st, lf32, lf_len, out);
+                       pj_dev, tile_begin, n_tiles, stride, queue, st, lfx, lf_len, scale, out);
   }
   return hipGetLastError();
 }
@@ -1095,9 +1129,9 @@ hipError_t launch_count_mfma_perm(const PermJob *pj_dev, int64_t tile_begin, int
                                   hipStream_t s) {
   const PermOut none{};
   return fp4 ? launch_count_t<true, 0>(pj_dev, tile_begin, n_tiles, stride, queue, nullptr, nullptr,
-                                       0, none, s)
+                                       0, 1.f, none, s)
              : launch_count_t<false, 0>(pj_dev, tile_begin, n_tiles, stride, queue, nullptr,
-                                        nullptr, 0, none, s);
+                                        nullptr, 0, 1.f, none, s);
 }
 
 bool perm_fused_ok(int32_t lf_len) {
@@ -1106,22 +1140,22 @@ bool perm_fused_ok(int32_t lf_len) {
 
 hipError_t launch_count_score_perm(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
                                    int64_t stride, unsigned long long *queue, SelState *st,
-                                   const float *lf32, int32_t lf_len, const PermOut &out,
+                                   const uint32_t *lfx, int32_t lf_len, float scale, const PermOut &out,
                                    hipStream_t s) {
   if (!perm_fused_ok(lf_len)) return hipErrorInvalidValue;
   if (out.mode == kPermOutSample)
-    return launch_count_t<true, kPermOutSample>(pj_dev, tile_begin, n_tiles, stride, queue, st, lf32,
-                                                lf_len, out, s);
+    return launch_count_t<true, kPermOutSample>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
+                                                lf_len, scale, out, s);
   if (out.mode == kPermOutBounded)
-    return launch_count_t<true, kPermOutBounded>(pj_dev, tile_begin, n_tiles, stride, queue, st, lf32,
-                                                 lf_len, out, s);
+    return launch_count_t<true, kPermOutBounded>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
+                                                 lf_len, scale, out, s);
   return hipErrorInvalidValue;
 }
 
 template <bool LDS, int MODE>
 static hipError_t launch_finish_perm_l(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
-                                       int64_t stride, SelState *st, const float *lf32,
-                                       int32_t lf_len, const PermOut &out, hipStream_t s) {
+                                       int64_t stride, SelState *st, const uint32_t *lfx,
+                                       int32_t lf_len, float scale, const PermOut &out, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
   int dev = 0, n_cu = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -1139,34 +1173,34 @@ static hipError_t launch_finish_perm_l(const PermJob *pj_dev, int64_t tile_begin
   int64_t blocks = (int64_t)n_cu * per_cu;
   if (blocks > n_tiles) blocks = n_tiles;
   hipLaunchKernelGGL((finish_perm_kernel<LDS, MODE>), dim3((unsigned)blocks), dim3(256), lds, s,
-                     pj_dev, tile_begin, n_tiles, stride, st, lf32, lf_len, out);
+                     pj_dev, tile_begin, n_tiles, stride, st, lfx, lf_len, scale, out);
   return hipGetLastError();
 }
 
 template <bool LDS>
 static hipError_t launch_finish_perm_m(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
-                                       int64_t stride, SelState *st, const float *lf32,
-                                       int32_t lf_len, const PermOut &out, hipStream_t s) {
+                                       int64_t stride, SelState *st, const uint32_t *lfx,
+                                       int32_t lf_len, float scale, const PermOut &out, hipStream_t s) {
   switch (out.mode) {
     case kPermOutPlane:
-      return launch_finish_perm_l<LDS, kPermOutPlane>(pj_dev, tile_begin, n_tiles, stride, st, lf32,
-                                                     lf_len, out, s);
+      return launch_finish_perm_l<LDS, kPermOutPlane>(pj_dev, tile_begin, n_tiles, stride, st, lfx,
+                                                     lf_len, scale, out, s);
     case kPermOutSample:
       return launch_finish_perm_l<LDS, kPermOutSample>(pj_dev, tile_begin, n_tiles, stride, st,
-                                                      lf32, lf_len, out, s);
+                                                      lfx, lf_len, scale, out, s);
     case kPermOutBounded:
       return launch_finish_perm_l<LDS, kPermOutBounded>(pj_dev, tile_begin, n_tiles, stride, st,
-                                                       lf32, lf_len, out, s);
+                                                       lfx, lf_len, scale, out, s);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_finish_perm(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
-                              int64_t stride, SelState *st, const float *lf32, int32_t lf_len,
-                              const PermOut &out, hipStream_t s) {
+                              int64_t stride, SelState *st, const uint32_t *lfx, int32_t lf_len,
+                              float scale, const PermOut &out, hipStream_t s) {
   return lf_in_lds(lf_len)
-             ? launch_finish_perm_m<true>(pj_dev, tile_begin, n_tiles, stride, st, lf32, lf_len, out, s)
-             : launch_finish_perm_m<false>(pj_dev, tile_begin, n_tiles, stride, st, lf32, lf_len, out, s);
+             ? launch_finish_perm_m<true>(pj_dev, tile_begin, n_tiles, stride, st, lfx, lf_len, scale, out, s)
+             : launch_finish_perm_m<false>(pj_dev, tile_begin, n_tiles, stride, st, lfx, lf_len, scale, out, s);
 }
 
 int64_t host_perm_sample_valid(int64_t M, int64_t stride) {

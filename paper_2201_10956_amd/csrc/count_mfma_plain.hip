@@ -390,11 +390,6 @@ __global__ void __launch_bounds__(256, 2) count_mfma_plain_kernel(
   }
 }
 
-// Completes both tables of every triplet of a pass and scores it; workgroup
-// per tile (persistent, round robin), thread per triplet of the tile.  Cells
-// are carried as 4 x count (byte offsets into the FP32 log-factorial table,
-// which sits at LDS address 0: the kernel declares no static LDS), so each
-// of the 81 lookups per triplet needs at most one add.
 // Lowest and highest key of the wave's lanes into keyrange[0..1].
 __device__ __forceinline__ void flush_range(uint32_t kmin, uint32_t kmax, uint32_t *keyrange) {
 #pragma unroll
@@ -409,32 +404,35 @@ __device__ __forceinline__ void flush_range(uint32_t kmin, uint32_t kmax, uint32
   }
 }
 
+// Completes both tables of every triplet of a pass and scores it; workgroup
+// per tile (persistent, round robin).  The 256 threads are the tile's (j, k)
+// and walk its 16 i, so the pair table (j, k) is completed once per tile and
+// the per-SNP counts of i are wave-uniform.  Cells are carried as 4 x count
+// (byte offsets into the log-factorial table, which sits at LDS address 0:
+// the kernel declares no static LDS), so each of the 81 lookups per triplet
+// needs at most one add.  The table is the job's own (its fixed-point step
+// depends on its samples) and reloaded when the job changes.
 template <int JB, bool LDS, bool COUNTS, int MODE>
 __global__ void __launch_bounds__(256) finish_plain_kernel(const PlainJob *__restrict__ jobs,
                                                            const int64_t *__restrict__ job_begin_p,
                                                            int n_jobs,
                                                            const uint4 *__restrict__ corners,
                                                            int64_t tile_begin, int64_t n_tiles,
-                                                           const float *__restrict__ lf32,
-                                                           int lf_len, PlainOut out) {
+                                                           PlainOut out) {
   constexpr int KT = 256 / JB;
   constexpr int kTile = kPI * JB * KT;  // 4096 triplets
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  // after the table (its dynamic block starts at LDS address 0)
-  int2(*smk)[KT] = reinterpret_cast<int2(*)[KT]>(lds + (LDS ? (lf_len * 4 + 15) / 16 * 16 : 0));
-  if (LDS) {
-    float *tab = reinterpret_cast<float *>(lds);
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) tab[x] = lf32[x];
-  }
-  __syncthreads();
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   typedef int i4e __attribute__((ext_vector_type(4)));
   typedef unsigned u4e __attribute__((ext_vector_type(4)));
   cptr<int64_t> job_begin = as_const(job_begin_p);
   JobDecoder jd;
-  int M = 0, Mp = 0, nJ = 0, N0x4 = 0, N1x4 = 0;
+  int M = 0, Mp = 0, nJ = 0, Nx4[2] = {0, 0};
   uint32_t MpMp = 0;  // pair tables < 4 G entries
   cptr<int64_t> pre = nullptr;
   gptr<i4e> pr = nullptr;
+  cptr<i4e> prc = nullptr;
+  const uint32_t *lfx = nullptr;
+  float scale = 1.f;
   float *score = nullptr;
   uint32_t *counts = nullptr, *keyrange = nullptr;
   // key range of this thread's scores of the current job (flushed per job)
@@ -442,6 +440,7 @@ __global__ void __launch_bounds__(256) finish_plain_kernel(const PlainJob *__res
   TileDecoder dec;
   // bounded: this launch's append bound (set before the launch)
   const float ub = MODE == kPermOutBounded ? out.st->ub : 0.f;
+  const int kl = threadIdx.x % KT, jl = threadIdx.x / KT;
   for (int64_t slot = blockIdx.x; slot < n_tiles; slot += gridDim.x) {
     const int64_t tg = tile_begin + slot * out.stride;
     if (jd.find(job_begin, n_jobs, tg)) {
@@ -452,36 +451,46 @@ __global__ void __launch_bounds__(256) finish_plain_kernel(const PlainJob *__res
       M = pj.M;
       Mp = pj.Mp;
       nJ = (int)plain_jblocks(M, JB);
-      N0x4 = pj.N0 << 2;
-      N1x4 = pj.N1 << 2;
+      Nx4[0] = pj.N0 << 2;
+      Nx4[1] = pj.N1 << 2;
       MpMp = (uint32_t)Mp * (uint32_t)Mp;
       pre = as_const(pj.jprefix);
       pr = (gptr<i4e>)pj.pairs;
+      prc = as_const(reinterpret_cast<const i4e *>(pj.pairs));
+      lfx = pj.lfx;
+      scale = pj.scale;
       score = pj.score;
       counts = pj.counts;
       keyrange = MODE == kPermOutSample ? out.range : pj.keyrange;
       dec.J = -1;
+      if (LDS) {
+        __syncthreads();  // the previous job's lookups are done
+        for (int x = threadIdx.x; x < pj.lf_len; x += 256) lds[x] = lfx[x];
+        __syncthreads();
+      }
     }
     const int64_t t = tg - jd.lo;  // tile within its job
     dec.find(pre, nJ, t);
     int i0, j0, k0;
     plain_tile_origin(dec, t, M, JB, i0, j0, k0);
+    i0 = __builtin_amdgcn_readfirstlane(i0);
     gptr<u4e> cor = (gptr<u4e>)(corners + slot * 2 * (int64_t)kTile);
-    // per-SNP counts (the pair tables' diagonals) of the tile's k range in
-    // LDS, so each lane's k margin is one conflict-free LDS read instead of a
-    // strided global load
-    __syncthreads();  // previous tile's readers are done
-    if (threadIdx.x < 2 * KT) {
-      const int c = threadIdx.x / KT, kl = threadIdx.x % KT;
-      const int k = k0 + kl < Mp ? k0 + kl : Mp - 1;
-      const i4e v = pr[(uint32_t)c * MpMp + (uint32_t)k * Mp + k];
-      smk[c][kl] = make_int2(v.x << 2, v.w << 2);
+    const int j = j0 + jl, k = k0 + kl;
+    if (j >= k || k >= M) continue;
+    int fjk[2][9];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const uint32_t cb = (uint32_t)c * MpMp;
+      const i4e c4 = pr[cb + (uint32_t)j * Mp + k];
+      const i4e jj = pr[cb + (uint32_t)j * Mp + j], kk = pr[cb + (uint32_t)k * Mp + k];
+      const int pjk[4] = {c4.x << 2, c4.y << 2, c4.z << 2, c4.w << 2};
+      const int mj[2] = {jj.x << 2, jj.w << 2}, mk[2] = {kk.x << 2, kk.w << 2};
+      pair_cells(pjk, mj, mk, Nx4[c], fjk[c]);
     }
-    __syncthreads();
-    for (int x = threadIdx.x; x < kTile; x += blockDim.x) {
-      const int il = x / (JB * KT), jl = (x / KT) % JB, kl = x % KT;
-      const int i = i0 + il, j = j0 + jl, k = k0 + kl;
-      if (i >= j || j >= k || k >= M) continue;
+    for (int il = 0; il < kPI; ++il) {
+      const int i = i0 + il;
+      if (i >= j) break;
+      const int x = il * 256 + threadIdx.x;
       int tab[2][27];
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -491,27 +500,14 @@ __global__ void __launch_bounds__(256) finish_plain_kernel(const PlainJob *__res
                                (q.x >> 14) & 0x3fffcu, (q.z >> 14) & 0x3fffcu,
                                (q.y << 2) & 0x3fffcu, (q.w << 2) & 0x3fffcu,
                                (q.y >> 14) & 0x3fffcu, (q.w >> 14) & 0x3fffcu};
-        const uint32_t cb = (uint32_t)c * MpMp;
-        const i4e a4 = pr[cb + (uint32_t)i * Mp + j], b4 = pr[cb + (uint32_t)i * Mp + k];
-        const i4e c4 = pr[cb + (uint32_t)j * Mp + k];
-        const i4e ii = pr[cb + (uint32_t)i * Mp + i], jj = pr[cb + (uint32_t)j * Mp + j];
-        const int2 kk2 = smk[c][kl];
+        const uint32_t cb = (uint32_t)c * MpMp + (uint32_t)i * Mp;
+        const i4e a4 = pr[cb + j], b4 = pr[cb + k], ii = prc[cb + i];
         const int pij[4] = {a4.x << 2, a4.y << 2, a4.z << 2, a4.w << 2};
+        const int pij2[2] = {(ii.x << 2) - pij[0] - pij[1], (ii.w << 2) - pij[2] - pij[3]};
         const int pik[4] = {b4.x << 2, b4.y << 2, b4.z << 2, b4.w << 2};
-        const int pjk[4] = {c4.x << 2, c4.y << 2, c4.z << 2, c4.w << 2};
-        const int mi[2] = {ii.x << 2, ii.w << 2}, mj[2] = {jj.x << 2, jj.w << 2};
-        const int mk[2] = {kk2.x, kk2.y};
-        complete_table(n, pij, pik, pjk, mi, mj, mk, c ? N1x4 : N0x4, tab[c]);
+        complete27(n, fjk[c], pij, pij2, pik, tab[c]);
       }
-      float k2 = 0.f;  // rows in order, each L[r + 1] - (L[r_0] + L[r_1])
-#pragma unroll
-      for (int x2 = 0; x2 < 27; ++x2) {
-        const int b0 = tab[0][x2], b1 = tab[1][x2];
-        if (LDS)
-          k2 += lf_at_lds0(b0 + b1 + 4) - (lf_at_lds0(b0) + lf_at_lds0(b1));
-        else
-          k2 += lf_at(lf32, b0 + b1 + 4) - (lf_at(lf32, b0) + lf_at(lf32, b1));
-      }
+      const float k2 = fx_score(fx_sum<27, LDS>(tab[0], tab[1], lfx), scale);
       const int64_t rank = lex_base(M, i, j) + k;
       if (MODE == kPermOutPlane) score[rank] = k2;
       if (MODE == kPermOutSample) out.sample[(out.sample_base + slot) * kTile + x] = k2;
@@ -607,14 +603,13 @@ hipError_t launch_count_mfma_plain(const PlainJob *jobs, const int64_t *job_begi
 template <int JB, bool LDS, bool COUNTS, int MODE>
 static hipError_t launch_finish_plain_t(const PlainJob *jobs, const int64_t *job_begin, int n_jobs,
                                         const uint4 *corners, int64_t tile_begin, int64_t n,
-                                        const float *lf32, int32_t lf_len, const PlainOut &out,
+                                        int32_t lf_len, const PlainOut &out,
                                         hipStream_t s) {
   if (n <= 0) return hipSuccess;
   int n_cu = 0;
   hipError_t e = cu_count(&n_cu);
   if (e != hipSuccess) return e;
-  const size_t lds = (LDS ? (size_t)(lf_len * 4 + 15) / 16 * 16 : 0) +
-                     2 * (256 / JB) * sizeof(int2);  // table, then the tile's k margins
+  const size_t lds = LDS ? (size_t)(lf_len * 4 + 15) / 16 * 16 : 0;
   auto kern = finish_plain_kernel<JB, LDS, COUNTS, MODE>;
   e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -626,23 +621,23 @@ static hipError_t launch_finish_plain_t(const PlainJob *jobs, const int64_t *job
   int64_t blocks = (int64_t)n_cu * per_cu;
   if (blocks > n) blocks = n;
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, s, jobs, job_begin, n_jobs,
-                     corners, tile_begin, n, lf32, lf_len, out);
+                     corners, tile_begin, n, out);
   return hipGetLastError();
 }
 
 template <int JB, bool LDS>
 static hipError_t launch_finish_plain_l(const PlainJob *jobs, const int64_t *job_begin, int n_jobs,
                                         const uint4 *corners, int64_t tile_begin, int64_t n,
-                                        const float *lf32, int32_t lf_len, bool counts,
+                                        int32_t lf_len, bool counts,
                                         const PlainOut &out, hipStream_t s) {
   switch (out.mode) {
     case kPermOutPlane:
-      return counts ? launch_finish_plain_t<JB, LDS, true, kPermOutPlane>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf32, lf_len, out, s)
-                    : launch_finish_plain_t<JB, LDS, false, kPermOutPlane>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf32, lf_len, out, s);
+      return counts ? launch_finish_plain_t<JB, LDS, true, kPermOutPlane>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf_len, out, s)
+                    : launch_finish_plain_t<JB, LDS, false, kPermOutPlane>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf_len, out, s);
     case kPermOutSample:
-      return launch_finish_plain_t<JB, LDS, false, kPermOutSample>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf32, lf_len, out, s);
+      return launch_finish_plain_t<JB, LDS, false, kPermOutSample>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf_len, out, s);
     case kPermOutBounded:
-      return launch_finish_plain_t<JB, LDS, false, kPermOutBounded>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf32, lf_len, out, s);
+      return launch_finish_plain_t<JB, LDS, false, kPermOutBounded>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf_len, out, s);
   }
   return hipErrorInvalidValue;
 }
@@ -650,22 +645,22 @@ static hipError_t launch_finish_plain_l(const PlainJob *jobs, const int64_t *job
 template <int JB>
 static hipError_t launch_finish_plain_j(const PlainJob *jobs, const int64_t *job_begin, int n_jobs,
                                         const uint4 *corners, int64_t tile_begin, int64_t n,
-                                        const float *lf32, int32_t lf_len, bool counts,
+                                        int32_t lf_len, bool counts,
                                         const PlainOut &out, hipStream_t s) {
   return lf_in_lds(lf_len)
-             ? launch_finish_plain_l<JB, true>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf32, lf_len, counts, out, s)
-             : launch_finish_plain_l<JB, false>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf32, lf_len, counts, out, s);
+             ? launch_finish_plain_l<JB, true>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf_len, counts, out, s)
+             : launch_finish_plain_l<JB, false>(jobs, job_begin, n_jobs, corners, tile_begin, n, lf_len, counts, out, s);
 }
 
 hipError_t launch_finish_plain(const PlainJob *jobs, const int64_t *job_begin, int32_t n_jobs,
                                int JB, const uint4 *corners, int64_t tile_begin, int64_t n_tiles,
-                               const float *lf32, int32_t lf_len, bool counts, const PlainOut &out,
+                               int32_t lf_len, bool counts, const PlainOut &out,
                                hipStream_t s) {
   if (out.stride < 1 || (counts && out.mode != kPermOutPlane)) return hipErrorInvalidValue;
   switch (JB) {
-    case 2: return launch_finish_plain_j<2>(jobs, job_begin, n_jobs, corners, tile_begin, n_tiles, lf32, lf_len, counts, out, s);
-    case 4: return launch_finish_plain_j<4>(jobs, job_begin, n_jobs, corners, tile_begin, n_tiles, lf32, lf_len, counts, out, s);
-    case 8: return launch_finish_plain_j<8>(jobs, job_begin, n_jobs, corners, tile_begin, n_tiles, lf32, lf_len, counts, out, s);
+    case 2: return launch_finish_plain_j<2>(jobs, job_begin, n_jobs, corners, tile_begin, n_tiles, lf_len, counts, out, s);
+    case 4: return launch_finish_plain_j<4>(jobs, job_begin, n_jobs, corners, tile_begin, n_tiles, lf_len, counts, out, s);
+    case 8: return launch_finish_plain_j<8>(jobs, job_begin, n_jobs, corners, tile_begin, n_tiles, lf_len, counts, out, s);
   }
   return hipErrorInvalidValue;
 }

@@ -1,5 +1,5 @@
 // Count stage on the vector ALU: AND + popcount over bit-planes, fused with
-// the FP32 K2 score.
+// the K2 score.
 //
 // Paper, Alg. 2 and the GPU approaches section: every combination i < j < k
 // gets a private frequency table in registers, filled over all samples of
@@ -96,9 +96,8 @@ __device__ __forceinline__ void accumulate(uint32_t (&acc)[P][8], const uint32_t
 }
 
 // One tile: P pivots i0 .. i0 + P - 1, pivot j, 64 lanes = 64 consecutive k.
-template <int P, bool COUNTS>
-__device__ __forceinline__ void valu_tile(cptr<Job> cj, int job, int j, int r, int lane,
-                                          const float *sL) {
+template <int P, bool COUNTS, bool LDS>
+__device__ __forceinline__ void valu_tile(cptr<Job> cj, int job, int j, int r, int lane) {
   const uint32_t *planes = cj[job].planes;
   const int32_t *pairs = cj[job].pairs;
   const int M = cj[job].M, Mp = cj[job].Mp;
@@ -116,48 +115,49 @@ __device__ __forceinline__ void valu_tile(cptr<Job> cj, int job, int j, int r, i
   accumulate<P>(acc0, planes, Mp, 0, W0, i0, j, k);
   accumulate<P>(acc1, planes, Mp, W0, W0 + W1, i0, j, k);
 
-  // ---- epilogue: complete the tables, K2 in FP32, write ----
+  // ---- epilogue: complete the tables, K2, write ----
+  // Cells are carried as 4 x count (byte offsets into the log-factorial
+  // table).  The nine cells of the pair (j, k) are completed once per tile;
+  // those of (i, j) are wave-uniform, so they stay on the scalar unit.
   const int N0 = cj[job].N0, N1 = cj[job].N1;
+  const uint32_t *lfx = cj[job].lfx;
+  const float scale = cj[job].scale;
   float *score = cj[job].score;
   uint32_t *counts = cj[job].counts;
   const int64_t MpMp = (int64_t)Mp * Mp;
   const int4 *pr = reinterpret_cast<const int4 *>(pairs);
+  typedef int i4v __attribute__((ext_vector_type(4)));
+  cptr<i4v> prc = as_const(reinterpret_cast<const i4v *>(pairs));
   const bool kvalid = k < M;
   uint32_t kmin = 0xffffffffu, kmax = 0u;
-  int mk0[2], mk1[2];
-  int4 pjk[2];
+  int fjk[2][9];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     const int4 kk = pr[c * MpMp + (int64_t)k * Mp + k];
-    mk0[c] = kk.x;
-    mk1[c] = kk.w;
-    pjk[c] = pr[c * MpMp + (int64_t)j * Mp + k];
+    const int4 jk = pr[c * MpMp + (int64_t)j * Mp + k];
+    const i4v mjj = prc[c * MpMp + (int64_t)j * Mp + j];
+    const int ajk[4] = {jk.x << 2, jk.y << 2, jk.z << 2, jk.w << 2};
+    const int mj[2] = {mjj.x << 2, mjj.w << 2}, mk[2] = {kk.x << 2, kk.w << 2};
+    pair_cells(ajk, mj, mk, (c == 0 ? N0 : N1) << 2, fjk[c]);
   }
-  typedef int i4v __attribute__((ext_vector_type(4)));
-  cptr<i4v> prc = as_const(reinterpret_cast<const i4v *>(pairs));
 #pragma unroll
   for (int tt = 0; tt < P; ++tt) {
     const int i = i0 + tt;
-    float k2 = 0.f;
     int tab[2][27];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       const i4v pij = prc[c * MpMp + (int64_t)i * Mp + j];
       const i4v mii = prc[c * MpMp + (int64_t)i * Mp + i];
-      const i4v mjj = prc[c * MpMp + (int64_t)j * Mp + j];
       const int4 pik = pr[c * MpMp + (int64_t)i * Mp + k];
-      const int aij[4] = {pij.x, pij.y, pij.z, pij.w};
-      const int aik[4] = {pik.x, pik.y, pik.z, pik.w};
-      const int ajk[4] = {pjk[c].x, pjk[c].y, pjk[c].z, pjk[c].w};
-      const int mi[2] = {mii.x, mii.w}, mj[2] = {mjj.x, mjj.w}, mk[2] = {mk0[c], mk1[c]};
-      complete_table(c == 0 ? acc0[tt] : acc1[tt], aij, aik, ajk, mi, mj, mk, c == 0 ? N0 : N1,
-                     tab[c]);
-    }
+      const int aij[4] = {pij.x << 2, pij.y << 2, pij.z << 2, pij.w << 2};
+      const int aij2[2] = {(mii.x - pij.x - pij.y) << 2, (mii.w - pij.z - pij.w) << 2};
+      const int aik[4] = {pik.x << 2, pik.y << 2, pik.z << 2, pik.w << 2};
+      uint32_t n[8];
 #pragma unroll
-    for (int x = 0; x < 27; ++x) {
-      const int r0 = tab[0][x], r1 = tab[1][x];
-      k2 += sL[r0 + r1 + 1] - (sL[r0] + sL[r1]);
+      for (int x = 0; x < 8; ++x) n[x] = (c == 0 ? acc0[tt][x] : acc1[tt][x]) << 2;
+      complete27(n, fjk[c], aij, aij2, aik, tab[c]);
     }
+    const float k2 = fx_score(fx_sum<27, LDS>(tab[0], tab[1], lfx), scale);
     if (i < j && kvalid) {
       const int64_t rank = lex_base(M, i, j) + k;
       score[rank] = k2;
@@ -168,8 +168,8 @@ __device__ __forceinline__ void valu_tile(cptr<Job> cj, int job, int j, int r, i
         uint32_t *o = counts + rank * 54;
 #pragma unroll
         for (int x = 0; x < 27; ++x) {
-          o[x] = (uint32_t)tab[0][x];
-          o[27 + x] = (uint32_t)tab[1][x];
+          o[x] = (uint32_t)tab[0][x] >> 2;
+          o[27 + x] = (uint32_t)tab[1][x] >> 2;
         }
       }
     }
@@ -189,33 +189,46 @@ __device__ __forceinline__ void valu_tile(cptr<Job> cj, int job, int j, int r, i
 
 // Persistent grid over the tiles of every job; a job's tiles use its own P
 // (PA or PB: one kernel serves a batch whose data sets prefer different P).
-template <int PA, int PB, bool COUNTS, bool LDS>
+// Dynamic LDS only: the log-factorial table (LDS) starts at LDS address 0,
+// followed by the workgroup's tile slot (MULTI).
+// One job (MULTI = false): each wave draws its own tiles.  Several jobs: each
+// has a log-factorial table of its own fixed-point step, so the workgroup
+// draws four consecutive tiles of one job at a time (job tile ranges start at
+// multiples of four) and reloads the table when the job changes.
+template <int PA, int PB, bool COUNTS, bool LDS, bool MULTI>
 __global__ void __launch_bounds__(256) count_valu_kernel(const Job *__restrict__ jobs, int n_jobs,
                                                          int64_t total_tiles,
                                                          unsigned long long *__restrict__ queue,
-                                                         const float *__restrict__ lf32,
                                                          int lf_len) {
-  extern __shared__ float sLds[];
-  const float *sL = lf32;
-  if (LDS) {
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) sLds[x] = lf32[x];
-    __syncthreads();
-    sL = sLds;
-  }
-
+  extern __shared__ __attribute__((aligned(16))) uint32_t sLds[];
+  unsigned long long *sTile =
+      reinterpret_cast<unsigned long long *>(sLds + (LDS ? (lf_len + 3) / 4 * 4 : 0));
   const int lane = threadIdx.x & 63;
   cptr<Job> cj = as_const(jobs);
   int job = -1;
   int64_t jb_begin = 0, jb_end = 0;
   int j = -1;
   int64_t jlo = 0, jhi = 0;
+  if (LDS && !MULTI) {
+    const uint32_t *tab = cj[0].lfx;
+    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) sLds[x] = tab[x];
+    __syncthreads();
+  }
 
   for (;;) {
-    unsigned long long got = 0;
-    if (lane == 0) got = atomicAdd(queue, 1ull);
-    const int64_t t = rfl64((int64_t)got);
+    int64_t t;
+    if (MULTI) {
+      __syncthreads();  // the previous draw's readers of sTile are done
+      if (threadIdx.x == 0) sTile[0] = atomicAdd(queue, 4ull);
+      __syncthreads();
+      t = rfl64((int64_t)sTile[0]);  // first of the four
+    } else {
+      unsigned long long got = 0;
+      if (lane == 0) got = atomicAdd(queue, 1ull);
+      t = rfl64((int64_t)got);
+    }
     if (t >= total_tiles) break;
-    if (t < jb_begin || t >= jb_end) {
+    if (job < 0 || t < jb_begin || t >= jb_end) {
       int lo = 0, hi = n_jobs - 1;  // last job whose first tile is <= t
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -226,6 +239,16 @@ __global__ void __launch_bounds__(256) count_valu_kernel(const Job *__restrict__
       jb_end = jb_begin + cj[job].n_tiles;
       jlo = jhi = 0;
       j = -1;
+      if (LDS && MULTI) {  // workgroup-uniform: t is
+        const uint32_t *tab = cj[job].lfx;
+        const int len = cj[job].lf_len;
+        for (int x = threadIdx.x; x < len; x += blockDim.x) sLds[x] = tab[x];
+        __syncthreads();
+      }
+    }
+    if (MULTI) {
+      t += __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      if (t >= jb_end) continue;  // padding of the job's tile range
     }
     const int M = cj[job].M;
     const int64_t local = t - jb_begin;
@@ -242,9 +265,9 @@ __global__ void __launch_bounds__(256) count_valu_kernel(const Job *__restrict__
     }
     const int r = (int)(local - jlo);
     if (PA == PB || cj[job].P == PA)
-      valu_tile<PA, COUNTS>(cj, job, j, r, lane, sL);
+      valu_tile<PA, COUNTS, LDS>(cj, job, j, r, lane);
     else
-      valu_tile<PB, COUNTS>(cj, job, j, r, lane, sL);
+      valu_tile<PB, COUNTS, LDS>(cj, job, j, r, lane);
   }
 }
 
@@ -261,53 +284,57 @@ hipError_t launch_write_jobs(const Job *jobs_host, int32_t n, Job *dst_dev, hipS
   return hipGetLastError();
 }
 
-template <int PA, int PB, bool C, bool LDS>
+template <int PA, int PB, bool C, bool LDS, bool MULTI>
 static hipError_t launch_valu_l(const Job *jobs_dev, int32_t n_jobs, int64_t total_tiles,
-                                unsigned long long *queue, const float *lf32, int32_t lf_len,
-                                hipStream_t s) {
+                                unsigned long long *queue, int32_t lf_len, hipStream_t s) {
   int dev = 0, n_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  const size_t lds = LDS ? (size_t)lf_len * sizeof(float) : 0;
-  e = hipFuncSetAttribute(reinterpret_cast<const void *>(&count_valu_kernel<PA, PB, C, LDS>),
+  auto kern = count_valu_kernel<PA, PB, C, LDS, MULTI>;
+  const size_t lds = (LDS ? (size_t)(lf_len + 3) / 4 * 16 : 0) + (MULTI ? 16 : 0);
+  e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   int per_cu = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, count_valu_kernel<PA, PB, C, LDS>, 256,
-                                                   lds);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, lds);
   if (e != hipSuccess) return e;
   if (per_cu <= 0) per_cu = 1;
   int64_t blocks = (int64_t)n_cu * per_cu;
   const int64_t need = (total_tiles + 3) / 4;
   if (blocks > need) blocks = need > 0 ? need : 1;
-  hipLaunchKernelGGL((count_valu_kernel<PA, PB, C, LDS>), dim3((unsigned)blocks), dim3(256), lds, s,
-                     jobs_dev, n_jobs, total_tiles, queue, lf32, lf_len);
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, s, jobs_dev, n_jobs, total_tiles,
+                     queue, lf_len);
   return hipGetLastError();
 }
 
-template <int PA, int PB, bool C>
+template <int PA, int PB, bool C, bool MULTI>
 static hipError_t launch_valu_t(const Job *jobs_dev, int32_t n_jobs, int64_t total_tiles,
-                                unsigned long long *queue, const float *lf32, int32_t lf_len,
-                                hipStream_t s) {
+                                unsigned long long *queue, int32_t lf_len, hipStream_t s) {
   return lf_in_lds(lf_len)
-             ? launch_valu_l<PA, PB, C, true>(jobs_dev, n_jobs, total_tiles, queue, lf32, lf_len, s)
-             : launch_valu_l<PA, PB, C, false>(jobs_dev, n_jobs, total_tiles, queue, lf32, lf_len, s);
+             ? launch_valu_l<PA, PB, C, true, MULTI>(jobs_dev, n_jobs, total_tiles, queue, lf_len, s)
+             : launch_valu_l<PA, PB, C, false, MULTI>(jobs_dev, n_jobs, total_tiles, queue, lf_len, s);
 }
 
 hipError_t launch_count_valu(const Job *jobs_dev, int32_t n_jobs, int64_t total_tiles,
-                             unsigned long long *queue, const float *lf32, int32_t lf_len,
-                             int32_t P_lo, int32_t P_hi, bool counts, hipStream_t s) {
-  if (P_lo != P_hi) {  // mixed batch (never with tables)
+                             unsigned long long *queue, int32_t lf_len, int32_t P_lo, int32_t P_hi,
+                             bool counts, hipStream_t s) {
+  if (n_jobs > 1) {  // batch (never with tables)
     if (counts) return hipErrorInvalidValue;
-    return launch_valu_t<8, 4, false>(jobs_dev, n_jobs, total_tiles, queue, lf32, lf_len, s);
+    if (P_lo != P_hi)
+      return launch_valu_t<8, 4, false, true>(jobs_dev, n_jobs, total_tiles, queue, lf_len, s);
+    return P_lo == 4
+               ? launch_valu_t<4, 4, false, true>(jobs_dev, n_jobs, total_tiles, queue, lf_len, s)
+               : launch_valu_t<8, 8, false, true>(jobs_dev, n_jobs, total_tiles, queue, lf_len, s);
   }
+  if (P_lo != P_hi) return hipErrorInvalidValue;
   if (P_lo == 4)
-    return counts ? launch_valu_t<4, 4, true>(jobs_dev, n_jobs, total_tiles, queue, lf32, lf_len, s)
-                  : launch_valu_t<4, 4, false>(jobs_dev, n_jobs, total_tiles, queue, lf32, lf_len, s);
-  return counts ? launch_valu_t<8, 8, true>(jobs_dev, n_jobs, total_tiles, queue, lf32, lf_len, s)
-                : launch_valu_t<8, 8, false>(jobs_dev, n_jobs, total_tiles, queue, lf32, lf_len, s);
+    return counts
+               ? launch_valu_t<4, 4, true, false>(jobs_dev, n_jobs, total_tiles, queue, lf_len, s)
+               : launch_valu_t<4, 4, false, false>(jobs_dev, n_jobs, total_tiles, queue, lf_len, s);
+  return counts ? launch_valu_t<8, 8, true, false>(jobs_dev, n_jobs, total_tiles, queue, lf_len, s)
+                : launch_valu_t<8, 8, false, false>(jobs_dev, n_jobs, total_tiles, queue, lf_len, s);
 }
 
 int64_t host_tiles(int64_t M, int P) {

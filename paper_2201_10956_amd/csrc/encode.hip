@@ -201,6 +201,24 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int64_t n) {
     p[x] = v;
 }
 
+__global__ void __launch_bounds__(256) log_tables_kernel(const double *__restrict__ lf64,
+                                                         float *__restrict__ lf32,
+                                                         uint32_t *__restrict__ lfx, int64_t n,
+                                                         double scale) {
+  const int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (x >= n) return;
+  const double v = lf64[x];
+  lf32[x] = (float)v;
+  lfx[x] = (uint32_t)(unsigned long long)rint(v * scale);
+}
+
+hipError_t launch_log_tables(const double *lf64, float *lf32, uint32_t *lfx, int64_t n, int shift,
+                             hipStream_t s) {
+  hipLaunchKernelGGL(log_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, lf64,
+                     lf32, lfx, n, ldexp(1.0, shift));
+  return hipGetLastError();
+}
+
 hipError_t launch_encode(const uint8_t *geno, int64_t ld, const int32_t *sample_list, int32_t M,
                          int32_t Mp, int32_t W0, int32_t W1, uint32_t *planes, int32_t *status,
                          hipStream_t s) {

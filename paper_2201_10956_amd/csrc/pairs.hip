@@ -12,22 +12,21 @@
 namespace epi3 {
 namespace {
 
-// Persistent workgroups, rows i round robin, thread per j > i: FP32 K2 by
-// lexicographic pair rank (rows in order, each L[r + 1] - (L[r_0] + L[r_1]))
-// and the scores' key range.  LDS: the log-factorial table, loaded once per
+// Persistent workgroups, rows i round robin, thread per j > i: K2 by
+// lexicographic pair rank (summed in fixed point, stored as FP32) and the
+// scores' key range.  LDS: the log-factorial table, loaded once per
 // workgroup.
 template <bool LDS>
 __global__ void __launch_bounds__(256) pair_scores_kernel(const int32_t *__restrict__ pairs,
                                                           int32_t M, int32_t Mp, int32_t N0,
-                                                          int32_t N1, const float *__restrict__ lf32,
-                                                          int32_t lf_len, float *__restrict__ score,
+                                                          int32_t N1, const uint32_t *__restrict__ lfx,
+                                                          int32_t lf_len, float scale,
+                                                          float *__restrict__ score,
                                                           uint32_t *__restrict__ keyrange) {
-  extern __shared__ float tab[];
-  const float *L = lf32;
+  extern __shared__ uint32_t tab[];  // no static LDS: the table starts at LDS address 0
   if (LDS) {
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) tab[x] = lf32[x];
+    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) tab[x] = lfx[x];
     __syncthreads();
-    L = tab;
   }
   const int4 *pr = reinterpret_cast<const int4 *>(pairs);
   const int64_t MpMp = (int64_t)Mp * Mp;
@@ -41,16 +40,11 @@ __global__ void __launch_bounds__(256) pair_scores_kernel(const int32_t *__restr
       for (int c = 0; c < 2; ++c) {
         const int4 p = pr[c * MpMp + (int64_t)i * Mp + j];
         const int4 jj = pr[c * MpMp + (int64_t)j * Mp + j];
-        const int n[4] = {p.x, p.y, p.z, p.w};
-        const int mi[2] = {ii[c].x, ii[c].w}, mj[2] = {jj.x, jj.w};
-        pair_cells(n, mi, mj, c ? N1 : N0, t[c]);
+        const int n[4] = {p.x << 2, p.y << 2, p.z << 2, p.w << 2};
+        const int mi[2] = {ii[c].x << 2, ii[c].w << 2}, mj[2] = {jj.x << 2, jj.w << 2};
+        pair_cells(n, mi, mj, (c ? N1 : N0) << 2, t[c]);
       }
-      float k2 = 0.f;
-#pragma unroll
-      for (int x = 0; x < 9; ++x) {
-        const int r0 = t[0][x], r1 = t[1][x];
-        k2 += L[r0 + r1 + 1] - (L[r0] + L[r1]);
-      }
+      const float k2 = fx_score(fx_sum<9, LDS>(t[0], t[1], lfx), scale);
       score[base + j] = k2;
       const uint32_t key = f2key(k2);
       kmin = key < kmin ? key : kmin;
@@ -89,7 +83,8 @@ hipError_t launch_pair_scores_t(const epi3_dataset &d, float *score, uint32_t *k
   int64_t blocks = (int64_t)n_cu * (per_cu > 0 ? per_cu : 1);
   if (blocks > M - 1) blocks = M - 1;
   hipLaunchKernelGGL(pair_scores_kernel<LDS>, dim3((unsigned)blocks), dim3(256), lds, s, d.pairs,
-                     M, d.snp_stride, d.n_controls, d.n_cases, d.lf32, lf_len, score, keyrange);
+                     M, d.snp_stride, d.n_controls, d.n_cases, fx_table(d), lf_len,
+                     fx_scale(d.n_samples), score, keyrange);
   return hipGetLastError();
 }
 

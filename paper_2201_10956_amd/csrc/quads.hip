@@ -57,15 +57,13 @@ __device__ __forceinline__ void unpack8(uint4 v, uint32_t *n) {
 template <bool LDS, bool T3>
 __global__ void __launch_bounds__(256) quad_scores_kernel(
     const uint32_t *__restrict__ planes, const int32_t *__restrict__ pairs, int32_t M, int32_t Mp,
-    int32_t W0, int32_t W1, int32_t N0, int32_t N1, const float *__restrict__ lf32, int32_t lf_len,
-    int64_t Q, const uint4 *__restrict__ t3, int64_t T, float *__restrict__ score,
+    int32_t W0, int32_t W1, int32_t N0, int32_t N1, const uint32_t *__restrict__ lfx, int32_t lf_len,
+    float scale, int64_t Q, const uint4 *__restrict__ t3, int64_t T, float *__restrict__ score,
     uint32_t *__restrict__ keyrange) {
-  extern __shared__ float tab[];
-  const float *L = lf32;
+  extern __shared__ uint32_t tab[];  // no static LDS: the table starts at LDS address 0
   if (LDS) {
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) tab[x] = lf32[x];
+    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) tab[x] = lfx[x];
     __syncthreads();
-    L = tab;
   }
   const int64_t MpMp4 = (int64_t)Mp * Mp * 4;
   uint32_t kmin = 0xffffffffu, kmax = 0u;
@@ -87,17 +85,14 @@ __global__ void __launch_bounds__(256) quad_scores_kernel(
       } else {
         quad_counts(planes, Mp, w0, w1, 1, i, j, k, l, cnt);
       }
+#pragma unroll
+      for (int x = 0; x < 48; ++x) cnt[x] <<= 2;  // byte offsets into the table
     };
     counts(0);
-    quad_cells(cnt, pairs, Mp, i, j, k, l, N0, t0);
+    quad_cells<2>(cnt, pairs, Mp, i, j, k, l, N0 << 2, t0);
     counts(1);
-    quad_cells(cnt, pairs + MpMp4, Mp, i, j, k, l, N1, t1);
-    float k2 = 0.f;  // rows in order: L[r + 1] - (L[r_0] + L[r_1])
-#pragma unroll
-    for (int x = 0; x < 81; ++x) {
-      const int r0 = t0[x], r1 = t1[x];
-      k2 += L[r0 + r1 + 1] - (L[r0] + L[r1]);
-    }
+    quad_cells<2>(cnt, pairs + MpMp4, Mp, i, j, k, l, N1 << 2, t1);
+    const float k2 = fx_score(fx_sum<81, LDS>(t0, t1, lfx), scale);
     score[r] = k2;
     const uint32_t key = f2key(k2);
     kmin = key < kmin ? key : kmin;
@@ -145,7 +140,8 @@ hipError_t launch_quad_scores_t(const epi3_dataset &d, const uint4 *t3, float *s
   if (blocks > need) blocks = need;
   hipLaunchKernelGGL((quad_scores_kernel<LDS, T3>), dim3((unsigned)blocks), dim3(256), lds, s,
                      static_cast<const uint32_t *>(d.planes), d.pairs, M, d.snp_stride, d.words[0],
-                     d.words[1], d.n_controls, d.n_cases, d.lf32, lf_len, Q, t3, T, score, keyrange);
+                     d.words[1], d.n_controls, d.n_cases, fx_table(d), lf_len,
+                     fx_scale(d.n_samples), Q, t3, T, score, keyrange);
   return hipGetLastError();
 }
 

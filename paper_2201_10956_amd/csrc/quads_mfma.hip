@@ -9,8 +9,8 @@
 // per 32 samples (the paper's table filling, Alg. 2, with a fourth SNP); here
 // they come from FP4 (E2M1) products with exact FP32 accumulation, the other
 // 65 cells by inclusion-exclusion (quad_cells) from the sub-triplet corner
-// table and the pairwise tables, and K2 with the expression and row order of
-// the vector-ALU kernel, so both give the same FP32 score.
+// table and the pairwise tables, and K2 in the same fixed point as the
+// vector-ALU kernel, so both give the same FP32 score.
 //
 // Workgroup tile: pivot j, four pivots i (one per wave), 16 consecutive k and
 // 32 consecutive l (blocks aligned to their size; combinations outside
@@ -320,15 +320,14 @@ template <bool LDS>
 __global__ void __launch_bounds__(256) finish_quad_kernel(
     const uint2 *__restrict__ corners, const int64_t *__restrict__ pre_p,
     const uint4 *__restrict__ t3, const int32_t *__restrict__ pairs, int M, int Mp, int N0,
-    int N1, int64_t T, int64_t tile_begin, int64_t n_tiles, const float *__restrict__ lf32,
-    int lf_len, float *__restrict__ score, uint32_t *__restrict__ keyrange) {
+    int N1, int64_t T, int64_t tile_begin, int64_t n_tiles, const uint32_t *__restrict__ lfx,
+    int lf_len, float scale, float *__restrict__ score, uint32_t *__restrict__ keyrange) {
   // the LDS table starts the kernel's dynamic LDS block, at LDS address 0
   // (no static LDS), so a lookup is one ds_read at the byte offset; the
   // per-SNP counts of the tile's l range follow it
-  extern __shared__ float qtab[];
-  const float *L = lf32;
+  extern __shared__ uint32_t qtab[];
   if (LDS) {
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) qtab[x] = lf32[x];
+    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) qtab[x] = lfx[x];
   }
   int2(*sml)[kQLB] = reinterpret_cast<int2(*)[kQLB]>(
       reinterpret_cast<unsigned char *>(qtab) + (LDS ? (lf_len * 4 + 15) / 16 * 16 : 0));
@@ -383,20 +382,12 @@ __global__ void __launch_bounds__(256) finish_quad_kernel(
         unpack8q(tcl[lex_base(M, i, j) + l], cnt + 24);
         unpack8q(tcl[lex_base(M, i, k) + l], cnt + 32);
         unpack8q(tcl[lex_base(M, j, k) + l], cnt + 40);
-        // cells as byte offsets into the FP32 table (x 4)
+        // cells as byte offsets into the table (x 4)
         const int2 mlv = sml[c][ll];
         const int ml[2] = {mlv.x, mlv.y};
         quad_cells<2>(cnt, pairs + c * MpMp4, Mp, i, j, k, l, (c ? N1 : N0) << 2, tc[c], ml);
       }
-      float k2 = 0.f;  // rows in order: L[r + 1] - (L[r_0] + L[r_1])
-#pragma unroll
-      for (int y = 0; y < 81; ++y) {
-        const int b0 = tc[0][y], b1 = tc[1][y];
-        if (LDS)
-          k2 += lf_at_lds0(b0 + b1 + 4) - (lf_at_lds0(b0) + lf_at_lds0(b1));
-        else
-          k2 += lf_at(L, b0 + b1 + 4) - (lf_at(L, b0) + lf_at(L, b1));
-      }
+      const float k2 = fx_score(fx_sum<81, LDS>(tc[0], tc[1], lfx), scale);
       score[quad_rank(M, i, j, k, l)] = k2;
       const uint32_t key = f2key(k2);
       kmin = key < kmin ? key : kmin;
@@ -431,7 +422,8 @@ hipError_t launch_finish_quad_t(const epi3_dataset &d, const uint2 *corners, con
   if (blocks > n_tiles) blocks = n_tiles;
   hipLaunchKernelGGL(finish_quad_kernel<LDS>, dim3((unsigned)blocks), dim3(256), lds, s, corners,
                      pre, t3, d.pairs, d.n_snps, d.snp_stride, d.n_controls, d.n_cases,
-                     c3(d.n_snps), tile_begin, n_tiles, d.lf32, lf_len, score, keyrange);
+                     c3(d.n_snps), tile_begin, n_tiles, fx_table(d), lf_len, fx_scale(d.n_samples),
+                     score, keyrange);
   return hipGetLastError();
 }
 

@@ -799,7 +799,7 @@ hipError_t launch_select(SelJob *sel_dev, int32_t n_jobs, int64_t max_T, int64_t
 // ------------------------------------------------------- test hook ----
 __global__ void __launch_bounds__(256) score_triplets_kernel(
     const uint32_t *__restrict__ planes, const int32_t *__restrict__ pairs,
-    const double *__restrict__ lf64, const float *__restrict__ lf32, int M, int64_t Mp, int W0,
+    const double *__restrict__ lf64, const uint32_t *__restrict__ lfx, float scale, int M, int64_t Mp, int W0,
     int W1, int N0, int N1, const uint32_t *__restrict__ ijk, int64_t n,
     uint32_t *__restrict__ counts, float *__restrict__ k2f, double *__restrict__ k2d) {
   const int lane = threadIdx.x & 63;
@@ -820,12 +820,12 @@ __global__ void __launch_bounds__(256) score_triplets_kernel(
     triplet_table(planes, pairs, nullptr, 1, nullptr, EPI3_LAYOUT_SPLIT, Mp, W0, W1, N0, N1, i, j,
                   k, tab);
     if (lane == 0) {
-      float f = 0.f;
+      uint32_t f = 0u;
       for (int x = 0; x < 27; ++x) {
         const int r0 = tab[0][x], r1 = tab[1][x];
-        f += lf32[r0 + r1 + 1] - (lf32[r0] + lf32[r1]);
+        f += lfx[r0 + r1 + 1] - (lfx[r0] + lfx[r1]);
       }
-      if (k2f) k2f[c] = f;
+      if (k2f) k2f[c] = fx_score(f, scale);
       if (k2d) k2d[c] = k2_fp64(tab, lf64);
       if (counts)
         for (int x = 0; x < 27; ++x) {
@@ -842,8 +842,8 @@ hipError_t launch_score_triplets(const epi3_dataset &d, const uint32_t *ijk, int
   int64_t blocks = (n + 3) / 4;
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL(score_triplets_kernel, dim3((unsigned)blocks), dim3(256), 0, s,
-                     (const uint32_t *)d.planes, d.pairs, d.lf64, d.lf32, d.n_snps,
-                     (int64_t)d.snp_stride,
+                     (const uint32_t *)d.planes, d.pairs, d.lf64, fx_table(d),
+                     fx_scale(d.n_samples), d.n_snps, (int64_t)d.snp_stride,
                      d.words[0], d.words[1], d.n_controls, d.n_cases, ijk, n, counts, k2f, k2);
   return hipGetLastError();
 }
