@@ -271,7 +271,7 @@ ScanLayout scan_layout(void *ws, const epi3_dataset &d, int32_t k, int64_t cand_
   Carver c(ws);
   L.job = c.take<Job>(1);
   L.jprefix = c.take<int64_t>((int64_t)d.n_snps + 1);
-  L.queue = c.take<unsigned long long>(4);
+  L.queue = c.take<unsigned long long>(8);
   L.sel = c.take<SelJob>(1);
   L.st = c.take<SelState>(1);
   L.hist = c.take<uint32_t>(kHistBins);
@@ -667,7 +667,22 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
   hipStream_t s2 = ctx->s2;
   hipEvent_t ev_start = ctx->ev[0], ev_cnt[2] = {ctx->ev[1], ctx->ev[2]},
              ev_fin[2] = {ctx->ev[3], ctx->ev[4]};
+  const bool fused = fp4 && !counts && plain_fused_ok(JB, lf_len);
   auto passes = [&](int64_t n_all, int64_t stride, PlainOut out) -> int {
+    if (fused) {
+      // counted and scored by one persistent kernel over all the tiles: no
+      // passes, no second stream
+      HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 16, s));
+      out.stride = stride;
+      out.sample_base = 0;
+      return timed(0, s, [&]() {
+        return launch_count_score_plain(W.pjobs, W.job_begin, n, JB, W.scratch,
+                                        2 * W.pass_tiles * kPlainTileScratch / kPlainStash, 0, n_all,
+                                        stride, W.queue, lf_len, out, s) == hipSuccess
+                   ? EPI3_OK
+                   : EPI3_E_HIP;
+      });
+    }
     HIP_OK(hipEventRecord(ev_start, s));
     HIP_OK(hipStreamWaitEvent(s2, ev_start, 0));
     int p = 0;

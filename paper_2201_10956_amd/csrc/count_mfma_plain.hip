@@ -7,17 +7,23 @@
 // (int8 bytes or FP4 nibbles) and exact accumulation.  This is the same
 // integer table the paper fills with AND + POPCNT (Alg. 2); the other 19
 // cells of each class follow from the pairwise tables as in the vector-ALU
-// kernel.  Counting writes the 8 corner cells of both classes of every
-// triplet of a pass of tiles to a scratch buffer; a second kernel completes
-// the tables and scores them (Eq. 1, FP32).
+// kernel.
+//
+// count_score_plain_kernel counts and scores (FP4 operands, tables of up to
+// about 17600 entries): the corner cells never leave the workgroup but for
+// one class's, kept in a small stash.  The two-kernel path below it serves
+// int8 operands, longer tables, tiles of 2 pivots j and tables written out:
+// counting writes the 8 corner cells of both classes of every triplet of a
+// pass of tiles to a scratch buffer; a second kernel completes the tables and
+// scores them (Eq. 1).
 //
 // Workgroup tile: 16 consecutive i, JB consecutive j, 256 / JB consecutive
 // k (4096 triplets), so one staged sample chunk serves 16 + JB + 256 / JB
 // SNPs instead of the 161 of a (32 i, one j, 128 k) slab.  Each of the 4
 // waves owns 2 i-blocks of 8 x 2 j (four 32-row A tiles: 8 i x (a, b), the
-// rows X_i[a] & X_j[b] formed in registers) and two 32-column B tiles
-// (16 k x g).  Operand rows are staged per chunk of 128 bytes (64 for
-// JB = 2) in double-buffered LDS.
+// rows X_i[a] & X_j[b] formed in registers) and two 32-column B tiles.
+// Operand rows are staged per chunk of 128 bytes (64 for JB = 2) in
+// double-buffered LDS.
 #include <algorithm>
 
 #include "epi3_internal.h"
@@ -40,7 +46,7 @@ constexpr int kPI = kPlainI;   // i per workgroup tile
 // Rows are padded by 16 bytes against bank conflicts.
 __host__ __device__ constexpr int plain_chunk(int JB) { return JB == 2 ? 64 : 128; }
 
-__host__ __device__ __forceinline__ int plain_kt(int JB) { return 256 / JB; }
+__host__ __device__ constexpr int plain_kt(int JB) { return 256 / JB; }
 
 // Tiles of j-block J (j in [JB J, JB J + JB)): i-blocks of 16 below the
 // block's last pivot, k-blocks of 256 / JB from JB J + 1 up to M - 1.
@@ -51,6 +57,22 @@ __host__ __device__ __forceinline__ int64_t plain_tiles_of_jb(int64_t M, int64_t
   if (jmax < 1 || j0 > M - 2) return 0;
   const int KT = plain_kt(JB);
   return ((jmax + kPI - 1) / kPI) * ((M - 1 - j0 + KT - 1) / KT);
+}
+
+// i-block and k-block of tile rr of j-block J: bands of 8 i-blocks, k-block
+// major within a band, so the tiles counted at a time on one XCD share the
+// operand rows of 8 i-blocks and of a few k-blocks.
+__host__ __device__ __forceinline__ void plain_tile_ib_kb(int rr, int64_t M, int64_t J, int JB,
+                                                          int nkb, int &ib, int &kb) {
+  int jmax = (int)J * JB + JB - 1;
+  if (jmax > (int)M - 2) jmax = (int)M - 2;
+  const int nib = (jmax + kPI - 1) / kPI;
+  const int band = rr / (8 * nkb);
+  const int rest = nib - 8 * band;
+  const int bcnt = rest < 8 ? rest : 8;
+  const int pos = rr - band * 8 * nkb;
+  kb = pos / bcnt;
+  ib = 8 * band + (pos - kb * bcnt);
 }
 
 __host__ __device__ __forceinline__ int64_t plain_jblocks(int64_t M, int JB) {
@@ -74,6 +96,12 @@ __device__ __forceinline__ int64_t rfl64q(int64_t v) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
   return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ int rfl(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T>
+__device__ __forceinline__ T *rflp(T *p) {
+  return reinterpret_cast<T *>(rfl64q((int64_t)reinterpret_cast<uintptr_t>(p)));
 }
 
 // jprefix[J] = tiles before j-block J; jprefix[nJ] = total.
@@ -147,8 +175,8 @@ __device__ __forceinline__ void plain_tile_origin(const TileDecoder &dec, int64_
   const int KT = 256 / JB;
   j0 = dec.J * JB;
   const int nkb = (M - 1 - j0 + KT - 1) / KT;
-  const int rr = (int)(t - dec.jlo);
-  const int ib = rr / nkb, kb = rr - ib * nkb;
+  int ib, kb;
+  plain_tile_ib_kb((int)(t - dec.jlo), M, dec.J, JB, nkb, ib, kb);
   i0 = ib * kPI;
   k0 = j0 + 1 + kb * KT;
 }
@@ -404,6 +432,532 @@ __device__ __forceinline__ void flush_range(uint32_t kmin, uint32_t kmax, uint32
   }
 }
 
+// 4 x the low half of v.
+__device__ __forceinline__ uint32_t lo_x4(uint32_t v, uint32_t two) {
+  uint32_t r;
+  asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
+      : "=v"(r)
+      : "v"(two), "v"(v));
+  return r;
+}
+
+// Three rows' lookups in the table at LDS address 0: L[r + 1], L[r_0], L[r_1]
+// of rows held as (class-0 count | all << 16).
+struct Lookups {
+  uint32_t up[3], d0[3], d1[3];
+};
+__device__ __forceinline__ Lookups look_up(const uint32_t c[3], uint32_t two) {
+  Lookups l;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const uint32_t r0 = lo_x4(c[a], two), r = (c[a] >> 16) << 2;
+    l.up[a] = fx_at_lds0((int)r + 4);
+    l.d0[a] = fx_at_lds0((int)r0);
+    l.d1[a] = fx_at_lds0((int)(r - r0));
+  }
+  return l;
+}
+__device__ __forceinline__ void add_up(const Lookups &l, uint32_t &up, uint32_t &down) {
+  up += l.up[0] + l.up[1];
+  down += l.d0[0] + l.d1[0];
+  down += l.d0[1] + l.d1[1];
+  up += l.up[2];
+  down += l.d0[2] + l.d1[2];
+}
+
+// Correction of a sum whose table in LDS ends after `lim` entries (it is
+// complete at `lfx`).  An entry past those is needed only by a row of more
+// than half of the samples, so by one row at most: `top`, the row with the
+// largest count.  Its three lookups are replaced (what the LDS held at those
+// addresses is subtracted again; nothing writes LDS meanwhile, and the
+// addresses stay inside the workgroup's block).
+__device__ __forceinline__ uint32_t fix_top(uint32_t sum, uint32_t top, const uint32_t *lfx,
+                                            uint32_t lim) {
+  const uint32_t r = top >> 16, r0 = top & 0xffffu;
+  if (r + 1 >= lim) {
+    sum += lfx[r + 1] - fx_at_lds0((int)(r + 1) << 2);
+    sum -= lfx[r0] - fx_at_lds0((int)r0 << 2);
+    sum -= lfx[r - r0] - fx_at_lds0((int)(r - r0) << 2);
+  }
+  return sum;
+}
+
+// Bytes between the two planes' k rows (half of the banks, for the stores).
+constexpr int kPlanePad = 128;
+// LDS of the count-and-score kernel: the log-factorial table at address 0,
+// then the staging buffers and the tile slot.
+template <int JB>
+__host__ __device__ constexpr int plain_stage_bytes() {
+  return 2 * ((2 * kPI + 2 * JB + 2 * plain_kt(JB)) * (plain_chunk(JB) + 16) + kPlanePad);
+}
+// Table entries that fit beside them with two workgroups per CU.
+template <int JB>
+constexpr int32_t plain_fused_entries() {
+  return ((kLdsTableBytes - plain_stage_bytes<JB>() - 16) / 16) * 4;
+}
+
+// Counts and scores the tiles in one kernel (FP4).  Both classes' samples are
+// one sequence of chunks.  The accumulators start at 2^23, so an FP32 sum's
+// low 16 bits are its count; at the class boundary each lane stores those of
+// the 128 class-0 cells to the workgroup's 64 KB stash (L2-resident), the
+// accumulators run on over class 1, and end with the all-sample cells.  The
+// column tiles are the two planes of the same 32 k, so a lane holds all 8
+// corner cells of its 16 triplets: half (g) of the 16 i, 2 j, one k.  Tables
+// are completed for both classes at once, two 16-bit counts per register, from
+// the pair table (j, k) completed once per j, (i, k) loaded once per i, and
+// (i, j) of the wave's 32 pairs kept in the idle staging buffer.  The next
+// tile's slot is drawn while this one is counted and its first chunk loaded
+// while this one is scored.
+//
+// Two waves per SIMD (227-231 registers), one of each workgroup, so one can
+// count while the other scores.  What bounds it, per 64 triplets: N / 16
+// cycles of matrix products, about 230 (2500 samples) to 330 (16384) cycles
+// of LDS lookups beside the count's own LDS reads (5/8 of its product time),
+// and 206 vector instructions of scoring; at 3100 x 2500 the LDS is busy 66%
+// of the time, the vector ALU 59%, the matrix cores 31%; at 2048 x 16384 the
+// matrix cores 56%.  Against the two-kernel path (32 bytes per triplet and
+// class through HBM, the scoring waiting on them): 2048 x 16384 84.1 ->
+// 71.8 ms, 3100 x 2500 112.5 -> 76.1 ms, 1003 x 6007 6.07 -> 5.09 ms, 32
+// uneven data sets 72.6 -> 65.8 ms.
+template <int JB, bool TRUNC, int MODE>
+__global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
+    const PlainJob *__restrict__ jobs, const int64_t *__restrict__ job_begin_p, int n_jobs,
+    uint4 *__restrict__ stash_p, int64_t tile_begin, int64_t n_tiles, int64_t stride,
+    unsigned long long *__restrict__ queue, int tab_cap, PlainOut out) {
+  typedef PlainAcc<true> Acc;
+  constexpr int KT = 256 / JB;
+  constexpr int kPKC = plain_chunk(JB), kPRow = kPKC + 16;
+  constexpr int kRowsI = 2 * kPI, kRowsJ = 2 * JB, kRowsK = 2 * KT;
+  constexpr int kRows = kRowsI + kRowsJ + kRowsK;
+  constexpr int kBuf = kRows * kPRow + kPlanePad;
+  constexpr int kPieces = kPKC / 16;
+  constexpr int kPer = (kRows * kPieces + 255) / 256;
+  constexpr int NBP = KT / 32;  // 32-wide k blocks; the 4 waves are (JB / 2) x NBP
+  constexpr int kSteps = kPKC / 32;
+  static_assert((JB / 2) * NBP == 4, "four waves per tile");
+  static_assert(2 * kBuf == plain_stage_bytes<JB>(), "LDS layout");
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+  uint8_t *stage = reinterpret_cast<uint8_t *>(lds + tab_cap);
+  int64_t *sTile = reinterpret_cast<int64_t *>(stage + 2 * kBuf);
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wj = wave / NBP, wb = wave - wj * NBP;
+  const int r = lane & 31, g = lane >> 5;
+  typedef int i4e __attribute__((ext_vector_type(4)));
+  cptr<int64_t> job_begin = as_const(job_begin_p);
+  JobDecoder jd;
+  int M = 0, Mp = 0, nJ = 0, nch0 = 0, nch = 0;
+  uint32_t Sb = 0, cls1 = 0, MpMp = 0, lim = 0, Npk = 0;
+  gptr<uint8_t> gv = nullptr;
+  cptr<int64_t> pre = nullptr;
+  gptr<i4e> pr = nullptr;
+  const uint32_t *lfx = nullptr;
+  float scale = 1.f;
+  float *score = nullptr;
+  uint32_t *keyrange = nullptr;
+  uint32_t kmin = 0xffffffffu, kmax = 0u;  // this thread's scores of the current job
+  TileDecoder dec;
+  const float ub = MODE == kPermOutBounded ? out.st->ub : 0.f;
+  uint4 *stash = stash_p + (int64_t)blockIdx.x * (kPlainStash / 16) + wave * 1024;  // [16][lane]
+  // lane roles: A row r = 4 i8 + 2 a + b; B column r = k (one plane per tile)
+  const int ra = (r >> 1) & 1, rb = r & 1;
+  const int o_xi = r * kPRow + 16 * g;
+  const int o_xj = (kRowsI + 2 * (2 * wj + ra) + rb) * kPRow + 16 * g;
+  const int o_b0 = (kRowsI + kRowsJ + 32 * wb + r) * kPRow + 16 * g;
+  const int o_b1 = o_b0 + KT * kPRow + kPlanePad;
+
+  // Slots are cut into 8 contiguous parts, one per XCD (workgroup b runs on
+  // XCD b mod 8), each with a counter in queue[0..7]: consecutive tiles share
+  // operand rows, which then stay in one XCD's L2.  A workgroup takes the next
+  // slot of its XCD's part and, once that is used up, of the others in turn.
+  // Thread 0: the part being drawn from, and the count drawn from it.
+  int part = 0;
+  const int xcd = blockIdx.x & 7;
+  auto draw = [&]() {  // a part holds fewer than 2^32 tiles
+    return atomicAdd(reinterpret_cast<unsigned *>(queue + ((xcd + part) & 7)), 1u);
+  };
+  auto slot_of = [&](unsigned c) {
+    for (;;) {
+      const int y = (xcd + part) & 7;
+      const int64_t lo = n_tiles * y / 8, hi = n_tiles * (y + 1) / 8;
+      if (lo + c < hi) return lo + c;
+      if (part >= 7) return n_tiles;  // every part is used up
+      ++part;
+      c = draw();
+    }
+  };
+  // (i0, j0, k0) of tile t of the current job
+  int i0 = 0, j0 = 0, k0 = 0;
+  auto place = [&](int64_t t) {
+    dec.find(pre, nJ, t);
+    plain_tile_origin(dec, t, M, JB, i0, j0, k0);
+    i0 = rfl(i0);
+    j0 = rfl(j0);
+    k0 = rfl(k0);
+  };
+  // Staged rows: [0, 32) X_i, then 2 JB rows X_j, then 2 KT rows X_k; SNP x's
+  // planes are rows 2 x and 2 x + 1 of the value planes.  Piece u of a thread
+  // is 16 bytes of row tid / kPieces + kStep u.  The i, j and k rows begin at
+  // multiples of a wave's rows, so every piece is a wave-uniform base plus one
+  // per-thread offset that is the same for all pieces.
+  // In LDS the rows lie in the order in which consecutive lanes read them
+  // (rows 36 words apart: no bank conflict among 16): X_i[a] of i-block b at
+  // row 4 (i % 8) + 2 a + b, the k rows plane by plane.
+  constexpr int kStep = 256 / kPieces, kWaveRows = 64 / kPieces;
+  static_assert(kRowsI == kStep && kWaveRows == 8 && kRowsJ % 8 == 0 && kRowsK % 8 == 0,
+                "a wave's 8 rows of a piece belong to one of i, j, k; piece 0 is i");
+  uint32_t thr = 0;  // this thread's row and column within the staged rows, in bytes
+  const int l_col = (lane & 7) * 16;
+  const int l_i = (4 * (lane >> 4) + 2 * ((lane >> 3) & 1)) * kPRow + l_col;
+  const int l_j = (lane >> 3) * kPRow + l_col;
+  const int l_k = ((lane >> 3) & 1) * (KT * kPRow + kPlanePad) + (lane >> 4) * kPRow + l_col;
+  auto has_piece = [&](int u) { return kWaveRows * wave + kStep * u < kRows; };  // wave-uniform
+  v4i pf[kPer];
+  auto fetch = [&](int ch) {
+    const uint32_t c0 = ch < nch0 ? (uint32_t)ch * kPKC : cls1 + (uint32_t)(ch - nch0) * kPKC;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (has_piece(u)) {
+        const int row = kWaveRows * wave + kStep * u;  // the wave's first row of this piece
+        const int base = row < kRowsI ? 2 * i0 : row < kRowsI + kRowsJ ? 2 * j0 - kRowsI : 2 * k0 - kRowsI - kRowsJ;
+        // (the row offset base + kStep u may be negative alone, never with thr's row)
+        const int64_t o = (int64_t)(base + kStep * u) * Sb + c0;
+        pf[u] = *reinterpret_cast<gptr<v4i>>(gv + o + thr);
+      }
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (has_piece(u)) {
+        const int row = kWaveRows * wave + kStep * u;  // the wave's first row of this piece
+        uint8_t *dst = stage + buf * kBuf;
+        if (u == 0)
+          dst += (16 * (wave & 1) + (wave >> 1)) * kPRow + l_i;
+        else if (row < kRowsI + kRowsJ)
+          dst += row * kPRow + l_j;
+        else
+          dst += (kRowsI + kRowsJ + (row - kRowsI - kRowsJ) / 2) * kPRow + l_k;
+        *reinterpret_cast<v4i *>(dst) = pf[u];
+      }
+  };
+
+  if (tid == 0) sTile[0] = slot_of(draw());
+  __syncthreads();
+  int64_t slot = rfl64q(sTile[0]);
+  bool loaded = false;  // the current tile's origin is set and its first chunk is in pf
+  while (slot < n_tiles) {
+    __builtin_amdgcn_s_setprio(0);
+    if (!loaded) {
+      const int64_t tg = tile_begin + slot * stride;
+      if (jd.find(job_begin, n_jobs, tg)) {
+        if (keyrange) flush_range(kmin, kmax, keyrange);
+        kmin = 0xffffffffu;
+        kmax = 0u;
+        const PlainJob &pj = jobs[jd.x];
+        M = rfl(pj.M);
+        Mp = rfl(pj.Mp);
+        Sb = (uint32_t)rfl(pj.Sb);
+        nch0 = (rfl(pj.Sb0) + kPKC - 1) / kPKC;
+        nch = nch0 + (rfl(pj.Sb1) + kPKC - 1) / kPKC;
+        cls1 = (uint32_t)Mp * 2u * Sb;
+        thr = (uint32_t)(tid / kPieces) * Sb + (uint32_t)(tid % kPieces) * 16u;
+        MpMp = (uint32_t)Mp * (uint32_t)Mp;
+        Npk = (uint32_t)rfl(pj.N0) | ((uint32_t)rfl(pj.N0 + pj.N1) << 16);
+        nJ = (int)plain_jblocks(M, JB);
+        gv = (gptr<uint8_t>)rflp(pj.vals);
+        pre = as_const(rflp(pj.jprefix));
+        pr = (gptr<i4e>)rflp(pj.pairs);
+        lfx = rflp(pj.lfx);
+        scale = __int_as_float(rfl(__float_as_int(pj.scale)));
+        score = rflp(pj.score);
+        keyrange = MODE == kPermOutSample ? out.range : rflp(pj.keyrange);
+        lim = (uint32_t)(pj.lf_len < tab_cap ? pj.lf_len : tab_cap);
+        dec.J = -1;
+        for (uint32_t x = tid; x < lim; x += 256) lds[x] = lfx[x];  // barrier below
+      }
+      place(tg - jd.lo);
+      fetch(0);
+    }
+    const unsigned drawn = tid == 0 ? draw() : 0u;  // for the next tile; used after the counts
+    typename Acc::type acc[2][2][2];  // [i-block][j of the pair][plane of k]
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int z = 0; z < 2; ++z)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[x][y][z][v] = 8388608.f;
+    // the low halves of triplet (x, y, u)'s 8 accumulators: words 4 (a, b) of
+    // plane 0, of plane 1
+    auto cells = [&](int x, int y, int u) {
+      uint32_t w[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h)
+        w[h] = __builtin_amdgcn_perm(__float_as_uint(acc[x][y][h >> 1][4 * u + 2 * (h & 1) + 1]),
+                                     __float_as_uint(acc[x][y][h >> 1][4 * u + 2 * (h & 1)]),
+                                     0x05040100u);
+      return make_uint4(w[0], w[1], w[2], w[3]);
+    };
+    auto keep = [&]() {
+      uint32_t lo = (uint32_t)lane;  // opaque: the addresses are formed here, not held through the tile
+      asm volatile("" : "+v"(lo));
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int y = 0; y < 2; ++y) (stash + (8 * x + 2 * u + y) * 64)[lo] = cells(x, y, u);
+    };
+    store(0);
+    __syncthreads();
+#define EPI3_PLD(BB, STP, XI, XJ, B0, B1)                                           \
+    XI = *reinterpret_cast<const v4i *>((BB) + o_xi + 32 * (STP));                \
+    XJ = *reinterpret_cast<const v4i *>((BB) + o_xj + 32 * (STP));                \
+    B0 = *reinterpret_cast<const v4i *>((BB) + o_b0 + 32 * (STP));                \
+    B1 = *reinterpret_cast<const v4i *>((BB) + o_b1 + 32 * (STP));
+#define EPI3_PSTEP(XI, XJ, B0, B1)                                                  \
+    {                                                                             \
+      const v4i xi_[2] = {quad_perm<0xA0>(XI), quad_perm<0xF5>(XI)};              \
+      _Pragma("unroll") for (int x = 0; x < 2; ++x) {                             \
+        const v4i a0 = xi_[x] & quad_perm<0x44>(XJ);                              \
+        acc[x][0][0] = Acc::mma(a0, B0, acc[x][0][0]);                            \
+        acc[x][0][1] = Acc::mma(a0, B1, acc[x][0][1]);                            \
+        const v4i a1 = xi_[x] & quad_perm<0xEE>(XJ);                              \
+        acc[x][1][0] = Acc::mma(a1, B0, acc[x][1][0]);                            \
+        acc[x][1][1] = Acc::mma(a1, B1, acc[x][1][1]);                            \
+      }                                                                           \
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // software pipeline over the steps of a chunk (operand sets X and Y in
+    // turn; the next chunk is stored before the last step)
+    v4i xiX, xjX, b0X, b1X, xiY, xjY, b0Y, b1Y;
+    EPI3_PLD(stage, 0, xiX, xjX, b0X, b1X)
+    for (int ch = 0; ch < nch; ++ch) {
+      const bool more = ch + 1 < nch;
+      if (ch == nch0) keep();
+      if (more) fetch(ch + 1);
+      const uint8_t *buf = stage + (ch & 1) * kBuf;
+      const uint8_t *nbuf = stage + ((ch + 1) & 1) * kBuf;
+      EPI3_PLD(buf, 1, xiY, xjY, b0Y, b1Y)
+      EPI3_PSTEP(xiX, xjX, b0X, b1X)
+      if constexpr (kSteps == 4) {
+        __builtin_amdgcn_sched_barrier(0);
+        EPI3_PLD(buf, 2, xiX, xjX, b0X, b1X)
+        EPI3_PSTEP(xiY, xjY, b0Y, b1Y)
+        __builtin_amdgcn_sched_barrier(0);
+        EPI3_PLD(buf, 3, xiY, xjY, b0Y, b1Y)
+        EPI3_PSTEP(xiX, xjX, b0X, b1X)
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) asm volatile("" : "+v"(acc[x][y][0]), "+v"(acc[x][y][1]));
+      if (more) store((ch + 1) & 1);
+      __syncthreads();
+      // after the last chunk this reads the other buffer's stale contents,
+      // which no product uses
+      EPI3_PLD(nbuf, 0, xiX, xjX, b0X, b1X)
+      EPI3_PSTEP(xiY, xjY, b0Y, b1Y)
+    }
+#undef EPI3_PLD
+#undef EPI3_PSTEP
+    if (nch == nch0) keep();
+    if (tid == 0) sTile[0] = slot_of(drawn);
+    __syncthreads();  // the staging buffers are idle from here to the next tile
+    // a scoring wave issues ahead of the other workgroup's counting waves: its
+    // lookups keep the LDS busy, and the products still fit between
+    __builtin_amdgcn_s_setprio(1);
+
+    const int64_t sslot = slot;
+    const int si0 = i0, jb = j0 + 2 * wj, kb = k0 + 32 * wb;
+    slot = rfl64q(sTile[0]);
+    // the next tile's first chunk, loaded towards the end of the scoring
+    auto next = [&]() {
+      loaded = false;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) pf[u] = v4i{};  // (ends the old chunk's live range)
+      if (slot < n_tiles) {
+        const int64_t tg = tile_begin + slot * stride;
+        if (tg >= jd.lo && tg < jd.hi) {  // (another job needs its own table first)
+          place(tg - jd.lo);
+          fetch(0);
+          loaded = true;
+        }
+      }
+    };
+
+    // ---- tables and scores ----
+    // lane values made opaque again: what is derived from them below is formed
+    // here and not held in registers through the counts
+    int ln = lane;
+    uint32_t two = 2u;
+    asm volatile("" : "+v"(ln), "+v"(two));
+    const int r = ln & 31, g = ln >> 5;
+    const int k = kb + r, kc = k < Mp ? k : Mp - 1;
+    const int i_end = kb < M ? jb + 1 - si0 : 0;  // first i (from si0) without a triplet here
+    if (i_end > 0) {  // wave-uniform
+    struct Raw { i4e a, b; };       // a pair's entries of both classes
+    auto load2 = [&](uint32_t row, uint32_t col) {
+      const uint32_t e = row * (uint32_t)Mp + col;
+      return Raw{pr[e], pr[MpMp + e]};
+    };
+    // -> (class 0 | all << 16) per cell
+    auto pack2 = [&](const Raw &w, u16x2 v[4]) {
+      v[0] = as_u16x2((uint32_t)w.a.x | ((uint32_t)(w.a.x + w.b.x) << 16));
+      v[1] = as_u16x2((uint32_t)w.a.y | ((uint32_t)(w.a.y + w.b.y) << 16));
+      v[2] = as_u16x2((uint32_t)w.a.z | ((uint32_t)(w.a.z + w.b.z) << 16));
+      v[3] = as_u16x2((uint32_t)w.a.w | ((uint32_t)(w.a.w + w.b.w) << 16));
+    };
+    auto pair4 = [&](uint32_t row, uint32_t col, u16x2 v[4]) { pack2(load2(row, col), v); };
+    // the all-sample cells, two per register (frees half of the accumulators)
+    uint4 all[2][4][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          all[x][u][y] = cells(x, y, u);
+          asm volatile("" : "+v"(all[x][u][y].x), "+v"(all[x][u][y].y), "+v"(all[x][u][y].z),
+                            "+v"(all[x][u][y].w));
+        }
+    // the next (i, k) entry and the next class-0 cells are loaded one triplet ahead
+    Raw pik_n = load2((uint32_t)(si0 + g), (uint32_t)kc);
+    uint4 q_n[2] = {stash[ln], (stash + 64)[ln]};
+    // lane = pair (si0 + lane / 2, jb + lane % 2): its four counted cells, the
+    // two (a, 2) cells and its lexicographic base, 32 bytes each, in this
+    // wave's part of the buffer
+    uint4 *pij_s = reinterpret_cast<uint4 *>(stage) + wave * 64;
+    if (ln < 32) {
+      u16x2 p[4], m[4];
+      const int i = si0 + (ln >> 1);
+      pair4((uint32_t)i, (uint32_t)(jb + (ln & 1)), p);
+      pair4((uint32_t)i, (uint32_t)i, m);
+      pij_s[2 * ln] = make_uint4(as_u32(p[0]), as_u32(p[1]), as_u32(p[2]), as_u32(p[3]));
+      const uint64_t base = (uint64_t)lex_base(M, i, jb + (ln & 1));
+      pij_s[2 * ln + 1] = make_uint4(as_u32(m[0] - p[0] - p[1]), as_u32(m[3] - p[2] - p[3]),
+                                     (uint32_t)base, (uint32_t)(base >> 32));
+    }
+    u16x2 fjk[2][9];
+    {
+      u16x2 mk4[4];
+      pair4((uint32_t)kc, (uint32_t)kc, mk4);
+      const u16x2 mk[2] = {mk4[0], mk4[3]};
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        u16x2 p[4], m[4];
+        pair4((uint32_t)(jb + y), (uint32_t)kc, p);
+        pair4((uint32_t)(jb + y), (uint32_t)(jb + y), m);
+        const u16x2 mj[2] = {m[0], m[3]};
+        pair_cells(p, mj, mk, as_u16x2(Npk), fjk[y]);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int il = 8 * x + 2 * u;
+        if (il == 10) next();
+        if (il >= i_end) continue;  // wave-uniform
+        const int i = si0 + il + g;
+        u16x2 pik[4];
+        pack2(pik_n, pik);
+        const uint4 q[2] = {q_n[0], q_n[1]};
+        if (il + 2 < kPI) {
+          pik_n = load2((uint32_t)(i + 2), (uint32_t)kc);
+          q_n[0] = (stash + (il + 2) * 64)[ln];
+          q_n[1] = (stash + (il + 3) * 64)[ln];
+        }
+        // Two triplets (j = jb, jb + 1), three rows (genotypes of i) of one
+        // (b, c) at a time: completed, looked up, and added two steps later, so
+        // vector instructions and lookups alternate and none waits for its
+        // own result (all lookups of a triplet at once leave the LDS idle
+        // while tables are completed and the vector ALU while it reads).
+        uint32_t up[2] = {0u, 0u}, down[2] = {0u, 0u}, top[2] = {0u, 0u};
+        uint4 pb[2];
+        Lookups in_flight[2];
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          const uint4 pa = pij_s[2 * (2 * (il + g) + y)], qa = all[x][u][y];
+          pb[y] = pij_s[2 * (2 * (il + g) + y) + 1];
+          const uint32_t pij[4] = {pa.x, pa.y, pa.z, pa.w}, pij2[2] = {pb[y].x, pb[y].y};
+          const uint32_t qs[4] = {q[y].x, q[y].y, q[y].z, q[y].w}, as[4] = {qa.x, qa.y, qa.z, qa.w};
+          u16x2 t[2][9];  // rows a = 0, 1: [a][3 b + c]
+#pragma unroll
+          for (int st = 0; st < 9; ++st) {
+            constexpr int order[9] = {0, 1, 3, 4, 2, 5, 6, 7, 8};  // cells with a 2 after their parts
+            const int bc = order[st], bb = bc / 3, cc = bc % 3;
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+              if (bb < 2 && cc < 2) {  // counted: class 0 from the stash, all from the accumulators
+                const int w = 2 * a + bb;
+                t[a][bc] = as_u16x2(__builtin_amdgcn_perm(as[2 * cc + (w >> 1)], qs[2 * cc + (w >> 1)],
+                                                          w & 1 ? 0x07060302u : 0x05040100u));
+              } else if (bb < 2) {
+                t[a][bc] = as_u16x2(pij[2 * a + bb]) - t[a][3 * bb] - t[a][3 * bb + 1];
+              } else if (cc < 2) {
+                t[a][bc] = pik[2 * a + cc] - t[a][cc] - t[a][3 + cc];
+              } else {
+                t[a][bc] = as_u16x2(pij2[a]) - t[a][6] - t[a][7];
+              }
+            }
+            const uint32_t c[3] = {as_u32(t[0][bc]), as_u32(t[1][bc]),
+                                   as_u32(fjk[y][bc] - t[0][bc] - t[1][bc])};
+            if (TRUNC) {
+#pragma unroll
+              for (int a = 0; a < 3; ++a) top[y] = c[a] > top[y] ? c[a] : top[y];
+            }
+            const int n = 9 * y + st;
+            if (n >= 2) {
+              add_up(in_flight[n & 1], up[(n - 2) / 9], down[(n - 2) / 9]);
+              // (keeps the additions of different steps apart)
+              asm volatile("" : "+v"(up[(n - 2) / 9]), "+v"(down[(n - 2) / 9]));
+            }
+            in_flight[n & 1] = look_up(c, two);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        add_up(in_flight[0], up[1], down[1]);
+        add_up(in_flight[1], up[1], down[1]);
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          uint32_t sum = up[y] - down[y];
+          if (TRUNC) sum = fix_top(sum, top[y], lfx, lim);
+          const float k2 = fx_score(sum, scale);
+          const int j = jb + y;
+          if (i < j && j < k && k < M) {
+            const int64_t rank = (int64_t)(((uint64_t)pb[y].w << 32) | pb[y].z) + k;
+            if (MODE == kPermOutPlane) score[rank] = k2;
+            if (MODE == kPermOutSample)  // slot: the tile's triplet order (i, j, k)
+              out.sample[(out.sample_base + sslot) * (int64_t)(kPI * 256) + (il + g) * 256 +
+                         (2 * wj + y) * KT + 32 * wb + r] = k2;
+            if (MODE == kPermOutBounded && k2 <= ub) {
+              // rare (a few thousand of the C(M,3) scores): one atomic per append
+              const unsigned long long pos = atomicAdd(&out.st->cn, 1ull);
+              if ((int64_t)pos < out.ccap) {
+                out.ckey[pos] = f2key(k2);
+                out.crank[pos] = rank;
+              }
+            }
+            const uint32_t key = f2key(k2);
+            kmin = key < kmin ? key : kmin;
+            kmax = key > kmax ? key : kmax;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      next();
+    }
+    __syncthreads();  // this tile's readers of the staging buffers and the table are done
+  }
+  if (keyrange) flush_range(kmin, kmax, keyrange);
+}
+
 // Completes both tables of every triplet of a pass and scores it; workgroup
 // per tile (persistent, round robin).  The 256 threads are the tile's (j, k)
 // and walk its 16 i, so the pair table (j, k) is completed once per tile and
@@ -600,6 +1154,88 @@ hipError_t launch_count_mfma_plain(const PlainJob *jobs, const int64_t *job_begi
   return hipErrorInvalidValue;
 }
 
+template <int JB, bool TRUNC, int MODE>
+static hipError_t launch_fused_t(const PlainJob *jobs, const int64_t *job_begin, int n_jobs,
+                                 void *stash, int64_t max_blocks, int64_t tile_begin, int64_t n,
+                                 int64_t stride, unsigned long long *queue, int32_t lf_len,
+                                 const PlainOut &out, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  int n_cu = 0;
+  hipError_t e = cu_count(&n_cu);
+  if (e != hipSuccess) return e;
+  auto kern = count_score_plain_kernel<JB, TRUNC, MODE>;
+  const int32_t cap = TRUNC ? plain_fused_entries<JB>() : (lf_len + 3) / 4 * 4;
+  const size_t lds = (size_t)cap * 4 + plain_stage_bytes<JB>() + 16;
+  e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  int per_cu = 0;
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, lds);
+  if (e != hipSuccess) return e;
+  if (per_cu <= 0) per_cu = 1;
+  int64_t blocks = (int64_t)n_cu * per_cu;
+  if (blocks > n) blocks = n;
+  if (blocks > max_blocks) blocks = max_blocks;
+  if (blocks < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, s, jobs, job_begin, n_jobs,
+                     static_cast<uint4 *>(stash), tile_begin, n, stride, queue, cap, out);
+  return hipGetLastError();
+}
+
+// Tables longer than the LDS holds beside the staging keep their first
+// entries there: at most one row of a triplet's table can need another as
+// long as those cover half of the samples, and the cover of 7/10 taken here
+// makes such rows rare.  16-bit counts.  The lookups that a longer table
+// would need stay inside the workgroup's LDS block.
+template <int JB>
+static bool fused_ok_t(int32_t lf_len) {
+  const int32_t cap = plain_fused_entries<JB>();
+  return lf_len - 2 <= 65535 && (int64_t)lf_len * 7 <= (int64_t)cap * 10 &&
+         (int64_t)lf_len * 4 <= (int64_t)cap * 4 + plain_stage_bytes<JB>();
+}
+
+bool plain_fused_ok(int JB, int32_t lf_len) {
+  return JB == 8 ? fused_ok_t<8>(lf_len) : JB == 4 && fused_ok_t<4>(lf_len);
+}
+
+template <int JB, bool TRUNC>
+static hipError_t launch_fused_m(const PlainJob *jobs, const int64_t *job_begin, int n_jobs,
+                                 void *stash, int64_t max_blocks, int64_t tile_begin, int64_t n,
+                                 int64_t stride, unsigned long long *queue, int32_t lf_len,
+                                 const PlainOut &out, hipStream_t s) {
+  switch (out.mode) {
+    case kPermOutPlane:
+      return launch_fused_t<JB, TRUNC, kPermOutPlane>(jobs, job_begin, n_jobs, stash, max_blocks, tile_begin, n, stride, queue, lf_len, out, s);
+    case kPermOutSample:
+      return launch_fused_t<JB, TRUNC, kPermOutSample>(jobs, job_begin, n_jobs, stash, max_blocks, tile_begin, n, stride, queue, lf_len, out, s);
+    case kPermOutBounded:
+      return launch_fused_t<JB, TRUNC, kPermOutBounded>(jobs, job_begin, n_jobs, stash, max_blocks, tile_begin, n, stride, queue, lf_len, out, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <int JB>
+static hipError_t launch_fused_j(const PlainJob *jobs, const int64_t *job_begin, int n_jobs,
+                                 void *stash, int64_t max_blocks, int64_t tile_begin, int64_t n,
+                                 int64_t stride, unsigned long long *queue, int32_t lf_len,
+                                 const PlainOut &out, hipStream_t s) {
+  return lf_len <= plain_fused_entries<JB>()
+             ? launch_fused_m<JB, false>(jobs, job_begin, n_jobs, stash, max_blocks, tile_begin, n, stride, queue, lf_len, out, s)
+             : launch_fused_m<JB, true>(jobs, job_begin, n_jobs, stash, max_blocks, tile_begin, n, stride, queue, lf_len, out, s);
+}
+
+hipError_t launch_count_score_plain(const PlainJob *jobs, const int64_t *job_begin, int32_t n_jobs,
+                                    int JB, void *stash, int64_t max_blocks, int64_t tile_begin,
+                                    int64_t n_tiles, int64_t stride, unsigned long long *queue,
+                                    int32_t lf_len, const PlainOut &out, hipStream_t s) {
+  if (stride < 1 || !plain_fused_ok(JB, lf_len)) return hipErrorInvalidValue;
+  switch (JB) {
+    case 4: return launch_fused_j<4>(jobs, job_begin, n_jobs, stash, max_blocks, tile_begin, n_tiles, stride, queue, lf_len, out, s);
+    case 8: return launch_fused_j<8>(jobs, job_begin, n_jobs, stash, max_blocks, tile_begin, n_tiles, stride, queue, lf_len, out, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 template <int JB, bool LDS, bool COUNTS, int MODE>
 static hipError_t launch_finish_plain_t(const PlainJob *jobs, const int64_t *job_begin, int n_jobs,
                                         const uint4 *corners, int64_t tile_begin, int64_t n,
@@ -677,8 +1313,9 @@ int64_t host_plain_sample_valid(int64_t M, int JB, int64_t stride, int64_t *n_sa
     // sampled tiles of this j-block: the multiples of stride in [t0, t0 + nt)
     for (int64_t t = (t0 + stride - 1) / stride * stride; t < t0 + nt; t += stride) {
       ++ns;
-      const int64_t rr = t - t0, ib = rr / nkb, kb = rr % nkb;
-      const int64_t i0 = ib * kPI, k0 = j0 + 1 + kb * KT;
+      int ib = 0, kb = 0;
+      plain_tile_ib_kb((int)(t - t0), M, J, JB, (int)nkb, ib, kb);
+      const int64_t i0 = (int64_t)ib * kPI, k0 = j0 + 1 + kb * KT;
       for (int64_t j = j0; j < j0 + JB && j < M; ++j) {
         const int64_t ni = std::max<int64_t>(0, std::min<int64_t>(i0 + kPI, j) - i0);
         const int64_t klo = std::max<int64_t>(k0, j + 1), khi = std::min<int64_t>(k0 + KT, M);

@@ -230,11 +230,18 @@ inline int64_t sort_len(int64_t cap) {
   return p;
 }
 
+// Two 16-bit counts of one register, added and subtracted as a pair: exact
+// modulo 2^16, and every completed count is below that.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 as_u16x2(uint32_t v) { return __builtin_bit_cast(u16x2, v); }
+__device__ __forceinline__ uint32_t as_u32(u16x2 v) { return __builtin_bit_cast(uint32_t, v); }
+
 // The 9 cells t[3 a + b] of one class of a pair (a, b in {0, 1, 2}) from the
 // counted cells n[2 a + b] (a, b in {0, 1}), the per-SNP counts mi[a], mj[b]
 // and the class size: every sample of the class is in exactly one row.
-__device__ __forceinline__ void pair_cells(const int n[4], const int mi[2], const int mj[2], int Nc,
-                                           int t[9]) {
+// V: int, or two counts per register (u16x2).
+template <typename V>
+__device__ __forceinline__ void pair_cells(const V n[4], const V mi[2], const V mj[2], V Nc, V t[9]) {
   t[0] = n[0];
   t[1] = n[1];
   t[3] = n[2];
@@ -254,14 +261,16 @@ __device__ __forceinline__ void pair_cells(const int n[4], const int mi[2], cons
 // lower-order cell without that SNP minus the rows with 0 and 1 there: two
 // subtractions for each of the 19.  (j, k) carries the full table because
 // callers walk i with j and k held, so its five derived cells leave the loop.
-__device__ __forceinline__ void complete27(const uint32_t n[8], const int fjk[9], const int pij[4],
-                                           const int pij2[2], const int pik[4], int t[27]) {
+// V: int, or two counts per register (u16x2).
+template <typename N, typename V>
+__device__ __forceinline__ void complete27(const N n[8], const V fjk[9], const V pij[4],
+                                           const V pij2[2], const V pik[4], V t[27]) {
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int c = 0; c < 2; ++c) t[9 * a + 3 * b + c] = (int)n[4 * a + 2 * b + c];
+      for (int c = 0; c < 2; ++c) t[9 * a + 3 * b + c] = (V)n[4 * a + 2 * b + c];
 #pragma unroll
     for (int b = 0; b < 2; ++b)
       t[9 * a + 3 * b + 2] = pij[2 * a + b] - t[9 * a + 3 * b] - t[9 * a + 3 * b + 1];
@@ -669,6 +678,16 @@ hipError_t launch_count_mfma_plain(const PlainJob *jobs, const int64_t *job_begi
                                    int JB, bool fp4, uint4 *corners, int64_t tile_begin,
                                    int64_t n_tiles, int64_t stride, unsigned long long *queue,
                                    hipStream_t s);
+// Count and score in one kernel (FP4 operands, no tables out): the tiles as
+// above, the first class's corner cells kept in `stash` (kPlainStash bytes per
+// workgroup, at most max_blocks of them); lf_len: the longest job's table;
+// queue: 8 zeroed 64-bit counters.
+constexpr int64_t kPlainStash = kPlainTileScratch / 2;
+bool plain_fused_ok(int JB, int32_t lf_len);
+hipError_t launch_count_score_plain(const PlainJob *jobs, const int64_t *job_begin, int32_t n_jobs,
+                                    int JB, void *stash, int64_t max_blocks, int64_t tile_begin,
+                                    int64_t n_tiles, int64_t stride, unsigned long long *queue,
+                                    int32_t lf_len, const PlainOut &out, hipStream_t s);
 hipError_t launch_finish_plain(const PlainJob *jobs, const int64_t *job_begin, int32_t n_jobs,
                                int JB, const uint4 *corners, int64_t tile_begin, int64_t n_tiles,
                                int32_t lf_len, bool counts, const PlainOut &out, hipStream_t s);
