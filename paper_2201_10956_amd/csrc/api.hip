@@ -1330,7 +1330,7 @@ BatchLayout batch_layout(void *ws, const epi3_job *jobs, int32_t n, int64_t cand
     // two buffers: the count kernel of pass p + 1 runs while pass p is
     // scored; not needed where FP4 passes count and score in one kernel
     const bool fp4 = variant != EPI3_VARIANT_MFMA;
-    if (!(L.bounded && fp4 && perm_fused_ok(d.n_samples + 2)))
+    if (!(fp4 && perm_fused_ok(d.n_samples + 2)))
       L.perm_scratch = c.take<uint8_t>(2 * L.pass_tiles * kPermTileScratch);
   }
   L.jprefix.resize(n);
@@ -1569,7 +1569,7 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
       // buffer).  Events order the two streams (also when captured); the join
       // at the end puts everything on `s` again.
       auto passes = [&](int64_t n_all, int64_t stride, SelState *fst, PermOut out) -> int {
-        if (fp4 && out.mode != kPermOutPlane && perm_fused_ok(d.n_samples + 2)) {
+        if (fp4 && perm_fused_ok(d.n_samples + 2)) {
           // counted and scored by one persistent kernel over all the tiles:
           // no scratch, no second stream
           if (n_all <= 0) return EPI3_OK;

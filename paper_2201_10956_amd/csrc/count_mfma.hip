@@ -14,10 +14,10 @@
 // controls = totals - cases.
 //
 // FP4 (E2M1) operands run the same products on the scaled f8f6f4 matrix
-// instructions.  Batches selected by bound count and score in one kernel
-// (count_score_perm_kernel): each wave scores its tile's tables from its
-// accumulators; otherwise the corner cells go through a scratch buffer to
-// finish_perm_kernel.
+// instructions.  FP4 batches whose log-factorial table fits count and score
+// in one kernel (count_score_perm_kernel): each wave scores its tile's tables
+// from its accumulators; otherwise the corner cells go through a scratch
+// buffer to finish_perm_kernel.
 //
 // Fragment layout of v_mfma_i32_32x32x32_i8 (gfx950, checked on hardware):
 // lane l supplies A row l % 32 and B column l % 32 with 16 consecutive K
@@ -202,6 +202,9 @@ constexpr int kRowsAll = kRowsPH + kRowsXK + kRowsP;
 constexpr int kStageBytes = kRowsAll * kRow; // one buffer
 
 
+// LDS row (after the phenotype rows) of plane c of the tile's k-th k.
+__device__ __forceinline__ int k_lds_row(int k, int c) { return 8 * (k & 3) + 4 * c + (k >> 2); }
+
 template <typename T>
 using gptr = const __attribute__((address_space(1))) T *;
 
@@ -222,8 +225,8 @@ __host__ __device__ __forceinline__ int perm_score_lds_bytes(int lf_len) {
 // wave then runs 8 MFMAs per 32 samples (4 row tiles of 4 triplets x 8
 // corner cells, 2 column tiles of 32 phenotypes).
 // FP4: operands are E2M1 nibbles (each staged byte holds two samples, so a
-// 32-byte step covers 64 samples) on v_mfma_scale_f32_32x32x64_f8f6f4 with
-// unit scales; accumulation in FP32 is exact for counts below 2^24.  The
+// 32-byte step covers 64 samples) on v_mfma_f32_32x32x64_f8f6f4;
+// accumulation in FP32 is exact for counts below 2^24.  The
 // all-sample corner counts (the phenotype-independent column) come from one
 // 16 x 16 x 128 product per wave and chunk over the staged pair and k rows;
 // int8 operands count them by popcounts of the A rows.
@@ -235,7 +238,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ v4f tot_mma(v4i a, v4i b, v4f c) {
   const v8i a8 = {a.x, a.y, a.z, a.w, 0, 0, 0, 0};
   const v8i b8 = {b.x, b.y, b.z, b.w, 0, 0, 0, 0};
-  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, b8, c, 4, 4, 0, 127, 0, 127);
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, b8, c, 4, 4, 0, 0, 0, 0);
 }
 
 template <bool FP4>
@@ -252,8 +255,10 @@ struct PermAcc<true> {
   static __device__ __forceinline__ type mma(v4i a, v4i b, type c) {
     const v8i a8 = {a.x, a.y, a.z, a.w, 0, 0, 0, 0};
     const v8i b8 = {b.x, b.y, b.z, b.w, 0, 0, 0, 0};
-    // cbsz = blgp = 4: both operands FP4 (E2M1); scale exponents 127 = 2^0
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 4, 4, 0, 127, 0, 127);
+    // cbsz = blgp = 4: both operands FP4 (E2M1); scale operands of constant 0
+    // select the form without the scale prefix (unit scales), one issue slot
+    // less per product (1024 x 8192 x 64 phenotypes 269.1 -> 261.9 ms)
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 4, 4, 0, 0, 0, 0);
   }
   static __device__ __forceinline__ uint32_t get(const type &c, int v) { return (uint32_t)c[v]; }
 };
@@ -292,17 +297,45 @@ __device__ __forceinline__ v4i quad_bcast(v4i x) {
   return y;
 }
 
+// Modes of the count-and-score kernel: 0 counts only.
+enum { kFuseSample = kPermOutSample, kFuseBounded = kPermOutBounded, kFusePlane = 3 };
+
+// Bytes of a wave's part of the idle staging buffers while it scores: its 16
+// all-sample tables (112 bytes each), then its scores (plane mode).
+constexpr int kScoreRows = 16 * 28 * 4;
+constexpr int kScorePart = kScoreRows + 16 * 64 * 4;
+static_assert(4 * kScorePart <= 2 * kStageBytes, "four waves' parts");
+
+// Three rows' lookups in the table at LDS address 0.
+struct Lookups {
+  uint32_t d0[3], d1[3];
+};
+
 // Completes and scores, in the count kernel, the 16 x 64 (triplet,
 // phenotype) case tables of one wave's pivot i of a tile (k = k0 .. k0 + 15,
 // lane = phenotype), as finish_perm_kernel does from the corner scratch: the
 // same cells, the same fixed-point sum, the same outputs.  The accumulators
-// hold, in lane (q, h), the case cells with genotype h at SNP k of phenotype
-// q mod 32 + 32 qb; one lane-half swap per register pair (qb = 0, 1) leaves
-// lane q with both genotypes of phenotype q.  Lanes 0..15 complete the
-// all-sample tables (cells from the tile's totals in LDS) and write, per k,
-// the 27 cells x 4 and the sum of their L[cell + 1] to the wave's part of the
-// idle staging buffer (`rows`, 112 bytes per k), which every lane then reads
-// as broadcasts.  The log-factorial table sits at LDS address 0.
+// start at 2^23 (their low halves are the counts) and hold, in lane (q, h),
+// the case cells with genotype h at SNP k of phenotype q mod 32 + 32 qb; one
+// lane-half swap per register pair (qb = 0, 1) leaves lane q with both
+// genotypes of phenotype q, packed in one register.  The case pair tables are
+// packed alike (genotypes 0 and 1 of k in one word), so the rows of k's
+// genotypes 0 and 1 are completed together in 16-bit pairs; those of genotype
+// 2 follow from the nine cells of the pair (i, j), completed once per tile.
+// Lanes 0..15 complete the all-sample tables (cells from the tile's totals in
+// LDS) and write, per k, the 27 cells x 4 and the sum of their L[cell + 1] to
+// the wave's part of the idle staging buffer (`rows`, 112 bytes per k), which
+// every lane then reads as broadcasts.  The log-factorial table sits at LDS
+// address 0.  Two k at a time, three rows (genotypes of k) per step: lookups
+// are added up two steps after they were issued, so they alternate with the
+// vector instructions (117 per k and wave instead of 170 with 32-bit cells and
+// all lookups of a k at once).  What bounds the kernel is instruction issue:
+// two waves per SIMD (240-254 registers), one counting while the other scores.
+// 203 x 1501, 20 phenotypes, score planes: 584 + 713 us in two kernels over the
+// corner scratch -> 1.82 instead of 2.00 ms for the whole call; 1024 x 8192, 64
+// phenotypes, bounded: 271 -> 269 ms.  Tables of k outside (j, M) and of phenotypes
+// past Q are consistent counts too (padding planes are zero), so they are
+// computed where they share a step and only their output is left out.
 template <int FUSE>
 __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPermT][2],
                                             const uint4 *tot16, uint32_t *rows,
@@ -322,12 +355,26 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
   for (int tt = 0; tt < kPermT; ++tt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)acc[tt][0][v],
-                                                       (uint32_t)acc[tt][1][v], false, false);
-      cc[tt][v] = sw[0] | (sw[1] << 16);
+      const auto sw = __builtin_amdgcn_permlane32_swap(
+          __float_as_uint(acc[tt][0][v]), __float_as_uint(acc[tt][1][v]), false, false);
+      cc[tt][v] = __builtin_amdgcn_perm(sw[1], sw[0], 0x05040100u);
+      asm volatile("" : "+v"(cc[tt][v]));  // packed here: the accumulators end
     }
+  typedef unsigned u2e __attribute__((ext_vector_type(2)));
+  gptr<u2e> cp = (gptr<u2e>)pj.case_pairs;
+  auto cp_row = [&](int x, int y) { return cp + ((int64_t)x * Mp + y) * Qp; };
+  const int q = lane;
+  // rows k0 .. k0 + 15 lie below the padded stride Mp (k0 + 15 < M + 16), one
+  // pair of k ahead, through uniform row pointers advanced per step
+  gptr<u2e> pik = cp_row(i, k0), pjk = cp_row(j, k0), pkk = cp_row(k0, k0);
+  const int64_t dkk = (int64_t)(Mp + 1) * Qp;
+  struct Rows { u2e ik, jk, kk; };
+  Rows next[2] = {{pik[q], pjk[q], pkk[q]}, {pik[Qp + q], pjk[Qp + q], pkk[dkk + q]}};
+  const u2e cij = cp_row(i, j)[q], cii = cp_row(i, i)[q], cjj = cp_row(j, j)[q];
+  const int n1x4 = pj.n1[q] << 2;
+  const float ubq = FUSE == kFuseBounded ? st[q < Q ? q : 0].ub : 0.f;
   // all-sample tables, lane kk = triplet (i, j, k0 + kk)
-  if (lane >= kk_lo && lane < kk_hi) {
+  if (lane < kPermKB) {
     const int4 *tp = reinterpret_cast<const int4 *>(pj.tot_pairs);
     const int k = k0 + lane;
     const uint4 tq = tot16[lane];
@@ -355,93 +402,120 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  typedef unsigned u2e __attribute__((ext_vector_type(2)));
-  gptr<u2e> cp = (gptr<u2e>)pj.case_pairs;
-  auto cp_row = [&](int x, int y) { return cp + ((int64_t)x * Mp + y) * Qp; };
-  auto lo4 = [](unsigned v) { return (int)((v & 0xffffu) << 2); };
-  auto hi4 = [](unsigned v) { return (int)((v >> 16) << 2); };
-  const int q = lane, qc = q < Q ? q : 0;
-  const int n1x4 = pj.n1[qc] << 2;
-  const float ubq = FUSE == kPermOutBounded ? st[qc].ub : 0.f;
-  const u2e cij = cp_row(i, j)[qc];
-  const u2e cii = cp_row(i, i)[qc], cjj = cp_row(j, j)[qc];
-  const int aij[4] = {lo4(cij.x), hi4(cij.x), lo4(cij.y), hi4(cij.y)};
-  const int mi[2] = {lo4(cii.x), hi4(cii.y)}, mj[2] = {lo4(cjj.x), hi4(cjj.y)};
-  int fij[9];
-  pair_cells(aij, mi, mj, n1x4, fij);
+  int fij[9];  // the pair (i, j) of this phenotype's cases, x 4
+  {
+    auto lo4 = [](unsigned v) { return (int)((v & 0xffffu) << 2); };
+    auto hi4 = [](unsigned v) { return (int)((v >> 16) << 2); };
+    const int aij[4] = {lo4(cij.x), hi4(cij.x), lo4(cij.y), hi4(cij.y)};
+    const int mi[2] = {lo4(cii.x), hi4(cii.y)}, mj[2] = {lo4(cjj.x), hi4(cjj.y)};
+    pair_cells(aij, mi, mj, n1x4, fij);
+  }
   const int64_t base = lex_base(M, i, j) + k0;
-  // rows k0 .. k0 + 15 lie below the padded stride Mp (k0 + 15 < M + 16):
-  // loaded for every k, used for k in (j, M) only; one k ahead, through
-  // uniform row pointers advanced by one k per step
-  gptr<u2e> pik = cp_row(i, k0), pjk = cp_row(j, k0), pkk = cp_row(k0, k0);
-  const int64_t dkk = (int64_t)(Mp + 1) * Qp;
-  u2e cik_n = pik[qc], cjk_n = pjk[qc], ckk_n = pkk[qc];
+  uint32_t two = 2u;
+  asm volatile("" : "+v"(two));
+  float *sc = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(rows) + kScoreRows);
 #pragma unroll
-  for (int tt = 0; tt < kPermT; ++tt)
+  for (int p = 0; p < kPermKB / 2; ++p) {
+    const Rows cur[2] = {next[0], next[1]};
+    if (p + 1 < kPermKB / 2) {
+      pik += 2 * Qp;
+      pjk += 2 * Qp;
+      pkk += 2 * dkk;
+      next[0] = {pik[q], pjk[q], pkk[q]};
+      next[1] = {pik[Qp + q], pjk[Qp + q], pkk[dkk + q]};
+    }
+    if (2 * p + 1 < kk_lo || 2 * p >= kk_hi) continue;  // wave-uniform
+    uint32_t up[2], down[2] = {0u, 0u};
+    Lookups in_flight[2];
+    auto add_up = [&](int n) {  // the lookups of step n
+      const Lookups &l = in_flight[n & 1];
+      uint32_t &d = down[n / 9];
+      d += l.d0[0] + l.d1[0];
+      d += l.d0[1] + l.d1[1];
+      d += l.d0[2] + l.d1[2];
+      asm volatile("" : "+v"(d));  // (keeps the additions of different steps apart)
+    };
 #pragma unroll
-    for (int t4 = 0; t4 < 4; ++t4) {
-      const int kk = 4 * tt + t4;
-      const u2e cik = cik_n, cjk = cjk_n, ckk = ckk_n;
-      if (kk + 1 < kPermKB) {
-        pik += Qp;
-        pjk += Qp;
-        pkk += dkk;
-        cik_n = pik[qc];
-        cjk_n = pjk[qc];
-        ckk_n = pkk[qc];
-      }
-      if (kk < kk_lo || kk >= kk_hi) continue;  // wave-uniform
-      int c4[27];
-      {
-        uint32_t cn[8];  // corner index 4 a + 2 b + c, x 4
-#pragma unroll
-        for (int ab = 0; ab < 4; ++ab) {
-          const uint32_t w = cc[tt][4 * t4 + ab];
-          cn[2 * ab] = (w << 2) & 0x3fffcu;
-          cn[2 * ab + 1] = (w >> 14) & 0x3fffcu;
-        }
-        const int aik[4] = {lo4(cik.x), hi4(cik.x), lo4(cik.y), hi4(cik.y)};
-        const int ajk[4] = {lo4(cjk.x), hi4(cjk.x), lo4(cjk.y), hi4(cjk.y)};
-        const int mk[2] = {lo4(ckk.x), hi4(ckk.y)};
-        complete_ij(cn, fij, aik, ajk, mk, c4);
-      }
-      // cells x 4 in words 0..26, the sum of their L[cell + 1] in word 27
-      // (same address in all lanes: broadcast reads), four rows at a time
+    for (int h = 0; h < 2; ++h) {
+      const int kk = 2 * p + h, tt = kk >> 2, t4 = kk & 3;
+      uint32_t ta[28];
       const uint4 *rk = reinterpret_cast<const uint4 *>(rows + kk * 28);
-      uint32_t up = 0u, down = 0u;  // sums of L[r + 1] and of L[r_0] + L[r_1], r_1 = cases
 #pragma unroll
-      for (int x4 = 0; x4 < 7; ++x4) {
-        const uint4 tv = rk[x4];
-        const uint32_t ta[4] = {tv.x, tv.y, tv.z, tv.w};
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-          const int x = 4 * x4 + y;
-          if (x < 27) {
-            const int r0 = (int)ta[y] - c4[x];
-            down += fx_at_lds0(r0) + fx_at_lds0(c4[x]);
-          } else {
-            up = ta[y];
-          }
-        }
+      for (int x = 0; x < 7; ++x) {
+        const uint4 w = rk[x];
+        ta[4 * x] = w.x; ta[4 * x + 1] = w.y; ta[4 * x + 2] = w.z; ta[4 * x + 3] = w.w;
       }
-      const float k2 = fx_score(up - down, scale);
+      up[h] = ta[27];
+      const u16x2 vik[2] = {as_u16x2(cur[h].ik.x), as_u16x2(cur[h].ik.y)};
+      const u16x2 vjk[2] = {as_u16x2(cur[h].jk.x), as_u16x2(cur[h].jk.y)};
+      // (i, k) with genotype 2 at i; the diagonal entry holds k's counts in
+      // its low .x and high .y halves
+      const u16x2 vik2 = as_u16x2(cur[h].kk.x | cur[h].kk.y) - vik[0] - vik[1];
+      u16x2 t[9];  // rows (a, b): genotypes 0 and 1 of k
+#pragma unroll
+      for (int sx = 0; sx < 9; ++sx) {
+        constexpr int order[9] = {0, 1, 3, 4, 2, 5, 6, 7, 8};
+        const int ab = order[sx], ga = ab / 3, gb = ab % 3;
+        if (ga < 2 && gb < 2)
+          t[ab] = as_u16x2(cc[tt][4 * t4 + 2 * ga + gb]);
+        else if (ga < 2)
+          t[ab] = vik[ga] - t[3 * ga] - t[3 * ga + 1];
+        else if (gb < 2)
+          t[ab] = vjk[gb] - t[gb] - t[3 + gb];
+        else
+          t[ab] = vik2 - t[6] - t[7];
+        const uint32_t v = as_u32(t[ab]);
+        uint32_t c[3];
+        c[0] = lo_x4(v, two);
+        c[1] = (v >> 16) << 2;
+        c[2] = (uint32_t)fij[ab] - c[0] - c[1];
+        const int n = 9 * h + sx;
+        if (n >= 2) add_up(n - 2);
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+          in_flight[n & 1].d0[x] = fx_at_lds0((int)(ta[3 * ab + x] - c[x]));
+          in_flight[n & 1].d1[x] = fx_at_lds0((int)c[x]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    add_up(16);
+    add_up(17);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int kk = 2 * p + h;
+      if (kk < kk_lo || kk >= kk_hi) continue;  // wave-uniform
+      const float k2 = fx_score(up[h] - down[h], scale);
       const uint32_t key = f2key(k2);
       kmin = key < kmin ? key : kmin;
       kmax = key > kmax ? key : kmax;
-      if (FUSE == kPermOutSample && q < Q)
+      if (FUSE == kFusePlane) sc[kk * 64 + q] = k2;
+      if (FUSE == kFuseSample && q < Q)
         out.sample[(int64_t)q * out.sample_T + (out.sample_base + slot) * 64 + wave * kPermKB + kk] = k2;
-      if (FUSE == kPermOutBounded && q < Q && k2 <= ubq) {
+      if (FUSE == kFuseBounded && q < Q && k2 <= ubq) {
         const unsigned long long pos = atomicAdd(&st[q].cn, 1ull);
         if ((int64_t)pos < out.ccap) {
           out.ckey[(int64_t)q * out.ccap + pos] = key;
           out.crank[(int64_t)q * out.ccap + pos] = base + kk;
         }
       }
-      __builtin_amdgcn_sched_barrier(0);  // one k at a time: short live ranges
     }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if constexpr (FUSE == kFusePlane) {
+    // scores of phenotype qq at ranks base + kk, 64-byte runs
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int e0 = 0; e0 < kPermKB * 64; e0 += 64) {
+      const int e = e0 + q, qq = e / kPermKB, kk = e % kPermKB;
+      if (qq < Q && kk >= kk_lo && kk < kk_hi) pj.score[(int64_t)qq * pj.T + base + kk] = sc[kk * 64 + qq];
+    }
+  }
 }
 
-// FUSE = kPermOutSample / kPermOutBounded (FP4 only): each wave completes
+// FUSE = kFuse* (FP4 only): each wave completes
 // and scores its own pivot's 16 x 64 (triplet, phenotype) tables right after
 // the tile's counts, from the accumulators (as the finish kernel does from
 // the corner scratch), with the log-factorial table at LDS address 0;
@@ -560,6 +634,9 @@ __device__ __forceinline__ void count_perm_body(
       offa = (uint32_t)(((int64_t)ii * 2 + ((x >> 1) & 1)) * S + col);
       offb = (uint32_t)(((int64_t)j * 2 + (x & 1)) * S + col);
     }
+    // LDS row of a staged row: the k rows lie in the order in which the lanes
+    // of a row tile read them (rows 36 words apart: no bank conflict among 16)
+    auto lds_row = [](int row) { return row < kRowsPH ? row : kRowsPH + k_lds_row((row - kRowsPH) >> 1, row & 1); };
     v4i pf[kMainU], pa, pb;
     auto fetch = [&](int ch) {
       const uint32_t c0 = (uint32_t)ch * kKC;
@@ -581,7 +658,7 @@ __device__ __forceinline__ void count_perm_body(
 #pragma unroll
       for (int u = 0; u < kMainU; ++u) {
         const int c16 = tid + 256 * u;
-        *reinterpret_cast<v4i *>(dst + (c16 / kPc) * kRow + (c16 % kPc) * 16) = pf[u];
+        *reinterpret_cast<v4i *>(dst + lds_row(c16 / kPc) * kRow + (c16 % kPc) * 16) = pf[u];
       }
       if (tid < kPairPieces)
         *reinterpret_cast<v4i *>(dst + (96 + tid / kPc) * kRow + (tid % kPc) * 16) = pa & pb;
@@ -593,7 +670,7 @@ __device__ __forceinline__ void count_perm_body(
     for (int tt = 0; tt < kPermT; ++tt) {
       tot[tt] = 0u;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[tt][0][v] = acc[tt][1][v] = 0;
+      for (int v = 0; v < 16; ++v) acc[tt][0][v] = acc[tt][1][v] = FUSE ? 8388608 : 0;  // 2^23
     }
     // FP4: the all-sample corner counts of the tile are one 16 x 16 product
     // per k half: rows = the 16 pair rows (4 pivots x (a, b)), columns = 8 k
@@ -602,13 +679,14 @@ __device__ __forceinline__ void count_perm_body(
     v4f tacc = {0.f, 0.f, 0.f, 0.f};
     const int tkh = wave & 1, tsh = wave >> 1;
     const int o_ta = (kRowsPH + kRowsXK + (lane & 15)) * kRow + 64 * tsh + 16 * (lane >> 4);
-    const int o_tb = (kRowsPH + 16 * tkh + (lane & 15)) * kRow + 64 * tsh + 16 * (lane >> 4);
+    const int o_tb = (kRowsPH + k_lds_row(8 * tkh + ((lane & 15) >> 1), lane & 1)) * kRow + 64 * tsh +
+                     16 * (lane >> 4);
     v4i tA, tB;
     fetch(0);
     store(0);
     __syncthreads();
     const int prow = kRowsPH + kRowsXK + wave * 4 + (ra * 2 + rb);
-    const int xrow = kRowsPH + (4 * (r & 3) + ta) * 2 + rc;  // k row of row tile r % 4
+    const int xrow = kRowsPH + k_lds_row(4 * (r & 3) + ta, rc);  // k row of row tile r % 4: row r
     // Software pipeline over the steps of a chunk: while the matrix products
     // of step s run, the operands of step s + 1 are read from LDS (two
     // register sets, X and Y, taken in turn), and each row tile's A rows are
@@ -739,7 +817,7 @@ __device__ __forceinline__ void count_perm_body(
     if constexpr (FUSE != 0) {
       // the staging buffers are idle until the next tile's first store
       __builtin_amdgcn_s_setprio(0);
-      fused_score<FUSE>(pj, acc, sT16[wave], reinterpret_cast<uint32_t *>(stage + wave * 4096), st,
+      fused_score<FUSE>(pj, acc, sT16[wave], reinterpret_cast<uint32_t *>(stage + wave * kScorePart), st,
                         out, scale, i, j, kbase, slot, wave, lane, kmin, kmax);
       continue;
     }
@@ -1143,6 +1221,9 @@ hipError_t launch_count_score_perm(const PermJob *pj_dev, int64_t tile_begin, in
                                    const uint32_t *lfx, int32_t lf_len, float scale, const PermOut &out,
                                    hipStream_t s) {
   if (!perm_fused_ok(lf_len)) return hipErrorInvalidValue;
+  if (out.mode == kPermOutPlane)
+    return launch_count_t<true, kFusePlane>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
+                                            lf_len, scale, out, s);
   if (out.mode == kPermOutSample)
     return launch_count_t<true, kPermOutSample>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
                                                 lf_len, scale, out, s);

@@ -146,7 +146,9 @@ struct PlainAcc<true> {
   static __device__ __forceinline__ type mma(v4i a, v4i b, type c) {
     const v8i a8 = {a.x, a.y, a.z, a.w, 0, 0, 0, 0};
     const v8i b8 = {b.x, b.y, b.z, b.w, 0, 0, 0, 0};
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 4, 4, 0, 127, 0, 127);
+    // FP4 operands; scale operands of constant 0 select the instruction form
+    // without the scale prefix (unit scales), one issue slot less per product
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 4, 4, 0, 0, 0, 0);
   }
   static __device__ __forceinline__ uint32_t get(const type &c, int v) { return (uint32_t)c[v]; }
 };
@@ -432,15 +434,6 @@ __device__ __forceinline__ void flush_range(uint32_t kmin, uint32_t kmax, uint32
   }
 }
 
-// 4 x the low half of v.
-__device__ __forceinline__ uint32_t lo_x4(uint32_t v, uint32_t two) {
-  uint32_t r;
-  asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
-      : "=v"(r)
-      : "v"(two), "v"(v));
-  return r;
-}
-
 // Three rows' lookups in the table at LDS address 0: L[r + 1], L[r_0], L[r_1]
 // of rows held as (class-0 count | all << 16).
 struct Lookups {
@@ -510,15 +503,19 @@ constexpr int32_t plain_fused_entries() {
 // while this one is scored.
 //
 // Two waves per SIMD (227-231 registers), one of each workgroup, so one can
-// count while the other scores.  What bounds it, per 64 triplets: N / 16
-// cycles of matrix products, about 230 (2500 samples) to 330 (16384) cycles
-// of LDS lookups beside the count's own LDS reads (5/8 of its product time),
-// and 206 vector instructions of scoring; at 3100 x 2500 the LDS is busy 66%
-// of the time, the vector ALU 59%, the matrix cores 31%; at 2048 x 16384 the
-// matrix cores 56%.  Against the two-kernel path (32 bytes per triplet and
-// class through HBM, the scoring waiting on them): 2048 x 16384 84.1 ->
-// 71.8 ms, 3100 x 2500 112.5 -> 76.1 ms, 1003 x 6007 6.07 -> 5.09 ms, 32
-// uneven data sets 72.6 -> 65.8 ms.
+// count while the other scores.  A lone wave issues one vector instruction
+// per 8 cycles and one lookup per 12 (measured with independent chains; two
+// waves on a SIMD share 2.7 cycles per vector instruction), so with one
+// scoring wave per SIMD the instructions of a triplet (206 vector, 83 LDS)
+// cost about 2600 cycles per 64, whatever the LDS and the vector ALU could do
+// together: at 3100 x 2500 the LDS is busy 66% of the time, the vector ALU 59%,
+// the matrix cores 31%.  The scoring wave therefore goes first (priority 1).
+// The X_i rows of both i-blocks are read from LDS instead of one read and
+// eight lane permutations (16 vector instructions per 8 products instead of
+// 24: 2048 x 16384 70.9 -> 69.4 ms).  Against the two-kernel path (32 bytes
+// per triplet and class through HBM, the scoring waiting on them):
+// 2048 x 16384 84.1 -> 69.4 ms, 3100 x 2500 112.5 -> 73.7 ms, 512 x 4096 1.06
+// -> 0.87 ms, 1003 x 6007 6.07 -> 5.09 ms, 32 uneven data sets 72.6 -> 65.8 ms.
 template <int JB, bool TRUNC, int MODE>
 __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
     const PlainJob *__restrict__ jobs, const int64_t *__restrict__ job_begin_p, int n_jobs,
@@ -561,7 +558,7 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
   uint4 *stash = stash_p + (int64_t)blockIdx.x * (kPlainStash / 16) + wave * 1024;  // [16][lane]
   // lane roles: A row r = 4 i8 + 2 a + b; B column r = k (one plane per tile)
   const int ra = (r >> 1) & 1, rb = r & 1;
-  const int o_xi = r * kPRow + 16 * g;
+  const int o_xi = (r & ~1) * kPRow + 16 * g;  // i-block 0; block 1 is the next row
   const int o_xj = (kRowsI + 2 * (2 * wj + ra) + rb) * kPRow + 16 * g;
   const int o_b0 = (kRowsI + kRowsJ + 32 * wb + r) * kPRow + 16 * g;
   const int o_b1 = o_b0 + KT * kPRow + kPlanePad;
@@ -713,12 +710,13 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
     __syncthreads();
 #define EPI3_PLD(BB, STP, XI, XJ, B0, B1)                                           \
     XI = *reinterpret_cast<const v4i *>((BB) + o_xi + 32 * (STP));                \
+    XI##1 = *reinterpret_cast<const v4i *>((BB) + o_xi + kPRow + 32 * (STP));     \
     XJ = *reinterpret_cast<const v4i *>((BB) + o_xj + 32 * (STP));                \
     B0 = *reinterpret_cast<const v4i *>((BB) + o_b0 + 32 * (STP));                \
     B1 = *reinterpret_cast<const v4i *>((BB) + o_b1 + 32 * (STP));
 #define EPI3_PSTEP(XI, XJ, B0, B1)                                                  \
     {                                                                             \
-      const v4i xi_[2] = {quad_perm<0xA0>(XI), quad_perm<0xF5>(XI)};              \
+      const v4i xi_[2] = {XI, XI##1};                                         \
       _Pragma("unroll") for (int x = 0; x < 2; ++x) {                             \
         const v4i a0 = xi_[x] & quad_perm<0x44>(XJ);                              \
         acc[x][0][0] = Acc::mma(a0, B0, acc[x][0][0]);                            \
@@ -731,7 +729,7 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
     __builtin_amdgcn_sched_barrier(0);
     // software pipeline over the steps of a chunk (operand sets X and Y in
     // turn; the next chunk is stored before the last step)
-    v4i xiX, xjX, b0X, b1X, xiY, xjY, b0Y, b1Y;
+    v4i xiX, xiX1, xjX, b0X, b1X, xiY, xiY1, xjY, b0Y, b1Y;
     EPI3_PLD(stage, 0, xiX, xjX, b0X, b1X)
     for (int ch = 0; ch < nch; ++ch) {
       const bool more = ch + 1 < nch;

@@ -547,6 +547,14 @@ __device__ __forceinline__ uint32_t fx_at(const uint32_t *L, int b) {
 __device__ __forceinline__ uint32_t fx_at_lds0(int b) {
   return *(const __attribute__((address_space(3))) uint32_t *)(uintptr_t)(uint32_t)b;
 }
+// 4 x the low half of v (two: a register holding 2).
+__device__ __forceinline__ uint32_t lo_x4(uint32_t v, uint32_t two) {
+  uint32_t r;
+  asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
+      : "=v"(r)
+      : "v"(two), "v"(v));
+  return r;
+}
 // K2 of a table of R rows given as byte offsets (4 x count), in fixed point:
 // sum over rows of L[r + 1] - L[r_0] - L[r_1].  LDS: table at LDS address 0.
 template <int R, bool LDS>
@@ -651,7 +659,7 @@ hipError_t launch_count_mfma_perm(const PermJob *pj_dev, int64_t tile_begin, int
 hipError_t launch_finish_perm(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
                               int64_t stride, SelState *st, const uint32_t *lfx, int32_t lf_len,
                               float scale, const PermOut &out, hipStream_t s);
-// Count and score in one kernel (FP4 operands, sample or bounded output, the
+// Count and score in one kernel (FP4 operands, any output mode, the
 // log-factorial table of lf_len entries in LDS: perm_fused_ok); no scratch.
 bool perm_fused_ok(int32_t lf_len);
 hipError_t launch_count_score_perm(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
