@@ -959,8 +959,8 @@ int epi3_encode(const uint8_t *geno_dev, int64_t ld, const uint8_t *pheno_host, 
     HIP_OK(launch_encode_values(geno_dev, ld, L.list, 0, n0, L.W0 * 32, n1, 2, n_snps, L.Mp, L.S,
                                 L.bytes, L.nibbles, s));
   const int prc = timed(4, s, [&]() {
-    return launch_pairs(L.planes, L.Mp, n_snps, L.W0, layout == EPI3_LAYOUT_SPLIT ? L.W1 : 0,
-                        L.classes, nullptr, L.pairs, s) == hipSuccess
+    return launch_pairs(L.planes, L.Mp, L.W0, layout == EPI3_LAYOUT_SPLIT ? L.W1 : 0, L.classes,
+                        L.pairs, s) == hipSuccess
                ? EPI3_OK
                : EPI3_E_HIP;
   });

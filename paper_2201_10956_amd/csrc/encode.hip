@@ -146,53 +146,163 @@ __global__ void __launch_bounds__(256) encode_values_kernel(
 }
 
 // Pairwise tables out[c][x][y] = (n00, n01, n10, n11), n_ab = number of
-// samples of class c with genotype a at SNP x and b at SNP y (a, b in {0, 1}),
-// by AND + POPCNT over the class's words (the MASKED layout's case tables
-// restrict x to the mask's samples).  The diagonal holds the per-SNP counts
-// (n_x(0), 0, 0, n_x(1)).  Workgroup tile: 64 x by 64 y, 16 x per
-// wave read as wave-uniform scalars, y = lane; a word of y planes feeds 64
-// AND + 64 popcounts.  Only tiles on or above the diagonal count; each writes
-// (x, y) and its mirror (y, x) = (n00, n10, n01, n11).
-constexpr int kPairX = 16;  // x rows per wave
+// samples of class c with genotype a at SNP x and b at SNP y (a, b in {0, 1}).
+// The diagonal holds the per-SNP counts (n_x(0), 0, 0, n_x(1)).
+//
+// A product of the plane rows with themselves over the class's samples, on
+// v_mfma_f32_32x32x64_f8f6f4: lane l supplies row l % 32 (SNP r / 2, plane
+// r % 2; a word's planes of consecutive SNPs are contiguous, so a load is two
+// 128-byte runs) and the 32 samples of word l / 32 of the step.  A word
+// becomes its 32 E2M1 nibbles by three shifts and four masks: operand dword t
+// takes the samples whose bit is t modulo 4, the same for both operands.  FP32
+// accumulation is exact below 2^24: segments of kPairSegment words are added
+// to the stored counts one after the other.
+//
+// Only tiles on or above the diagonal count; the others are written as
+// mirrors, (y, x) = (n00, n10, n01, n11).  RT = 2: workgroup tile 64 x 64
+// SNPs, wave 32 x 32 (four products per four operand loads).  RT = 1, where
+// those tiles would leave most CUs idle: workgroup tile 16 x 16 SNPs, the
+// words split over the four waves and the counts added through LDS.  Whole
+// encodes without value planes, popcounts of 64 x 64 tiles -> products: 64 x
+// 1024 56 -> 43 us, 512 x 4096 124 -> 80 us (RT = 2 there: 83), 1003 x 6007 169
+// -> 96 us, 2048 x 16384 524 -> 219 us (RT = 1 there: 273; 1400 SNPs: 85 against
+// 90).  At 2048 SNPs the products take about 35 us and writing the 134 MB of
+// tables about 30 us.
+constexpr int kPairSegment = 1 << 18;  // words: 2^23 samples
+constexpr int64_t kPairSmall = 256;     // fewer 64 x 64 tiles: RT = 1
+constexpr int kPairAhead = 4;          // steps loaded ahead of the products
 
-__global__ void __launch_bounds__(256) pairs_kernel(const uint32_t *__restrict__ planes, int32_t Mp,
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// The E2M1 nibbles (0 or 1.0) of a word's 32 samples.
+__device__ __forceinline__ v8i fp4_of_bits(uint32_t w) {
+  const uint32_t m = 0x22222222u;
+  return v8i{(int)((w << 1) & m), (int)(w & m), (int)((w >> 1) & m), (int)((w >> 2) & m), 0, 0, 0, 0};
+}
+
+template <int RT>
+__global__ void __launch_bounds__(256, 3) pairs_kernel(const uint32_t *__restrict__ planes, int32_t Mp,
                                                     int32_t W0, int32_t W1,
-                                                    const uint32_t *__restrict__ mask,
                                                     int32_t *__restrict__ pairs) {
-  const int xb = blockIdx.y, yb = blockIdx.x;
-  if (yb < xb) return;  // below the diagonal: written as mirrors
-  const int lane = threadIdx.x & 63;
-  const int x0 = __builtin_amdgcn_readfirstlane(xb * 64 + (threadIdx.x >> 6) * kPairX);
-  const int y = yb * 64 + lane;
-  const int c = blockIdx.z;
-  const int w0 = c == 0 ? 0 : W0;
-  const int w1 = c == 0 ? W0 : W0 + W1;
-  uint32_t acc[kPairX][4];
-#pragma unroll
-  for (int r = 0; r < kPairX; ++r) acc[r][0] = acc[r][1] = acc[r][2] = acc[r][3] = 0u;
-  cptr<uint32_t> pc = as_const(planes);
-  const uint2 *pv = reinterpret_cast<const uint2 *>(planes);
-  for (int w = w0; w < w1; ++w) {
-    const uint2 yv = pv[(int64_t)w * Mp + y];
-    const uint32_t mk = mask ? as_const(mask)[w] : 0xffffffffu;
-    cptr<uint32_t> xr = pc + ((int64_t)w * Mp + x0) * 2;
-#pragma unroll
-    for (int r = 0; r < kPairX; ++r) {
-      const uint32_t a0 = xr[2 * r] & mk, a1 = xr[2 * r + 1] & mk;
-      acc[r][0] += __builtin_popcount(a0 & yv.x);
-      acc[r][1] += __builtin_popcount(a0 & yv.y);
-      acc[r][2] += __builtin_popcount(a1 & yv.x);
-      acc[r][3] += __builtin_popcount(a1 & yv.y);
-    }
-  }
+  constexpr int kSnps = 16 * RT;             // SNPs of a wave's rows and columns
+  constexpr int kTile = RT == 2 ? 64 : 16;   // SNPs of a workgroup's
+  __shared__ float part[RT == 1 ? 4 : 1][RT == 1 ? 16 : 1][64];
+  const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // tile of the upper triangle, column by column: blockIdx.x = yb (yb + 1) / 2 + xb
+  int yb = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
+  while (yb * (yb + 1) / 2 > (int)blockIdx.x) --yb;
+  while ((yb + 1) * (yb + 2) / 2 <= (int)blockIdx.x) ++yb;
+  const int xb = (int)blockIdx.x - yb * (yb + 1) / 2;
+  const int x0 = xb * kTile + (RT == 2 ? kSnps * (wave >> 1) : 0);
+  const int y0 = yb * kTile + (RT == 2 ? kSnps * (wave & 1) : 0);
+  if (y0 < x0) return;  // RT = 2, diagonal tile: no barriers there
+  const int c = blockIdx.y;
+  const int wb = c == 0 ? 0 : W0, we = c == 0 ? W0 : W0 + W1;
+  const int64_t stride = (int64_t)Mp * 2;  // dwords of a word's planes
   int4 *out = reinterpret_cast<int4 *>(pairs) + (int64_t)c * Mp * Mp;
+  int seg = wb;
+  do {
+    const int seg_end = we - seg > kPairSegment ? seg + kPairSegment : we;
+    // this wave's steps of two words
+    int s = seg, e = seg_end;
+    if (RT == 1) {
+      const int per = (((seg_end - seg + 1) / 2 + 3) / 4) * 2;
+      s = seg + wave * per;
+      e = s + per < seg_end ? s + per : seg_end;
+    }
+    v16f acc[RT][RT];
 #pragma unroll
-  for (int r = 0; r < kPairX; ++r) {
-    const int x = x0 + r;
-    out[(int64_t)x * Mp + y] = make_int4((int)acc[r][0], (int)acc[r][1], (int)acc[r][2], (int)acc[r][3]);
-    if (y != x)
-      out[(int64_t)y * Mp + x] = make_int4((int)acc[r][0], (int)acc[r][2], (int)acc[r][1], (int)acc[r][3]);
-  }
+    for (int a = 0; a < RT; ++a)
+#pragma unroll
+      for (int b = 0; b < RT; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+    uint32_t px[kPairAhead][RT], py[kPairAhead][RT];
+    const uint32_t *bx = planes + 2 * x0 + r, *by = planes + 2 * y0 + r;
+    auto load = [&](int w) {  // words w .. w + 2 kPairAhead - 1, zero past e
+#pragma unroll
+      for (int t = 0; t < kPairAhead; ++t) {
+        const int wl = w + 2 * t + h;
+        const int64_t o = (int64_t)(wl < e ? wl : e - 1) * stride;
+#pragma unroll
+        for (int a = 0; a < RT; ++a) {
+          px[t][a] = bx[o + 32 * a];
+          py[t][a] = by[o + 32 * a];
+        }
+      }
+    };
+    if (s < e) load(s);
+    for (; s < e; s += 2 * kPairAhead) {
+      uint32_t cx[kPairAhead][RT], cy[kPairAhead][RT];
+#pragma unroll
+      for (int t = 0; t < kPairAhead; ++t)
+#pragma unroll
+        for (int a = 0; a < RT; ++a) {
+          cx[t][a] = s + 2 * t + h < e ? px[t][a] : 0u;
+          cy[t][a] = py[t][a];
+        }
+      if (s + 2 * kPairAhead < e) load(s + 2 * kPairAhead);
+#pragma unroll
+      for (int t = 0; t < kPairAhead; ++t) {
+        v8i fx[RT], fy[RT];
+#pragma unroll
+        for (int a = 0; a < RT; ++a) {
+          fx[a] = fp4_of_bits(cx[t][a]);
+          fy[a] = fp4_of_bits(cy[t][a]);
+        }
+#pragma unroll
+        for (int a = 0; a < RT; ++a)
+#pragma unroll
+          for (int b = 0; b < RT; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fx[a], fy[b], acc[a][b], 4,
+                                                                        4, 0, 0, 0, 0);
+      }
+    }
+    // Registers 4 g .. 4 g + 3 of lane (column q = (y, b), half h): rows
+    // (x, a = 0, 1), (x + 1, a = 0, 1) with x = 4 g + 2 h; the lanes of a
+    // column pair exchange two of them, then each has one pair's four cells.
+    auto put = [&](int a, int b, int g, float v0, float v1, float v2, float v3) {
+      const bool odd = r & 1;
+      const uint32_t u0 = (uint32_t)v0, u1 = (uint32_t)v1, u2 = (uint32_t)v2, u3 = (uint32_t)v3;
+      const uint32_t k0 = odd ? u2 : u0, k1 = odd ? u3 : u1;
+      const uint32_t r0 = __builtin_amdgcn_mov_dpp(odd ? u0 : u2, 0xB1, 0xf, 0xf, true);
+      const uint32_t r1 = __builtin_amdgcn_mov_dpp(odd ? u1 : u3, 0xB1, 0xf, 0xf, true);
+      const int x = x0 + 16 * a + 4 * g + 2 * h + (odd ? 1 : 0), y = y0 + 16 * b + (r >> 1);
+      int4 n = odd ? make_int4((int)r0, (int)k0, (int)r1, (int)k1)
+                   : make_int4((int)k0, (int)r0, (int)k1, (int)r1);
+      int4 *o = out + (int64_t)x * Mp + y;
+      if (seg != wb) {
+        const int4 p = *o;
+        n.x += p.x; n.y += p.y; n.z += p.z; n.w += p.w;
+      }
+      *o = n;
+      if (x0 != y0) out[(int64_t)y * Mp + x] = make_int4(n.x, n.z, n.y, n.w);
+    };
+    if constexpr (RT == 1) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) part[wave][v][lane] = acc[0][0][v];
+      __syncthreads();
+      float t[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        t[v] = part[0][4 * wave + v][lane] + part[1][4 * wave + v][lane] +
+               part[2][4 * wave + v][lane] + part[3][4 * wave + v][lane];
+      put(0, 0, wave, t[0], t[1], t[2], t[3]);
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int a = 0; a < RT; ++a)
+#pragma unroll
+        for (int b = 0; b < RT; ++b)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            put(a, b, g, acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2],
+                acc[a][b][4 * g + 3]);
+    }
+    seg = seg_end;
+  } while (seg < we);
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int64_t n) {
@@ -259,12 +369,18 @@ hipError_t launch_encode_values(const uint8_t *geno, int64_t ld, const int32_t *
   return hipGetLastError();
 }
 
-hipError_t launch_pairs(const uint32_t *planes, int32_t Mp, int32_t M, int32_t W0, int32_t W1,
-                        int32_t n_classes, const uint32_t *mask, int32_t *pairs, hipStream_t s) {
-  (void)M;
-  if (Mp % 64 != 0) return hipErrorInvalidValue;  // tiles of 64 x 64 SNPs cover the stride exactly
-  dim3 grid(Mp / 64, Mp / 64, n_classes);
-  hipLaunchKernelGGL(pairs_kernel, grid, dim3(256), 0, s, planes, Mp, W0, W1, mask, pairs);
+hipError_t launch_pairs(const uint32_t *planes, int32_t Mp, int32_t W0, int32_t W1,
+                        int32_t n_classes, int32_t *pairs, hipStream_t s) {
+  if (Mp % 64 != 0) return hipErrorInvalidValue;  // tiles cover the stride exactly
+  const int64_t n = Mp / 64;
+  if (n * (n + 1) / 2 * n_classes >= kPairSmall) {
+    hipLaunchKernelGGL(pairs_kernel<2>, dim3((unsigned)(n * (n + 1) / 2), n_classes), dim3(256), 0, s,
+                       planes, Mp, W0, W1, pairs);
+  } else {
+    const int64_t m = Mp / 16;
+    hipLaunchKernelGGL(pairs_kernel<1>, dim3((unsigned)(m * (m + 1) / 2), n_classes), dim3(256), 0, s,
+                       planes, Mp, W0, W1, pairs);
+  }
   return hipGetLastError();
 }
 

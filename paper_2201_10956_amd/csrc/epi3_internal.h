@@ -591,8 +591,8 @@ hipError_t launch_encode_values(const uint8_t *geno, int64_t ld, const int32_t *
                                 int32_t len0, int32_t off1, int32_t len1, int32_t classes,
                                 int32_t M, int32_t Mp, int32_t S, uint8_t *bytes, uint8_t *nib,
                                 hipStream_t s);
-hipError_t launch_pairs(const uint32_t *planes, int32_t Mp, int32_t M, int32_t W0, int32_t W1,
-                        int32_t n_classes, const uint32_t *mask, int32_t *pairs, hipStream_t s);
+hipError_t launch_pairs(const uint32_t *planes, int32_t Mp, int32_t W0, int32_t W1,
+                        int32_t n_classes, int32_t *pairs, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 // lf32[x] = fl32(lf64[x]) and lfx[x] = round(2^shift lf64[x]) mod 2^32, x < n.
 hipError_t launch_log_tables(const double *lf64, float *lf32, uint32_t *lfx, int64_t n, int shift,
