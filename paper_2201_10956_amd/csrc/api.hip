@@ -946,21 +946,15 @@ int epi3_encode(const uint8_t *geno_dev, int64_t ld, const uint8_t *pheno_host, 
   const LfTables *lt = log_factorial_tables((int64_t)n_samples + 1);
   const size_t n_lf = (size_t)n_samples + 2;  // L[0 .. n_samples + 1]
 
-  HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(L.status), 0u, 64, s));
   HIP_OK(hipMemcpyAsync(L.list, list.data(), list.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
   HIP_OK(hipMemcpyAsync(L.lf64, lt->L64.data(), n_lf * sizeof(double), hipMemcpyHostToDevice, s));
-  HIP_OK(launch_log_tables(L.lf64, L.lf32, L.lfx, (int64_t)n_lf, fx_shift(n_samples), s));
-  HIP_OK(launch_encode(geno_dev, ld, L.list, n_snps, L.Mp, layout == EPI3_LAYOUT_SPLIT ? L.W0 : L.Wtot,
-                       layout == EPI3_LAYOUT_SPLIT ? L.W1 : 0, L.planes, L.status, s));
-  if (layout == EPI3_LAYOUT_MASKED)
-    HIP_OK(launch_encode_values(geno_dev, ld, L.list, 0, n_samples, 0, 0, 1, n_snps, L.Mp, L.S,
-                                L.bytes, L.nibbles, s));
-  else if (values)
-    HIP_OK(launch_encode_values(geno_dev, ld, L.list, 0, n0, L.W0 * 32, n1, 2, n_snps, L.Mp, L.S,
-                                L.bytes, L.nibbles, s));
+  HIP_OK(launch_log_tables(L.lf64, L.lf32, L.lfx, (int64_t)n_lf, fx_shift(n_samples), L.status, s));
+  const bool split = layout == EPI3_LAYOUT_SPLIT;
+  HIP_OK(launch_encode(geno_dev, ld, L.list, n_snps, L.Mp, split ? L.W0 : L.Wtot, split ? L.W1 : 0,
+                       L.classes, L.S, L.planes, values ? L.bytes : nullptr, values ? L.nibbles : nullptr,
+                       L.status, s));
   const int prc = timed(4, s, [&]() {
-    return launch_pairs(L.planes, L.Mp, L.W0, layout == EPI3_LAYOUT_SPLIT ? L.W1 : 0, L.classes,
-                        L.pairs, s) == hipSuccess
+    return launch_pairs(L.planes, L.Mp, L.W0, split ? L.W1 : 0, L.classes, L.pairs, s) == hipSuccess
                ? EPI3_OK
                : EPI3_E_HIP;
   });

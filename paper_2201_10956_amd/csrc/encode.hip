@@ -14,134 +14,128 @@ namespace epi3 {
 
 // planes[w][m][0..1]: bit b of word w = sample list[w * 32 + b] has genotype
 // 0 (plane 0) / 1 (plane 1).  list < 0 marks padding; padding bits stay 0 in
-// both planes.  SNP slots m >= M are zero.  One wave per SNP and group of 64
-// words: per step the 64 lanes read the genotype bytes of 64 consecutive
-// list positions (two words; within a class the list is in sample order, so
-// the reads fall in a few cache lines of the SNP's row) and two ballots form
-// both planes of both words.
-constexpr int kEncWords = 64;  // words per wave
+// both planes.  SNP slots m >= M are zero.  Words W0 .. W0 + W1 - 1 are class 1.
+// VALUES: the same bits as 0/1 values for the matrix cores, a row of S
+// positions per (class c, SNP m, genotype g): bytes[c][m][g][p] = 1 and
+// nib[c][m][g][p / 2] nibble = 0x2 (E2M1 1.0) where bit p of the class is set;
+// positions past the class's words are 0.
+//
+// One workgroup per 16 SNPs and WORDS words of a class.  A wave reads 64
+// consecutive list positions (two words) of four SNPs per step: within a class
+// the list is in sample order, so the byte loads fall in a few cache lines of
+// each SNP's row; two ballots per SNP form both planes of both words.  All
+// steps' list entries, then all genotypes, are in flight at once (a step alone
+// waits for the list entry, then for the genotype), so the kernel needs many
+// short workgroups rather than few long ones.  The bits are turned in LDS:
+// planes leave as 128-byte runs (16 SNPs), value rows as runs of 16 WORDS and
+// 32 WORDS bytes, and the genotypes are read once for all three.  WORDS = 8
+// until that makes kEncWide workgroups, 16 from there on.  Whole encodes with
+// value planes, one kernel per SNP and 64 words plus one per value plane ->
+// this: 64 x 1024 47 -> 37 us, 512 x 4096 94 -> 57 us (WORDS 16: 59, 64: 76),
+// 1003 x 6007 121 -> 75 us (80, 107), 2048 x 16384 306 -> 188 us (WORDS 8: 194).
+constexpr int kEncSnps = 16;
+constexpr int64_t kEncWide = 4096;  // workgroups
 
+// The E2M1 nibbles of bits 8 t .. 8 t + 7 of w, low nibble first.
+__device__ __forceinline__ uint32_t nibbles_of(uint32_t w, int t) {
+  uint32_t x = (w >> (8 * t)) & 0xffu;
+  x = (x | x << 12) & 0x000f000fu;
+  x = (x | x << 6) & 0x03030303u;
+  return ((x | x << 3) & 0x11111111u) << 1;
+}
+
+// The bytes of bits 4 t .. 4 t + 3 of w.
+__device__ __forceinline__ uint32_t bytes_of(uint32_t w, int t) {
+  return (((w >> (4 * t)) & 0xfu) * 0x00204081u) & 0x01010101u;
+}
+
+template <bool VALUES, int WORDS>
 __global__ void __launch_bounds__(256) encode_kernel(const uint8_t *__restrict__ geno, int64_t ld,
                                                      const int32_t *__restrict__ list, int32_t M,
-                                                     int32_t Mp, int32_t Wtot,
+                                                     int32_t Mp, int32_t W0, int32_t W1, int32_t S,
                                                      uint32_t *__restrict__ planes,
+                                                     uint32_t *__restrict__ bytes,
+                                                     uint32_t *__restrict__ nib,
                                                      int32_t *__restrict__ status) {
+  __shared__ uint2 bits[WORDS][kEncSnps + 1];
   const int lane = threadIdx.x & 63;
-  const int m = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  if (m >= Mp) return;
-  const int w0 = blockIdx.y * kEncWords;
-  const uint8_t *row = geno + (int64_t)(m < M ? m : 0) * ld;
-  uint2 *out = reinterpret_cast<uint2 *>(planes);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = blockIdx.z, W = c ? W1 : W0, off = c ? W0 : 0;
+  const int w0 = blockIdx.y * WORDS, m0 = blockIdx.x * kEncSnps;
+  uint32_t z0[4], z1[4], o0[4], o1[4];  // lane u: words 2 u and 2 u + 1 of the four SNPs
+#pragma unroll
+  for (int q = 0; q < 4; ++q) z0[q] = z1[q] = o0[q] = o1[q] = 0u;
   bool bad = false;
-  for (int w = w0; w < w0 + kEncWords && w < Wtot; w += 2) {
-    const int wl = w + (lane >> 5);  // this lane's word
-    int g = 3;                       // no genotype: padding, SNP slot >= M, word >= Wtot
-    if (m < M && wl < Wtot) {
-      const int sidx = list[(int64_t)wl * 32 + (lane & 31)];
-      if (sidx >= 0) {
-        g = row[sidx];
-        bad |= g > 2;
-      }
+  if (w0 < W && m0 + 4 * wave < M) {
+    int sidx[WORDS / 2];
+#pragma unroll
+    for (int u = 0; u < WORDS / 2; ++u) {
+      const int w = w0 + 2 * u + (lane >> 5);  // this lane's word
+      sidx[u] = w < W ? list[(int64_t)(off + w) * 32 + (lane & 31)] : -1;
     }
-    const unsigned long long z = __ballot(g == 0), o = __ballot(g == 1);
-    if (lane == 0) out[(int64_t)w * Mp + m] = make_uint2((uint32_t)z, (uint32_t)o);
-    if (lane == 32 && w + 1 < Wtot)
-      out[(int64_t)(w + 1) * Mp + m] = make_uint2((uint32_t)(z >> 32), (uint32_t)(o >> 32));
+    int g[WORDS / 2][4];
+#pragma unroll
+    for (int u = 0; u < WORDS / 2; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m = m0 + 4 * wave + q;
+        g[u][q] = 3;  // no genotype: padding, SNP slot >= M, word >= W
+        if (m < M && sidx[u] >= 0) {
+          g[u][q] = geno[(int64_t)m * ld + sidx[u]];
+          bad |= g[u][q] > 2;
+        }
+      }
+#pragma unroll
+    for (int u = 0; u < WORDS / 2; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const unsigned long long z = __ballot(g[u][q] == 0), o = __ballot(g[u][q] == 1);
+        const bool mine = lane == u;
+        z0[q] = mine ? (uint32_t)z : z0[q];
+        z1[q] = mine ? (uint32_t)(z >> 32) : z1[q];
+        o0[q] = mine ? (uint32_t)o : o0[q];
+        o1[q] = mine ? (uint32_t)(o >> 32) : o1[q];
+      }
   }
   if (__ballot(bad) != 0ull && lane == 0) atomicOr(status, 1);
-}
-
-// bytes[m][p][s] = 1 if sample s of SNP m has genotype p (p = 0, 1), else 0;
-// samples s >= N and SNPs m >= M are 0.  S is a multiple of 4.
-__global__ void __launch_bounds__(256) encode_bytes_kernel(const uint8_t *__restrict__ geno,
-                                                           int64_t ld, int32_t M, int32_t N,
-                                                           int32_t Mp, int32_t S,
-                                                           uint32_t *__restrict__ bytes) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;  // dword within a row
-  const int S4 = S >> 2;
-  if (q >= S4) return;
-  for (int m = blockIdx.y; m < Mp; m += gridDim.y) {
-    uint32_t v0 = 0, v1 = 0;
-    if (m < M) {
-      const uint8_t *row = geno + (int64_t)m * ld;
+  if (lane < WORDS / 2) {
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int s = 4 * q + b;
-        if (s < N) {
-          const uint32_t g = row[s];
-          v0 |= (uint32_t)(g == 0u) << (8 * b);
-          v1 |= (uint32_t)(g == 1u) << (8 * b);
-        }
-      }
+    for (int q = 0; q < 4; ++q) {
+      bits[2 * lane][4 * wave + q] = make_uint2(z0[q], o0[q]);
+      bits[2 * lane + 1][4 * wave + q] = make_uint2(z1[q], o1[q]);
     }
-    bytes[((int64_t)m * 2 + 0) * S4 + q] = v0;
-    bytes[((int64_t)m * 2 + 1) * S4 + q] = v1;
   }
-}
-
-// nib[m][p][s / 2]: E2M1 value 1.0 (nibble 0x2) if sample s of SNP m has
-// genotype p, else 0.0; samples 2d and 2d + 1 share byte d (low nibble first).
-__global__ void __launch_bounds__(256) encode_nibbles_kernel(const uint8_t *__restrict__ geno,
-                                                             int64_t ld, int32_t M, int32_t N,
-                                                             int32_t Mp, int32_t S,
-                                                             uint32_t *__restrict__ nib) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;  // dword of a row: 8 samples
-  const int S8 = S >> 3;
-  if (q >= S8) return;
-  for (int m = blockIdx.y; m < Mp; m += gridDim.y) {
-    uint32_t v0 = 0, v1 = 0;
-    if (m < M) {
-      const uint8_t *row = geno + (int64_t)m * ld;
+  __syncthreads();
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const int s = 8 * q + b;
-        if (s < N) {
-          const uint32_t g = row[s];
-          v0 |= (uint32_t)(g == 0u) << (4 * b + 1);
-          v1 |= (uint32_t)(g == 1u) << (4 * b + 1);
-        }
-      }
-    }
-    nib[((int64_t)m * 2 + 0) * S8 + q] = v0;
-    nib[((int64_t)m * 2 + 1) * S8 + q] = v1;
+  for (int x = 0; x < WORDS * kEncSnps / 2; x += 256) {
+    if (x + (int)threadIdx.x >= WORDS * kEncSnps / 2) break;
+    const int w = (x + threadIdx.x) / (kEncSnps / 2), m = 2 * (threadIdx.x % (kEncSnps / 2));
+    if (w0 + w >= W) continue;
+    const uint2 a = bits[w][m], b = bits[w][m + 1];
+    *reinterpret_cast<uint4 *>(planes + ((int64_t)(off + w0 + w) * Mp + m0 + m) * 2) =
+        make_uint4(a.x, a.y, b.x, b.y);
   }
-}
-
-// Per-class 0/1 value planes for the matrix cores, through the class sample
-// list: position p of class c is sample list[off_c + p] (p < len_c), else
-// padding.  bytes[c][m][g][p] = 1 and nib[c][m][g][p / 2] nibble = 0x2 (E2M1
-// 1.0) when that sample has genotype g in {0, 1}; padding and SNPs m >= M
-// are 0.  One thread per 8 positions.
-__global__ void __launch_bounds__(256) encode_values_kernel(
-    const uint8_t *__restrict__ geno, int64_t ld, const int32_t *__restrict__ list, int32_t off0,
-    int32_t len0, int32_t off1, int32_t len1, int32_t M, int32_t Mp, int32_t S,
-    uint32_t *__restrict__ bytes, uint32_t *__restrict__ nib) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;  // positions 8q .. 8q + 7
-  if (q >= S / 8) return;
-  const int c = blockIdx.z;
-  const int off = c ? off1 : off0, len = c ? len1 : len0;
-  for (int m = blockIdx.y; m < Mp; m += gridDim.y) {
-    uint32_t b0[2] = {0, 0}, b1[2] = {0, 0}, n0 = 0, n1 = 0;
-    if (m < M) {
-      const uint8_t *row = geno + (int64_t)m * ld;
+  if constexpr (VALUES) {
+    const int WS = S / 32;  // words of a row; the last group may end early
+    const int64_t row0 = ((int64_t)c * Mp + m0) * 2;
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const int p = 8 * q + b;
-        if (p < len) {
-          const uint32_t g = row[list[off + p]];
-          const uint32_t is0 = g == 0u, is1 = g == 1u;
-          b0[b >> 2] |= is0 << (8 * (b & 3));
-          b1[b >> 2] |= is1 << (8 * (b & 3));
-          n0 |= is0 << (4 * b + 1);
-          n1 |= is1 << (4 * b + 1);
-        }
-      }
+    for (int x = 0; x < WORDS * kEncSnps * 2; x += 256) {  // 16 bytes: a word's nibbles
+      const int w = (x + threadIdx.x) % WORDS, row = (x + threadIdx.x) / WORDS;
+      if (w0 + w >= WS) continue;
+      const uint2 v = bits[w][row >> 1];
+      const uint32_t b = row & 1 ? v.y : v.x;
+      *reinterpret_cast<uint4 *>(nib + (row0 + row) * (S / 8) + 4 * (w0 + w)) =
+          make_uint4(nibbles_of(b, 0), nibbles_of(b, 1), nibbles_of(b, 2), nibbles_of(b, 3));
     }
-    const int64_t rb = ((int64_t)c * Mp + m) * 2;  // row of (class, snp, plane 0)
-    reinterpret_cast<uint2 *>(bytes)[(rb + 0) * (S / 8) + q] = make_uint2(b0[0], b0[1]);
-    reinterpret_cast<uint2 *>(bytes)[(rb + 1) * (S / 8) + q] = make_uint2(b1[0], b1[1]);
-    nib[(rb + 0) * (S / 8) + q] = n0;
-    nib[(rb + 1) * (S / 8) + q] = n1;
+#pragma unroll
+    for (int x = 0; x < WORDS * kEncSnps * 4; x += 256) {  // 16 bytes: half a word's
+      const int h = (x + threadIdx.x) % (2 * WORDS), row = (x + threadIdx.x) / (2 * WORDS);
+      if (w0 + (h >> 1) >= WS) continue;
+      const uint2 v = bits[h >> 1][row >> 1];
+      const uint32_t b = (row & 1 ? v.y : v.x) >> (16 * (h & 1));
+      *reinterpret_cast<uint4 *>(bytes + (row0 + row) * (S / 4) + 8 * w0 + 4 * h) =
+          make_uint4(bytes_of(b, 0), bytes_of(b, 1), bytes_of(b, 2), bytes_of(b, 3));
+    }
   }
 }
 
@@ -311,10 +305,12 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int64_t n) {
     p[x] = v;
 }
 
+// The scan's tables of n log factorials and a cleared status block.
 __global__ void __launch_bounds__(256) log_tables_kernel(const double *__restrict__ lf64,
                                                          float *__restrict__ lf32,
                                                          uint32_t *__restrict__ lfx, int64_t n,
-                                                         double scale) {
+                                                         double scale, int32_t *__restrict__ status) {
+  if (blockIdx.x == 0 && threadIdx.x < kStatusWords) status[threadIdx.x] = 0;
   const int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (x >= n) return;
   const double v = lf64[x];
@@ -323,49 +319,26 @@ __global__ void __launch_bounds__(256) log_tables_kernel(const double *__restric
 }
 
 hipError_t launch_log_tables(const double *lf64, float *lf32, uint32_t *lfx, int64_t n, int shift,
-                             hipStream_t s) {
+                             int32_t *status, hipStream_t s) {
   hipLaunchKernelGGL(log_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, lf64,
-                     lf32, lfx, n, ldexp(1.0, shift));
+                     lf32, lfx, n, ldexp(1.0, shift), status);
   return hipGetLastError();
 }
 
 hipError_t launch_encode(const uint8_t *geno, int64_t ld, const int32_t *sample_list, int32_t M,
-                         int32_t Mp, int32_t W0, int32_t W1, uint32_t *planes, int32_t *status,
+                         int32_t Mp, int32_t W0, int32_t W1, int32_t n_classes, int32_t S,
+                         uint32_t *planes, uint8_t *bytes, uint8_t *nib, int32_t *status,
                          hipStream_t s) {
-  const int Wtot = W0 + W1;
-  if (Wtot <= 0) return hipSuccess;
-  dim3 grid((Mp + 3) / 4, (Wtot + kEncWords - 1) / kEncWords);
-  hipLaunchKernelGGL(encode_kernel, grid, dim3(256), 0, s, geno, ld, sample_list, M, Mp, Wtot,
-                     planes, status);
-  return hipGetLastError();
-}
-
-hipError_t launch_encode_bytes(const uint8_t *geno, int64_t ld, int32_t M, int32_t N, int32_t Mp,
-                               int32_t S, uint8_t *bytes, hipStream_t s) {
-  const int S4 = S / 4;
-  dim3 grid((S4 + 255) / 256, Mp < 65535 ? Mp : 65535);
-  hipLaunchKernelGGL(encode_bytes_kernel, grid, dim3(256), 0, s, geno, ld, M, N, Mp, S,
-                     reinterpret_cast<uint32_t *>(bytes));
-  return hipGetLastError();
-}
-
-hipError_t launch_encode_nibbles(const uint8_t *geno, int64_t ld, int32_t M, int32_t N, int32_t Mp,
-                                 int32_t S, uint8_t *nib, hipStream_t s) {
-  const int S8 = S / 8;
-  dim3 grid((S8 + 255) / 256, Mp < 65535 ? Mp : 65535);
-  hipLaunchKernelGGL(encode_nibbles_kernel, grid, dim3(256), 0, s, geno, ld, M, N, Mp, S,
-                     reinterpret_cast<uint32_t *>(nib));
-  return hipGetLastError();
-}
-
-hipError_t launch_encode_values(const uint8_t *geno, int64_t ld, const int32_t *list, int32_t off0,
-                                int32_t len0, int32_t off1, int32_t len1, int32_t classes,
-                                int32_t M, int32_t Mp, int32_t S, uint8_t *bytes, uint8_t *nib,
-                                hipStream_t s) {
-  dim3 grid((S / 8 + 255) / 256, Mp < 65535 ? Mp : 65535, classes);
-  hipLaunchKernelGGL(encode_values_kernel, grid, dim3(256), 0, s, geno, ld, list, off0, len0, off1,
-                     len1, M, Mp, S, reinterpret_cast<uint32_t *>(bytes),
-                     reinterpret_cast<uint32_t *>(nib));
+  if (Mp % kEncSnps != 0) return hipErrorInvalidValue;
+  const int words = bytes ? S / 32 : (W0 > W1 ? W0 : W1);  // value rows run on to S
+  if (words <= 0) return hipSuccess;
+  const bool wide = (int64_t)(Mp / kEncSnps) * ((words + 7) / 8) * n_classes >= kEncWide;
+  const int per = wide ? 16 : 8;
+  auto *kernel = bytes ? (wide ? encode_kernel<true, 16> : encode_kernel<true, 8>)
+                       : (wide ? encode_kernel<false, 16> : encode_kernel<false, 8>);
+  hipLaunchKernelGGL(kernel, dim3(Mp / kEncSnps, (words + per - 1) / per, n_classes), dim3(256), 0, s,
+                     geno, ld, sample_list, M, Mp, W0, W1, S, planes,
+                     reinterpret_cast<uint32_t *>(bytes), reinterpret_cast<uint32_t *>(nib), status);
   return hipGetLastError();
 }
 

@@ -580,23 +580,18 @@ constexpr int64_t kLdsTableBytes = 80 * 1024;
 inline bool lf_in_lds(int32_t lf_len) { return (int64_t)lf_len * 4 <= kLdsTableBytes; }
 
 // ---- host-side launchers (defined in the .hip files) ----
-hipError_t launch_encode(const uint8_t *geno, int64_t ld, const int32_t *sample_list,
-                         int32_t M, int32_t Mp, int32_t W0, int32_t W1, uint32_t *planes,
-                         int32_t *status, hipStream_t s);
-hipError_t launch_encode_bytes(const uint8_t *geno, int64_t ld, int32_t M, int32_t N, int32_t Mp,
-                               int32_t S, uint8_t *bytes, hipStream_t s);
-hipError_t launch_encode_nibbles(const uint8_t *geno, int64_t ld, int32_t M, int32_t N, int32_t Mp,
-                                 int32_t S, uint8_t *nib, hipStream_t s);
-hipError_t launch_encode_values(const uint8_t *geno, int64_t ld, const int32_t *list, int32_t off0,
-                                int32_t len0, int32_t off1, int32_t len1, int32_t classes,
-                                int32_t M, int32_t Mp, int32_t S, uint8_t *bytes, uint8_t *nib,
-                                hipStream_t s);
+// bytes, nib: value planes (both or neither)
+hipError_t launch_encode(const uint8_t *geno, int64_t ld, const int32_t *sample_list, int32_t M,
+                         int32_t Mp, int32_t W0, int32_t W1, int32_t n_classes, int32_t S,
+                         uint32_t *planes, uint8_t *bytes, uint8_t *nib, int32_t *status,
+                         hipStream_t s);
 hipError_t launch_pairs(const uint32_t *planes, int32_t Mp, int32_t W0, int32_t W1,
                         int32_t n_classes, int32_t *pairs, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 // lf32[x] = fl32(lf64[x]) and lfx[x] = round(2^shift lf64[x]) mod 2^32, x < n.
+constexpr int kStatusWords = 64;  // of an encode buffer's status block
 hipError_t launch_log_tables(const double *lf64, float *lf32, uint32_t *lfx, int64_t n, int shift,
-                             hipStream_t s);
+                             int32_t *status, hipStream_t s);
 hipError_t launch_tile_prefix(Job *jobs_dev, int32_t n_jobs, hipStream_t s);
 int64_t host_tiles(int64_t M, int P);
 hipError_t launch_write_jobs(const Job *jobs_host, int32_t n, Job *dst_dev, hipStream_t s);
