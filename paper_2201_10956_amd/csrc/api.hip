@@ -125,7 +125,7 @@ struct ScanLayout {
   unsigned long long *queue;
   SelJob *sel;
   SelState *st;
-  uint32_t *hist;
+  uint32_t *hist, *hist2;
   float *score;
   int64_t *cand;
   uint32_t *candkey;
@@ -157,6 +157,14 @@ int64_t default_cap(int64_t T, int32_t k, int64_t cand_cap) {
   int64_t cap = cand_cap > 0 ? cand_cap : std::max<int64_t>(4096, 4 * (int64_t)k);
   if (T > 0 && cap > T) cap = T;
   return std::max<int64_t>(cap, 1);
+}
+
+// Histograms of the second and third pass: over the candidate records, which
+// are written after them, where those are long enough.
+uint32_t *take_hist2(Carver &c, CandRec *rec, int64_t cap) {
+  return cap * (int64_t)sizeof(CandRec) >= 2 * kHistBins * (int64_t)sizeof(uint32_t)
+             ? reinterpret_cast<uint32_t *>(rec)
+             : c.take<uint32_t>(2 * kHistBins);
 }
 
 constexpr int64_t kPlainPassBytes = 1ll << 30;  // per scratch buffer of the plain matrix-core path
@@ -306,7 +314,7 @@ ScanLayout scan_layout(void *ws, const epi3_dataset &d, int32_t k, int64_t cand_
     L.sample = c.take<float>(ns * 4096);
     L.ssel = c.take<SelJob>(1);
     L.sst = c.take<SelState>(1);
-    L.shist = c.take<uint32_t>(kHistBins);
+    L.shist = c.take<uint32_t>(kHistPasses * kHistBins);
   }
   L.ccap = compact_cap(T, L.cap);
   if (L.bounded && mfma && compact_cap_override() <= 0) {
@@ -317,6 +325,7 @@ ScanLayout scan_layout(void *ws, const epi3_dataset &d, int32_t k, int64_t cand_
   }
   L.ckey = c.take<uint32_t>(L.ccap);
   L.crank = c.take<int64_t>(L.ccap);
+  L.hist2 = take_hist2(c, L.rec, L.cap);
   L.pjob = c.take<PlainJob>(1);
   L.jbegin = c.take<int64_t>(2);
   if (T > 0 && mfma) {
@@ -333,7 +342,7 @@ ScanLayout scan_layout(void *ws, const epi3_dataset &d, int32_t k, int64_t cand_
 struct OrderLayout {
   SelJob *sel;
   SelState *st;
-  uint32_t *hist;
+  uint32_t *hist, *hist2;
   float *score;
   int64_t *cand;
   uint32_t *candkey;
@@ -381,6 +390,7 @@ OrderLayout order_layout(void *ws, const epi3_dataset &d, int order, int32_t k, 
   L.ccap = compact_cap(T, L.cap);
   L.ckey = c.take<uint32_t>(L.ccap);
   L.crank = c.take<int64_t>(L.ccap);
+  L.hist2 = take_hist2(c, L.rec, L.cap);
   if (order == 4 && d.n_cases <= 65535 && d.n_controls <= 65535)
     L.t3 = c.take<uint8_t>(quad_triplet_table_bytes(d.n_snps));
   if (order == 4 && T > 0 && mfma_supported(d)) {
@@ -432,8 +442,8 @@ Job make_job(const epi3_dataset &d, float *score, uint32_t *counts, int64_t *jpr
 }
 
 SelJob make_seljob(const epi3_dataset &d, const float *score, int64_t T, SelState *st,
-                   uint32_t *hist, int64_t *cand, uint32_t *candkey, CandRec *rec, epi3_hit *hits,
-                   int64_t cap, int32_t k, uint32_t *ckey, int64_t *crank, int64_t ccap) {
+                   uint32_t *hist, uint32_t *hist2, int64_t *cand, uint32_t *candkey, CandRec *rec,
+                   epi3_hit *hits, int64_t cap, int32_t k, uint32_t *ckey, int64_t *crank, int64_t ccap) {
   SelJob S{};
   S.candkey = candkey;
   S.ckey = ckey;
@@ -443,6 +453,7 @@ SelJob make_seljob(const epi3_dataset &d, const float *score, int64_t T, SelStat
   S.T = T;
   S.st = st;
   S.hist = hist;
+  S.hist2 = hist2;
   S.cand = cand;
   S.rec = rec;
   S.hits = hits;
@@ -625,10 +636,12 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
   const int32_t unit = fp4 ? 128 : 64;  // samples per 64-byte staged chunk
   const int n = (int)tasks.size();
   std::vector<int64_t> begin(n + 1, 0);
+  std::vector<PlainJob> records(n);
   int32_t lf_len = 0;  // longest table
   for (int x = 0; x < n; ++x) {
     const epi3_dataset &d = *tasks[x].d;
-    PlainJob pj{};
+    PlainJob &pj = records[x];
+    pj = PlainJob{};
     pj.vals = static_cast<const uint8_t *>(fp4 ? d.nibbles : d.bytes);
     pj.pairs = d.pairs;
     pj.score = tasks[x].score;
@@ -649,14 +662,13 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
     pj.scale = fx_scale(d.n_samples);
     pj.lf_len = d.n_samples + 2;
     if (pj.Sb0 > pj.Sb || pj.Sb1 > pj.Sb) return EPI3_E_INVALID;
-    HIP_OK(launch_write_plainjob(pj, W.pjobs + x, s));
-    HIP_OK(launch_plain_prefix(W.pjobs + x, s));
     begin[x + 1] = begin[x] + pj.n_tiles;
     lf_len = std::max(lf_len, pj.lf_len);
   }
   const int64_t tiles = begin[n];
   if (tiles == 0) return EPI3_OK;
-  HIP_OK(launch_write_i64(begin.data(), n + 1, W.job_begin, s));
+  HIP_OK(launch_plain_setup(records.data(), begin.data(), n, W.pjobs, W.job_begin, W.queue, s));
+  bool clean = true;  // the tile queue, until a pass has run
   const bool counts = n > 0 && tasks[0].counts != nullptr;
   uint4 *buf[2] = {reinterpret_cast<uint4 *>(W.scratch),
                    reinterpret_cast<uint4 *>(W.scratch + W.pass_tiles * kPlainTileScratch)};
@@ -672,7 +684,8 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
     if (fused) {
       // counted and scored by one persistent kernel over all the tiles: no
       // passes, no second stream
-      HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 16, s));
+      if (!clean) HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 16, s));
+      clean = false;
       out.stride = stride;
       out.sample_base = 0;
       return timed(0, s, [&]() {
@@ -767,7 +780,7 @@ static int order_scan(const epi3_dataset *d, int order, int32_t k, int64_t cand_
   if (ws_bytes < W.total) return EPI3_E_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int64_t T = order_combos(order, d->n_snps);
-  SelJob S = make_seljob(*d, W.score, T, W.st, W.hist, W.cand, W.candkey, W.rec, nullptr, W.cap, k,
+  SelJob S = make_seljob(*d, W.score, T, W.st, W.hist, W.hist2, W.cand, W.candkey, W.rec, nullptr, W.cap, k,
                          W.ckey, W.crank, W.ccap);
   S.order = order;
   S.skey = W.skey;
@@ -776,8 +789,7 @@ static int order_scan(const epi3_dataset *d, int order, int32_t k, int64_t cand_
   if (order == 2) S.pair_hits = reinterpret_cast<epi3_pair_hit *>(W.hits);
   else S.quad_hits = reinterpret_cast<epi3_quad_hit *>(W.hits);
   S.err2 = 2.0 * order_error_bound(order, d->n_samples);
-  HIP_OK(launch_write_seljobs(&S, 1, W.sel, s));
-  HIP_OK(launch_init_select(W.sel, 1, s));
+  HIP_OK(launch_init_select(&S, 1, W.sel, s));
   if (T > 0 && W.qmfma) {
     // quads on the matrix cores: pass p of tiles is counted (timed as the
     // count stage) into scratch buffer p % 2 on `s`; its finish kernel (timed
@@ -828,9 +840,10 @@ static int order_scan(const epi3_dataset *d, int order, int32_t k, int64_t cand_
     });
     if (rc != EPI3_OK) return rc;
   }
+  SelectSizes z{};
+  add_select_sizes(z, S);
   return timed(1, s, [&]() {
-    return launch_select(W.sel, 1, T, W.cap, k, S.sample != 0, s) == hipSuccess ? EPI3_OK
-                                                                                : EPI3_E_HIP;
+    return launch_select(W.sel, 1, z, s) == hipSuccess ? EPI3_OK : EPI3_E_HIP;
   });
 }
 
@@ -1011,9 +1024,7 @@ static int enqueue_count(const epi3_dataset &d, int32_t variant, float *score, u
   if (bounded) return EPI3_E_UNSUPPORTED;
   const int P = pick_P(d);
   Job J = make_job(d, score, counts, W.jprefix, &W.st->kmin, P);
-  HIP_OK(launch_write_jobs(&J, 1, W.job, s));
-  HIP_OK(launch_tile_prefix(W.job, 1, s));
-  HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 2, s));
+  HIP_OK(launch_valu_setup(&J, 1, W.job, W.queue, s));
   return timed(0, s, [&]() {
     return launch_count_valu(W.job, 1, J.n_tiles, W.queue, d.n_samples + 2, P, P,
                              counts != nullptr, s) == hipSuccess
@@ -1034,34 +1045,28 @@ int epi3_scan(const epi3_dataset *d, int32_t k, int32_t variant, int64_t cand_ca
   if (ws_bytes < W.total) return EPI3_E_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int64_t T = epi3_n_triplets(d->n_snps);
-  SelJob S = make_seljob(*d, W.score, T, W.st, W.hist, W.cand, W.candkey, W.rec, W.hits, W.cap, k,
+  SelJob S = make_seljob(*d, W.score, T, W.st, W.hist, W.hist2, W.cand, W.candkey, W.rec, W.hits, W.cap, k,
                          W.ckey, W.crank, W.ccap);
   S.skey = W.skey;
   S.sidx = W.sidx;
   S.sortP = sort_len(W.cap);
   if (W.bounded) S.sample = 1;  // the list is built before the selection starts
-  HIP_OK(launch_write_seljobs(&S, 1, W.sel, s));
-  HIP_OK(launch_init_select(W.sel, 1, s));
+  HIP_OK(launch_init_select(&S, 1, W.sel, s));
   if (W.bounded) {
     // selection of the k-th smallest sample score (the sample plane read whole)
-    SelJob ss = make_seljob(*d, W.sample, W.sample_tiles * 4096, W.sst, W.shist, nullptr, nullptr,
-                            nullptr, nullptr, 1, k, nullptr, nullptr, 0);
+    SelJob ss = make_seljob(*d, W.sample, W.sample_tiles * 4096, W.sst, W.shist, W.shist + kHistBins,
+                            nullptr, nullptr, nullptr, nullptr, 1, k, nullptr, nullptr, 0);
     ss.sample = 0;
-    HIP_OK(launch_write_seljobs(&ss, 1, W.ssel, s));
-    HIP_OK(launch_init_select(W.ssel, 1, s));
+    HIP_OK(launch_init_select(&ss, 1, W.ssel, s));
   }
   if (T > 0) {
     const int rc = enqueue_count(*d, variant, W.score, nullptr, W, s, W.bounded);
     if (rc != EPI3_OK) return rc;
   }
-  // a bounded scan's selection reads its list only: size the grids for that;
-  // its sample flag only says that the list exists (the selection's sample
-  // phase reads a score plane, so it runs for plane jobs only)
-  const int64_t sel_T = W.bounded ? W.ccap : T;
-  const bool sampled = S.sample != 0 && S.score != nullptr;
+  SelectSizes z{};
+  add_select_sizes(z, S);
   return timed(1, s, [&]() {
-    return launch_select(W.sel, 1, sel_T, W.cap, k, sampled, s) == hipSuccess ? EPI3_OK
-                                                                              : EPI3_E_HIP;
+    return launch_select(W.sel, 1, z, s) == hipSuccess ? EPI3_OK : EPI3_E_HIP;
   });
 }
 
@@ -1203,6 +1208,7 @@ struct BatchLayout {
   std::vector<int64_t *> cand;
   std::vector<uint32_t *> candkey;
   std::vector<CandRec *> rec;
+  std::vector<uint32_t *> hist2;
   std::vector<uint64_t *> skey;   // sort buffers of jobs with capacities above kRankDirectMax
   std::vector<uint32_t *> sidx;
   std::vector<uint32_t *> ckey;
@@ -1318,7 +1324,7 @@ BatchLayout batch_layout(void *ws, const epi3_job *jobs, int32_t n, int64_t cand
         L.sample = c.take<float>((int64_t)L.groups * kPermGroup * L.sample_T);
         L.ssel = c.take<SelJob>(n);
         L.sst = c.take<SelState>(n);
-        L.shist = c.take<uint32_t>((int64_t)n * kHistBins);
+        L.shist = c.take<uint32_t>((int64_t)n * kHistPasses * kHistBins);
       }
     }
     // two buffers: the count kernel of pass p + 1 runs while pass p is
@@ -1332,6 +1338,7 @@ BatchLayout batch_layout(void *ws, const epi3_job *jobs, int32_t n, int64_t cand
   L.cand.resize(n);
   L.candkey.resize(n);
   L.rec.resize(n);
+  L.hist2.resize(n);
   L.skey.resize(n);
   L.sidx.resize(n);
   L.ckey.resize(n);
@@ -1374,6 +1381,7 @@ BatchLayout batch_layout(void *ws, const epi3_job *jobs, int32_t n, int64_t cand
     L.cand[x] = c.take<int64_t>(L.cap[x]);
     L.candkey[x] = c.take<uint32_t>(L.cap[x]);
     L.rec[x] = c.take<CandRec>(L.cap[x]);
+    L.hist2[x] = take_hist2(c, L.rec[x], L.cap[x]);
     L.skey[x] = c.take<uint64_t>(sort_len(L.cap[x]));
     L.sidx[x] = c.take<uint32_t>(sort_len(L.cap[x]));
     if (L.bounded) {
@@ -1396,18 +1404,16 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
   if (lease.rc != EPI3_OK) return lease.rc;
   // selection state first: the count kernels write each job's key range into it
   std::vector<SelJob> sj(n);
-  bool any_sample = false;
   for (int x = 0; x < n; ++x) {
     const epi3_dataset &d = *jobs[x].d;
     sj[x] = make_seljob(d, W.score[x], W.T[x], W.st + x, W.hist + (int64_t)x * kHistBins,
-                        W.cand[x], W.candkey[x], W.rec[x], W.hits + W.hit_off[x], W.cap[x],
+                        W.hist2[x], W.cand[x], W.candkey[x], W.rec[x], W.hits + W.hit_off[x], W.cap[x],
                         jobs[x].k, W.ckey[x], W.crank[x], W.ccap[x]);
     sj[x].skey = W.skey[x];
     sj[x].sidx = W.sidx[x];
     sj[x].sortP = sort_len(W.cap[x]);
     // bounded jobs have their list before the selection starts (no plane pass)
     if (W.bounded) sj[x].sample = 1;
-    any_sample = any_sample || (sj[x].sample && sj[x].score);
     if (W.layout == EPI3_LAYOUT_MASKED) {
       const int g = x / kPermGroup, q = x % kPermGroup;
       sj[x].case_mask = jobs[x].case_mask;
@@ -1417,16 +1423,7 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
       sj[x].n1_dev = W.n1 + (int64_t)g * kPermGroup + q;
     }
   }
-  HIP_OK(launch_write_seljobs(sj.data(), n, W.sel, s));
-  HIP_OK(launch_init_select(W.sel, n, s));
-
-  int64_t max_T = 0, max_cap = 0;
-  int32_t max_k = 0;
-  for (int x = 0; x < n; ++x) {
-    max_T = std::max(max_T, W.T[x]);
-    max_cap = std::max(max_cap, W.cap[x]);
-    max_k = std::max(max_k, jobs[x].k);
-  }
+  HIP_OK(launch_init_select(sj.data(), n, W.sel, s));
 
   if (W.layout == EPI3_LAYOUT_SPLIT) {
     // matrix-core jobs: one sequence of passes per (operand type, tile JB)
@@ -1483,11 +1480,7 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
       // a launch over several jobs draws four tiles of one job at a time
       begin += nv > 1 ? (J[y].n_tiles + 3) / 4 * 4 : J[y].n_tiles;
     }
-    if (nv > 0) {
-      HIP_OK(launch_write_jobs(J.data(), nv, W.jobs, s));
-      HIP_OK(launch_tile_prefix(W.jobs, nv, s));
-      HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 2, s));
-    }
+    if (nv > 0) HIP_OK(launch_valu_setup(J.data(), nv, W.jobs, W.queue, s));
     if (begin > 0) {
       const int rc = timed(0, s, [&]() {
         return launch_count_valu(W.jobs, nv, begin, W.queue, lf_len, P_lo, P_hi, false, s) ==
@@ -1509,11 +1502,12 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
       std::vector<SelJob> ss(n);
       for (int x = 0; x < n; ++x)
         ss[x] = make_seljob(d, W.sample + (int64_t)x * W.sample_T, W.sample_T, W.sst + x,
-                            W.shist + (int64_t)x * kHistBins, nullptr, nullptr, nullptr, nullptr,
+                            W.shist + (int64_t)x * kHistPasses * kHistBins,
+                            W.shist + ((int64_t)x * kHistPasses + 1) * kHistBins, nullptr, nullptr,
+                            nullptr, nullptr,
                             1, jobs[x].k, nullptr, nullptr, 0);
       for (SelJob &j : ss) j.sample = 0;  // read as a whole
-      HIP_OK(launch_write_seljobs(ss.data(), n, W.ssel, s));
-      HIP_OK(launch_init_select(W.ssel, n, s));
+      HIP_OK(launch_init_select(ss.data(), n, W.ssel, s));
     }
     for (int g = 0; g < W.groups; ++g) {
       const int Q = std::min(kPermGroup, n - g * kPermGroup);
@@ -1541,21 +1535,19 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
       pj.N = d.n_samples;
       pj.Q = Q;
       pj.Qp = kPermGroup;
-      HIP_OK(launch_write_permjob(pj, W.pjobs + g, s));
+      PermJob pjb[2] = {pj, pj};
+      pjb[1].corners = reinterpret_cast<uint4 *>(scr[1]);
+      pjb[1].totals = scr[1] ? reinterpret_cast<uint4 *>(scr[1] + W.pass_tiles * 64 * 64 * 16) : nullptr;
+      HIP_OK(launch_perm_setup(pjb[0], pjb[1], W.pjobs + g, W.pjobs_alt + g, g == 0, s));
       HIP_OK(launch_mask_bytes(W.masks + (int64_t)g * kPermGroup, Q, kPermGroup, d.n_samples,
                                d.byte_stride, const_cast<uint8_t *>(pj.ph),
                                const_cast<int32_t *>(pj.n1), fp4, s));
       HIP_OK(launch_case_pairs(static_cast<const uint32_t *>(d.planes), d.snp_stride, d.words[0],
                                W.masks + (int64_t)g * kPermGroup, Q, kPermGroup,
                                const_cast<int32_t *>(pj.case_pairs), s));
-      if (g == 0) HIP_OK(launch_perm_prefix(W.pjobs + 0, s));
       hipStream_t s2 = lease.c->s2;
       hipEvent_t ev_start = lease.c->ev[0], ev_cnt[2] = {lease.c->ev[1], lease.c->ev[2]},
                  ev_fin[2] = {lease.c->ev[3], lease.c->ev[4]};
-      PermJob pjb[2] = {pj, pj};
-      pjb[1].corners = reinterpret_cast<uint4 *>(scr[1]);
-      pjb[1].totals = scr[1] ? reinterpret_cast<uint4 *>(scr[1] + W.pass_tiles * 64 * 64 * 16) : nullptr;
-      HIP_OK(launch_write_permjob(pjb[1], W.pjobs_alt + g, s));
       const PermJob *pdev[2] = {W.pjobs + g, W.pjobs_alt + g};
       // Passes over the tiles n * stride, n < n_all: pass p counts into scratch
       // buffer p % 2 on `s`; its finish kernel runs on the second stream while
@@ -1639,11 +1631,10 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
       if (rc != EPI3_OK) return rc;
     }
   }
-  // bounded jobs' passes read their lists only: size the grids for those
-  const int64_t sel_T = W.bounded ? W.ccap[0] : max_T;
+  SelectSizes z{};
+  for (const SelJob &j : sj) add_select_sizes(z, j);
   return timed(1, s, [&]() {
-    return launch_select(W.sel, n, sel_T, max_cap, max_k, any_sample, s) == hipSuccess ? EPI3_OK
-                                                                                    : EPI3_E_HIP;
+    return launch_select(W.sel, n, z, s) == hipSuccess ? EPI3_OK : EPI3_E_HIP;
   });
 }
 

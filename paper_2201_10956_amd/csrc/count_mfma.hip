@@ -81,10 +81,17 @@ __device__ __forceinline__ uint32_t popc4_acc(v4i x, uint32_t acc) {
   return bcnt_acc((uint32_t)x.w, acc);
 }
 
-// jprefix for the permutation tiles (one block).
-__global__ void __launch_bounds__(1024) perm_prefix_kernel(PermJob *pj) {
-  const int64_t M = pj->M;
-  int64_t *pre = const_cast<int64_t *>(pj->jprefix);
+// The job record for either scratch buffer (one block); jprefix for the tiles,
+// which every group of phenotypes shares, with the first group.
+__global__ void __launch_bounds__(1024) perm_setup_kernel(PermJob pj, PermJob alt, PermJob *dst, PermJob *alt_dst,
+                                                          int prefix) {
+  if (threadIdx.x == 0) {
+    *dst = pj;
+    *alt_dst = alt;
+  }
+  if (!prefix) return;
+  const int64_t M = pj.M;
+  int64_t *pre = const_cast<int64_t *>(pj.jprefix);
   __shared__ int64_t part[1024];
   const int t = threadIdx.x;
   const int64_t chunk = (M + 1023) / 1024;
@@ -1114,8 +1121,10 @@ __global__ void __launch_bounds__(256) finish_perm_kernel(const PermJob *__restr
   }
 }
 
-hipError_t launch_perm_prefix(PermJob *pj_dev, hipStream_t s) {
-  hipLaunchKernelGGL(perm_prefix_kernel, dim3(1), dim3(1024), 0, s, pj_dev);
+hipError_t launch_perm_setup(const PermJob &pj, const PermJob &alt, PermJob *dst_dev, PermJob *alt_dev,
+                             bool prefix, hipStream_t s) {
+  hipLaunchKernelGGL(perm_setup_kernel, dim3(1), dim3(1024), 0, s, pj, alt, dst_dev, alt_dev,
+                     prefix ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -1134,15 +1143,8 @@ hipError_t launch_case_pairs(const uint32_t *planes, int32_t Mp, int32_t W,
   return hipGetLastError();
 }
 
-__global__ void write_permjob_kernel(PermJob h, PermJob *dst) { if (threadIdx.x == 0) *dst = h; }
-
-hipError_t launch_write_permjob(const PermJob &h, PermJob *dst_dev, hipStream_t s) {
-  hipLaunchKernelGGL(write_permjob_kernel, dim3(1), dim3(64), 0, s, h, dst_dev);
-  return hipGetLastError();
-}
-
 struct PtrPack {
-  const uint32_t *p[32];
+  const uint32_t *p[256];
 };
 __global__ void write_ptrs_kernel(PtrPack h, int n, const uint32_t **dst) {
   if ((int)threadIdx.x < n) dst[threadIdx.x] = h.p[threadIdx.x];
@@ -1150,11 +1152,11 @@ __global__ void write_ptrs_kernel(PtrPack h, int n, const uint32_t **dst) {
 
 hipError_t launch_write_ptrs(const uint32_t *const *h, int32_t n, const uint32_t **dst_dev,
                              hipStream_t s) {
-  for (int32_t base = 0; base < n; base += 32) {
+  for (int32_t base = 0; base < n; base += 256) {
     PtrPack pk{};
-    const int m = n - base < 32 ? n - base : 32;
+    const int m = n - base < 256 ? n - base : 256;
     for (int x = 0; x < m; ++x) pk.p[x] = h[base + x];
-    hipLaunchKernelGGL(write_ptrs_kernel, dim3(1), dim3(64), 0, s, pk, m, dst_dev + base);
+    hipLaunchKernelGGL(write_ptrs_kernel, dim3(1), dim3(256), 0, s, pk, m, dst_dev + base);
   }
   return hipGetLastError();
 }

@@ -104,14 +104,32 @@ __device__ __forceinline__ T *rflp(T *p) {
   return reinterpret_cast<T *>(rfl64q((int64_t)reinterpret_cast<uintptr_t>(p)));
 }
 
-// jprefix[J] = tiles before j-block J; jprefix[nJ] = total.
-__global__ void __launch_bounds__(1024) plain_prefix_kernel(PlainJob *pj) {
+// Job records and first tiles of a launch, passed by value.
+constexpr int kPlainJobsPerLaunch = 24;
+struct PlainJobs {
+  PlainJob j[kPlainJobsPerLaunch];
+  int64_t begin[kPlainJobsPerLaunch + 1];
+};
+static_assert(sizeof(PlainJobs) <= 3968, "kernel argument block");
+
+// One workgroup per job: the record, its first global tile, the tiles before
+// each of its j-blocks (jprefix[J]; jprefix[nJ] = all of them), and a clear
+// tile queue.
+__global__ void __launch_bounds__(1024) plain_setup_kernel(PlainJobs jobs, PlainJob *dst, int64_t *job_begin,
+                                                           unsigned long long *queue) {
+  const PlainJob *pj = &jobs.j[blockIdx.x];
+  const int t = threadIdx.x;
+  if (t == 0) {
+    dst[blockIdx.x] = *pj;
+    job_begin[blockIdx.x] = jobs.begin[blockIdx.x];
+    if (blockIdx.x + 1 == gridDim.x) job_begin[gridDim.x] = jobs.begin[gridDim.x];
+  }
+  if (blockIdx.x == 0 && t < 8) queue[t] = 0ull;
   const int64_t M = pj->M;
   const int JB = pj->JB;
   const int64_t nJ = plain_jblocks(M, JB);
   int64_t *pre = const_cast<int64_t *>(pj->jprefix);
   __shared__ int64_t part[1024];
-  const int t = threadIdx.x;
   const int64_t chunk = (nJ + 1023) / 1024;
   const int64_t a = t * chunk, b = (a + chunk < nJ) ? a + chunk : nJ;
   int64_t sum = 0;
@@ -1086,8 +1104,6 @@ __global__ void __launch_bounds__(256) finish_plain_kernel(const PlainJob *__res
   if (keyrange) flush_range(kmin, kmax, keyrange);
 }
 
-__global__ void write_plainjob_kernel(PlainJob h, PlainJob *dst) { if (threadIdx.x == 0) *dst = h; }
-
 }  // namespace
 
 int64_t host_plain_tiles(int64_t M, int JB) {
@@ -1097,13 +1113,16 @@ int64_t host_plain_tiles(int64_t M, int JB) {
   return n;
 }
 
-hipError_t launch_write_plainjob(const PlainJob &h, PlainJob *dst_dev, hipStream_t s) {
-  hipLaunchKernelGGL(write_plainjob_kernel, dim3(1), dim3(64), 0, s, h, dst_dev);
-  return hipGetLastError();
-}
-
-hipError_t launch_plain_prefix(PlainJob *pj_dev, hipStream_t s) {
-  hipLaunchKernelGGL(plain_prefix_kernel, dim3(1), dim3(1024), 0, s, pj_dev);
+hipError_t launch_plain_setup(const PlainJob *h, const int64_t *begin, int32_t n, PlainJob *dst_dev,
+                              int64_t *job_begin_dev, unsigned long long *queue, hipStream_t s) {
+  for (int x = 0; x < n; x += kPlainJobsPerLaunch) {
+    PlainJobs jobs{};
+    const int m = n - x < kPlainJobsPerLaunch ? n - x : kPlainJobsPerLaunch;
+    for (int y = 0; y < m; ++y) jobs.j[y] = h[x + y];
+    for (int y = 0; y <= m; ++y) jobs.begin[y] = begin[x + y];
+    hipLaunchKernelGGL(plain_setup_kernel, dim3(m), dim3(1024), 0, s, jobs, dst_dev + x,
+                       job_begin_dev + x, queue);
+  }
   return hipGetLastError();
 }
 
@@ -1324,23 +1343,6 @@ int64_t host_plain_sample_valid(int64_t M, int JB, int64_t stride, int64_t *n_sa
   }
   if (n_sample) *n_sample = ns;
   return valid;
-}
-
-struct I64Pack {
-  int64_t v[32];
-};
-__global__ void write_i64_kernel(I64Pack h, int n, int64_t *dst) {
-  if ((int)threadIdx.x < n) dst[threadIdx.x] = h.v[threadIdx.x];
-}
-
-hipError_t launch_write_i64(const int64_t *h, int32_t n, int64_t *dst_dev, hipStream_t s) {
-  for (int32_t base = 0; base < n; base += 32) {
-    I64Pack pk{};
-    const int m = n - base < 32 ? n - base : 32;
-    for (int x = 0; x < m; ++x) pk.v[x] = h[base + x];
-    hipLaunchKernelGGL(write_i64_kernel, dim3(1), dim3(64), 0, s, pk, m, dst_dev + base);
-  }
-  return hipGetLastError();
 }
 
 }  // namespace epi3

@@ -30,9 +30,16 @@ __host__ __device__ __forceinline__ int64_t tiles_of_j(int64_t M, int64_t j, int
   return ((j + P - 1) / P) * ((M - 1 - j + 63) / 64);
 }
 
-// jprefix[j] = job-local tiles before pivot j, jprefix[M] = total; one block per job.
-__global__ void __launch_bounds__(1024) tile_prefix_kernel(Job *jobs) {
-  Job &J = jobs[blockIdx.x];
+// The job records (by value), jprefix[j] = job-local tiles before pivot j,
+// jprefix[M] = total, one block per job, and a clear tile queue.
+struct Jobs {
+  Job j[kJobsPerLaunch];
+};
+static_assert(sizeof(Jobs) <= 3968, "kernel argument block");
+__global__ void __launch_bounds__(1024) valu_setup_kernel(Jobs jobs, Job *dst, unsigned long long *queue) {
+  const Job &J = jobs.j[blockIdx.x];
+  if (threadIdx.x == 0) dst[blockIdx.x] = J;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *queue = 0ull;
   const int64_t M = J.M;
   const int P = J.P;
   int64_t *pre = const_cast<int64_t *>(J.jprefix);
@@ -271,16 +278,14 @@ __global__ void __launch_bounds__(256) count_valu_kernel(const Job *__restrict__
   }
 }
 
-hipError_t launch_tile_prefix(Job *jobs_dev, int32_t n_jobs, hipStream_t s) {
-  hipLaunchKernelGGL(tile_prefix_kernel, dim3(n_jobs), dim3(1024), 0, s, jobs_dev);
-  return hipGetLastError();
-}
-
-__global__ void write_jobs_kernel(Job j0, Job *dst) { if (threadIdx.x == 0) *dst = j0; }
-
-hipError_t launch_write_jobs(const Job *jobs_host, int32_t n, Job *dst_dev, hipStream_t s) {
-  for (int x = 0; x < n; ++x)
-    hipLaunchKernelGGL(write_jobs_kernel, dim3(1), dim3(64), 0, s, jobs_host[x], dst_dev + x);
+hipError_t launch_valu_setup(const Job *h, int32_t n, Job *dst_dev, unsigned long long *queue,
+                             hipStream_t s) {
+  for (int x = 0; x < n; x += kJobsPerLaunch) {
+    Jobs jobs{};
+    const int m = n - x < kJobsPerLaunch ? n - x : kJobsPerLaunch;
+    for (int y = 0; y < m; ++y) jobs.j[y] = h[x + y];
+    hipLaunchKernelGGL(valu_setup_kernel, dim3(m), dim3(1024), 0, s, jobs, dst_dev + x, queue);
+  }
   return hipGetLastError();
 }
 

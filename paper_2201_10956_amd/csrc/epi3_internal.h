@@ -5,6 +5,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "epi3.h"
 
 namespace epi3 {
@@ -78,25 +80,35 @@ struct Job {
   int32_t pad;
 };
 
+// Key window of a radix-select pass.
+struct SelWindow {
+  uint64_t krem;           // 1-based rank of the k-th key inside the window
+  uint32_t lo, whi;        // first and last key
+  int32_t shift;           // bin width of the pass = 1 << shift
+  uint32_t done;           // 1: collapsed to the k-th key; 2: nothing to select; 3: list overflowed
+  uint32_t kth;            // done = 1: key of the k-th smallest score
+  uint32_t pad;
+};
+
 // Per-job radix-select state.
 struct SelState {
   uint32_t kmin, kmax;     // key range of the score plane (written by the count kernel)
-  uint32_t lo;             // lower end of the key window holding the k-th key
-  int32_t shift;           // bin width of the current pass = 1 << shift
-  uint64_t krem;           // 1-based rank of the k-th key inside the window
-  uint32_t done;           // window collapsed to one key
+  uint32_t done;           // 1: candidates collected; 2, 3 as SelWindow
   uint32_t kth;            // key of the k-th smallest score
   float thr;               // candidate threshold (FP32, rounded up)
+  uint32_t pending;        // left to the kernels after tail_kernel, from window `rest`
   uint32_t overflow;       // candidates beyond capacity
   unsigned long long ncand;
   int64_t keff;            // min(k, T)
   int64_t T;
   int32_t k;
-  uint32_t whi;            // last key of the current window (set with lo)
   float ub;                // compaction bound: last key of the first window + 2 e(N), as float
   uint32_t cmode;          // 1 once the compaction pass ran
+  uint32_t pad;
   unsigned long long cn;   // keys <= ub found by the compaction pass
+  SelWindow win[kHistPasses], rest;  // windows of the passes over a plane or its sample
 };
+static_assert(sizeof(SelState) <= 256, "one 256-byte unit of a workspace");
 
 // One scored candidate.
 struct CandRec {
@@ -185,7 +197,8 @@ struct SelJob {
   const float *score;
   int64_t T;
   SelState *st;
-  uint32_t *hist;          // [kHistBins]
+  uint32_t *hist;          // [kHistBins] first pass
+  uint32_t *hist2;         // [2][kHistBins] second and third; may lie over rec (used before it)
   int64_t *cand;           // [cap] ranks
   uint32_t *candkey;       // [cap] their FP32 score keys
   CandRec *rec;            // [cap]
@@ -592,28 +605,52 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 constexpr int kStatusWords = 64;  // of an encode buffer's status block
 hipError_t launch_log_tables(const double *lf64, float *lf32, uint32_t *lfx, int64_t n, int shift,
                              int32_t *status, hipStream_t s);
-hipError_t launch_tile_prefix(Job *jobs_dev, int32_t n_jobs, hipStream_t s);
 int64_t host_tiles(int64_t M, int P);
-hipError_t launch_write_jobs(const Job *jobs_host, int32_t n, Job *dst_dev, hipStream_t s);
+// Job records, their tile prefixes and a clear tile queue.
+constexpr int kJobsPerLaunch = 24;
+hipError_t launch_valu_setup(const Job *h, int32_t n, Job *dst_dev, unsigned long long *queue,
+                             hipStream_t s);
 hipError_t launch_count_valu(const Job *jobs_dev, int32_t n_jobs, int64_t total_tiles,
                              unsigned long long *queue, int32_t lf_len, int32_t P_lo, int32_t P_hi,
                              bool counts, hipStream_t s);
-// sampled: at least one job has SelJob::sample set.
-hipError_t launch_select(SelJob *sel_dev, int32_t n_jobs, int64_t max_T, int64_t max_cap,
-                         int32_t max_k, bool sampled, hipStream_t s);
-hipError_t launch_write_seljobs(const SelJob *h, int32_t n, SelJob *dst_dev, hipStream_t s);
-// The k-th smallest key of each job's plane only (st->kth, done = 1; jobs
-// with fewer than k keys in their key range end with done = 0).
+constexpr int kSelJobsPerLaunch = 12;
+// Lists and planes up to these lengths are finished by one workgroup: 64 keys
+// and 256 scores per thread and pass, about 5 and 15 us.
+constexpr int64_t kTailList = 1ll << 16;
+constexpr int64_t kTailPlane = 1ll << 18;
+// What a launch of selections has to provide for.
+struct SelectSizes {
+  int64_t max_T;    // scores of the longest plane (no planes: entries of the longest list)
+  int64_t max_cap;
+  int32_t max_k;
+  bool sampled, unsampled;  // some job with a plane has SelJob::sample set / clear
+  bool rest;        // some job may leave its list or plane to the passes after the tail
+};
+hipError_t launch_select(SelJob *sel_dev, int32_t n_jobs, const SelectSizes &z, hipStream_t s);
+// Adds job J to the sizes of a launch.
+inline void add_select_sizes(SelectSizes &z, const SelJob &J) {
+  z.max_T = std::max(z.max_T, J.score ? J.T : J.ccap);
+  z.max_cap = std::max(z.max_cap, J.cap);
+  z.max_k = std::max(z.max_k, J.k);
+  if (J.score) (J.sample ? z.sampled : z.unsampled) = true;
+  // a plane's list holds at most ccap >= min(T, ...) entries; past that the plane is read
+  z.rest = z.rest || J.ccap > kTailList || (J.score && J.T > J.ccap && J.T > kTailPlane);
+}
+// The histograms of the three passes that find each job's k-th smallest key
+// (jobs with fewer than k keys in their key range end without one).
 hipError_t launch_select_kth(SelJob *sel_dev, int32_t n_jobs, int64_t max_T, hipStream_t s);
 // After a sample pass: main job x's compacted list bound = the sample's k-th
 // score + 2 e(N) (rounded up; +inf if the sample had no k-th score), empty list.
-hipError_t launch_sample_bound(SelJob *main_dev, const SelJob *sample_dev, int32_t n_jobs,
+hipError_t launch_sample_bound(const SelJob *main_dev, const SelJob *sample_dev, int32_t n_jobs,
                                hipStream_t s);
-hipError_t launch_init_select(SelJob *sel_dev, int32_t n_jobs, hipStream_t s);
+// Writes the job records to dst_dev and sets up their states and histograms.
+hipError_t launch_init_select(const SelJob *h, int32_t n, SelJob *dst_dev, hipStream_t s);
 hipError_t launch_score_triplets(const epi3_dataset &d, const uint32_t *ijk, int64_t n,
                                  uint32_t *counts, float *k2f, double *k2, hipStream_t s);
 
-hipError_t launch_perm_prefix(PermJob *pj_dev, hipStream_t s);
+// One group's record for either scratch buffer; prefix: the tiles' prefix too.
+hipError_t launch_perm_setup(const PermJob &pj, const PermJob &alt, PermJob *dst_dev, PermJob *alt_dev,
+                             bool prefix, hipStream_t s);
 hipError_t launch_mask_bytes(const uint32_t *const *masks_dev, int32_t Q, int32_t Qp, int32_t N,
                              int32_t S, uint8_t *ph, int32_t *n1, bool fp4, hipStream_t s);
 hipError_t launch_case_pairs(const uint32_t *planes, int32_t Mp, int32_t W,
@@ -664,15 +701,16 @@ hipError_t launch_count_score_perm(const PermJob *pj_dev, int64_t tile_begin, in
 // Triplets (i < j < k < M) in the phenotype-batch tiles 0, stride, 2 stride, ...
 int64_t host_perm_sample_valid(int64_t M, int64_t stride);
 constexpr int64_t kPermTileScratch = 64 * 64 * 16 + 64 * 16;  // bytes per tile (corners + totals)
-hipError_t launch_write_permjob(const PermJob &h, PermJob *dst_dev, hipStream_t s);
 hipError_t launch_write_ptrs(const uint32_t *const *h, int32_t n, const uint32_t **dst_dev,
                              hipStream_t s);
 
 int64_t host_plain_tiles(int64_t M, int JB);
 constexpr int kPlainI = 16;  // pivots i per plain matrix-core tile (x JB j x 256 / JB k)
 constexpr int64_t kPlainTileScratch = 2ll * kPlainI * 256 * 16;  // bytes per tile, both classes
-hipError_t launch_write_plainjob(const PlainJob &h, PlainJob *dst_dev, hipStream_t s);
-hipError_t launch_plain_prefix(PlainJob *pj_dev, hipStream_t s);
+// Job records, their first tiles begin[0 .. n], tile prefixes and 8 clear queue
+// counters.
+hipError_t launch_plain_setup(const PlainJob *h, const int64_t *begin, int32_t n, PlainJob *dst_dev,
+                              int64_t *job_begin_dev, unsigned long long *queue, hipStream_t s);
 // Plain matrix-core count / finish of the global tiles tile_begin + q stride,
 // q < n_tiles, of n_jobs data sets (same JB and operand type): job x owns
 // global tiles job_begin[x] .. job_begin[x + 1] (device int64 [n_jobs + 1]);
@@ -697,7 +735,6 @@ hipError_t launch_finish_plain(const PlainJob *jobs, const int64_t *job_begin, i
 // Triplets (i < j < k < M) in the plain tiles 0, stride, 2 stride, ... of a
 // data set of M SNPs (tile JB); the number of such tiles in *n_sample.
 int64_t host_plain_sample_valid(int64_t M, int JB, int64_t stride, int64_t *n_sample);
-hipError_t launch_write_i64(const int64_t *h, int32_t n, int64_t *dst_dev, hipStream_t s);
 
 int tile_P_default(int32_t M, int32_t N);
 
