@@ -545,6 +545,131 @@ struct AuxLease {
   AuxLease &operator=(const AuxLease &) = delete;
 };
 
+// Pinned host memory that kernels read inputs from and write results to: small
+// transfers of a call then cost one kernel instead of a staged copy each (a
+// pageable copy takes 8-15 us of host time whatever its size).  A call holds a
+// block of its own until its stream has finished with it.  At most kStagingIdle
+// blocks stay idle; epi3_release gives them back.  A block whose stream did not
+// finish (an error) is never used again.  Where nothing may be allocated
+// (epi3_topk, which epi3_scan_topk_static ends in), only an idle block is taken:
+// every encode leaves one, and epi3_init.
+constexpr int64_t kStagingBytes = 1 << 20;
+constexpr size_t kStagingIdle = 8;
+struct StagingPool {
+  std::mutex mu;
+  std::vector<uint8_t *> idle;
+  StagingPool() { idle.reserve(kStagingIdle); }
+};
+StagingPool &staging_pool() {
+  static StagingPool p;
+  return p;
+}
+class StagingLease {
+ public:
+  uint8_t *host = nullptr, *dev = nullptr;  // NULL: use plain copies
+  bool busy = false;                        // work that touches the block may be running
+  StagingLease(int64_t bytes, bool allocate) {
+    if (bytes > kStagingBytes) return;
+    {
+      StagingPool &p = staging_pool();
+      std::lock_guard<std::mutex> g(p.mu);
+      if (!p.idle.empty()) {
+        host = p.idle.back();
+        p.idle.pop_back();
+      }
+    }
+    void *m = host;
+    if (!m && !allocate) return;
+    if (!m && hipHostMalloc(&m, kStagingBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    host = static_cast<uint8_t *>(m);
+    void *d = nullptr;
+    if (hipHostGetDevicePointer(&d, m, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      return;  // dev stays NULL: plain copies
+    }
+    dev = static_cast<uint8_t *>(d);
+  }
+  ~StagingLease() {
+    if (!host || busy) return;
+    StagingPool &p = staging_pool();
+    {
+      std::lock_guard<std::mutex> g(p.mu);
+      if (p.idle.size() < kStagingIdle) {
+        p.idle.push_back(host);
+        return;
+      }
+    }
+    (void)hipHostFree(host);
+  }
+  StagingLease(const StagingLease &) = delete;
+  StagingLease &operator=(const StagingLease &) = delete;
+};
+
+// The results of n jobs on `s`, waited for: their states, their data sets'
+// status words and, where they fit the staging block, hit_bytes of hits.
+class Results {
+ public:
+  int rc;
+  const SelState *st;     // [n]
+  const int32_t *status;  // [n]
+  Results(const SelState *st_dev, const int32_t *const *status_dev, int32_t n, const void *hits_dev,
+          int64_t hit_bytes, hipStream_t s, bool allocate)
+      : s_(s), hits_dev_(hits_dev), head_(result_head_bytes(n)),
+        staged_(head_ + hit_bytes <= kStagingBytes ? hit_bytes : 0), lease_(head_ + staged_, allocate) {
+    rc = fetch(st_dev, status_dev, n);
+  }
+  // The first `bytes` of hits to `out` (waited for).
+  int copy_hits(void *out, int64_t bytes) {
+    if (bytes <= 0) return EPI3_OK;
+    if (lease_.dev && bytes <= staged_) {
+      memcpy(out, lease_.host + head_, bytes);
+      return EPI3_OK;
+    }
+    HIP_OK(hipMemcpyAsync(out, hits_dev_, bytes, hipMemcpyDeviceToHost, s_));
+    HIP_OK(hipStreamSynchronize(s_));
+    return EPI3_OK;
+  }
+
+ private:
+  int fetch(const SelState *st_dev, const int32_t *const *status_dev, int32_t n) {
+    if (lease_.dev) {
+      lease_.busy = true;
+      HIP_OK(launch_gather_results(st_dev, status_dev, n, hits_dev_, staged_, lease_.dev, s_));
+      HIP_OK(hipStreamSynchronize(s_));
+      lease_.busy = false;
+      st = reinterpret_cast<const SelState *>(lease_.host);
+      status = reinterpret_cast<const int32_t *>(st + n);
+      return EPI3_OK;
+    }
+    SelState *sp = &one_;
+    int32_t *cp = &one_status_;
+    if (n > 1) {
+      states_.resize(n);
+      statuses_.resize(n);
+      sp = states_.data();
+      cp = statuses_.data();
+    }
+    HIP_OK(hipMemcpyAsync(sp, st_dev, n * sizeof(SelState), hipMemcpyDeviceToHost, s_));
+    for (int32_t x = 0; x < n; ++x)
+      HIP_OK(hipMemcpyAsync(cp + x, status_dev[x], sizeof(int32_t), hipMemcpyDeviceToHost, s_));
+    HIP_OK(hipStreamSynchronize(s_));
+    st = sp;
+    status = cp;
+    return EPI3_OK;
+  }
+  SelState one_;
+  int32_t one_status_;
+  std::vector<SelState> states_;
+  std::vector<int32_t> statuses_;
+  hipStream_t s_;
+  const void *hits_dev_;
+  int64_t head_, staged_;
+  StagingLease lease_;
+};
+
 // ---- optional kernel timing: HIP events on the call's stream ----
 struct Timing {
   std::mutex mu;
@@ -854,22 +979,19 @@ static int order_topk(const epi3_dataset *d, int order, int32_t k, int64_t cand_
   if (!ws_dev || !hits_host || !n_out) return EPI3_E_INVALID;
   OrderLayout W = order_layout(ws_dev, *d, order, k, cand_cap);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  SelState st;
-  int32_t status = 0;
-  HIP_OK(hipMemcpyAsync(&st, W.st, sizeof(st), hipMemcpyDeviceToHost, s));
-  HIP_OK(hipMemcpyAsync(&status, d->status, sizeof(status), hipMemcpyDeviceToHost, s));
-  HIP_OK(hipStreamSynchronize(s));
+  const int64_t T = order_combos(order, d->n_snps);
+  Results res(W.st, &d->status, 1, W.hits, std::min<int64_t>(k, T) * order_hit_bytes(order), s, false);
+  if (res.rc != EPI3_OK) return res.rc;
+  const SelState &st = res.st[0];
   *n_out = 0;
-  if (status & 1) return EPI3_E_GENOTYPE;
+  if (res.status[0] & 1) return EPI3_E_GENOTYPE;
   if ((int64_t)st.ncand > W.cap) {
     *n_out = (int32_t)std::min<unsigned long long>(st.ncand, 0x7fffffffull);
     return EPI3_E_CAPACITY;
   }
   const int64_t keff = st.keff;
-  if (keff > 0) {
-    HIP_OK(hipMemcpyAsync(hits_host, W.hits, keff * order_hit_bytes(order), hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
-  }
+  const int rh = res.copy_hits(hits_host, keff * order_hit_bytes(order));
+  if (rh != EPI3_OK) return rh;
   *n_out = (int32_t)keff;
   return EPI3_OK;
 }
@@ -946,8 +1068,16 @@ int epi3_encode(const uint8_t *geno_dev, int64_t ld, const uint8_t *pheno_host, 
   if (buf_bytes < L.total) return EPI3_E_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
-  // sample list per output word: controls then cases (SPLIT), or all (MASKED)
-  std::vector<int32_t> list((size_t)L.Wtot * 32, -1);
+  // log factorials, then the sample list per output word: controls then cases
+  // (SPLIT), or all (MASKED)
+  const LfTables *lt = log_factorial_tables((int64_t)n_samples + 1);
+  const int64_t n_lf = (int64_t)n_samples + 2;  // L[0 .. n_samples + 1]
+  const int64_t n_list = (int64_t)L.Wtot * 32;
+  StagingLease lease(n_lf * (int64_t)sizeof(double) + n_list * (int64_t)sizeof(int32_t), true);
+  std::vector<int32_t> own;  // without a staging block
+  if (!lease.dev) own.resize(n_list);
+  int32_t *list = lease.dev ? reinterpret_cast<int32_t *>(lease.host + n_lf * sizeof(double)) : own.data();
+  std::fill(list, list + n_list, -1);
   if (layout == EPI3_LAYOUT_SPLIT) {
     int32_t p0 = 0, p1 = L.W0 * 32;
     for (int32_t x = 0; x < n_samples; ++x) {
@@ -956,12 +1086,19 @@ int epi3_encode(const uint8_t *geno_dev, int64_t ld, const uint8_t *pheno_host, 
   } else {
     for (int32_t x = 0; x < n_samples; ++x) list[x] = x;
   }
-  const LfTables *lt = log_factorial_tables((int64_t)n_samples + 1);
-  const size_t n_lf = (size_t)n_samples + 2;  // L[0 .. n_samples + 1]
-
-  HIP_OK(hipMemcpyAsync(L.list, list.data(), list.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(L.lf64, lt->L64.data(), n_lf * sizeof(double), hipMemcpyHostToDevice, s));
-  HIP_OK(launch_log_tables(L.lf64, L.lf32, L.lfx, (int64_t)n_lf, fx_shift(n_samples), L.status, s));
+  const double *src_lf64 = L.lf64;
+  const int32_t *src_list = L.list;
+  if (lease.dev) {
+    memcpy(lease.host, lt->L64.data(), n_lf * sizeof(double));
+    src_lf64 = reinterpret_cast<const double *>(lease.dev);
+    src_list = reinterpret_cast<const int32_t *>(lease.dev + n_lf * sizeof(double));
+  } else {
+    HIP_OK(hipMemcpyAsync(L.list, list, n_list * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    HIP_OK(hipMemcpyAsync(L.lf64, lt->L64.data(), n_lf * sizeof(double), hipMemcpyHostToDevice, s));
+  }
+  lease.busy = lease.dev != nullptr;
+  HIP_OK(launch_tables(src_lf64, src_list, n_list, L.lf64, L.lf32, L.lfx, n_lf, fx_shift(n_samples), L.list,
+                       L.status, s));
   const bool split = layout == EPI3_LAYOUT_SPLIT;
   HIP_OK(launch_encode(geno_dev, ld, L.list, n_snps, L.Mp, split ? L.W0 : L.Wtot, split ? L.W1 : 0,
                        L.classes, L.S, L.planes, values ? L.bytes : nullptr, values ? L.nibbles : nullptr,
@@ -972,7 +1109,8 @@ int epi3_encode(const uint8_t *geno_dev, int64_t ld, const uint8_t *pheno_host, 
                : EPI3_E_HIP;
   });
   if (prc != EPI3_OK) return prc;
-  HIP_OK(hipStreamSynchronize(s));  // host vectors above must outlive the copies
+  HIP_OK(hipStreamSynchronize(s));  // the host memory above must outlive the work that reads it
+  lease.busy = false;
 
   memset(out, 0, sizeof(*out));
   out->n_snps = n_snps;
@@ -1075,13 +1213,12 @@ int epi3_topk(const epi3_dataset *d, int32_t k, int64_t cand_cap, void *ws_dev, 
   if (!valid_dataset(d) || k <= 0 || !ws_dev || !hits_host || !n_out) return EPI3_E_INVALID;
   ScanLayout W = scan_layout(ws_dev, *d, k, cand_cap, EPI3_VARIANT_VALU);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  SelState st;
-  int32_t status = 0;
-  HIP_OK(hipMemcpyAsync(&st, W.st, sizeof(st), hipMemcpyDeviceToHost, s));
-  HIP_OK(hipMemcpyAsync(&status, d->status, sizeof(status), hipMemcpyDeviceToHost, s));
-  HIP_OK(hipStreamSynchronize(s));
+  Results res(W.st, &d->status, 1, W.hits,
+              std::min<int64_t>(k, epi3_n_triplets(d->n_snps)) * (int64_t)sizeof(epi3_hit), s, false);
+  if (res.rc != EPI3_OK) return res.rc;
+  const SelState &st = res.st[0];
   *n_out = 0;
-  if (status & 1) return EPI3_E_GENOTYPE;
+  if (res.status[0] & 1) return EPI3_E_GENOTYPE;
   if (st.done == 3u) {
     // the bounded list overflowed: 16 x cand_cap entries hold it on a retry
     const int64_t need = std::max<int64_t>((int64_t)((st.cn + 15) / 16), W.cap + 1);
@@ -1093,10 +1230,8 @@ int epi3_topk(const epi3_dataset *d, int32_t k, int64_t cand_cap, void *ws_dev, 
     return EPI3_E_CAPACITY;
   }
   const int64_t keff = st.keff;
-  if (keff > 0) {
-    HIP_OK(hipMemcpyAsync(hits_host, W.hits, keff * sizeof(epi3_hit), hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
-  }
+  const int rh = res.copy_hits(hits_host, keff * (int64_t)sizeof(epi3_hit));
+  if (rh != EPI3_OK) return rh;
   *n_out = (int32_t)keff;
   return EPI3_OK;
 }
@@ -1758,13 +1893,15 @@ int epi3_scan_batched(const epi3_job *jobs, int32_t n_jobs, int32_t variant, int
     if (hipGraphLaunch(exec, s) != hipSuccess) return EPI3_E_HIP;
   }
 
-  std::vector<SelState> st(n_jobs);
-  HIP_OK(hipMemcpyAsync(st.data(), W.st, sizeof(SelState) * n_jobs, hipMemcpyDeviceToHost, s));
-  std::vector<int32_t> status(n_jobs, 0);
-  for (int x = 0; x < n_jobs; ++x)
-    HIP_OK(hipMemcpyAsync(&status[x], jobs[x].d->status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  HIP_OK(hipMemcpyAsync(hits_host, W.hits, sizeof(epi3_hit) * W.total_k, hipMemcpyDeviceToHost, s));
-  HIP_OK(hipStreamSynchronize(s));
+  std::vector<const int32_t *> status_dev(n_jobs);
+  for (int x = 0; x < n_jobs; ++x) status_dev[x] = jobs[x].d->status;
+  const int64_t hit_bytes = W.total_k * (int64_t)sizeof(epi3_hit);
+  Results res(W.st, status_dev.data(), n_jobs, W.hits, hit_bytes, s, true);
+  if (res.rc != EPI3_OK) return res.rc;
+  rc = res.copy_hits(hits_host, hit_bytes);
+  if (rc != EPI3_OK) return rc;
+  const SelState *st = res.st;
+  const int32_t *status = res.status;
   int worst = EPI3_OK;
   for (int x = 0; x < n_jobs; ++x) {
     n_out_host[x] = (int32_t)st[x].keff;
@@ -1788,6 +1925,7 @@ int epi3_init(void) {
   {
     AuxLease lease;  // one idle context in the pool from now on
     if (lease.rc != EPI3_OK) return lease.rc;
+    StagingLease staging(0, true);  // and one block of pinned memory
   }
   {
     const int rc = static_scratch_ptr(nullptr);  // epi3_scan_topk_static's workspace
@@ -1804,6 +1942,12 @@ void epi3_release(void) {
     AuxPool &p = aux_pool();
     std::lock_guard<std::mutex> lk(p.mu);
     for (AuxCtx *c : p.idle) aux_destroy(c);
+    p.idle.clear();
+  }
+  {
+    StagingPool &p = staging_pool();
+    std::lock_guard<std::mutex> lk(p.mu);
+    for (uint8_t *m : p.idle) (void)hipHostFree(m);
     p.idle.clear();
   }
   GraphCache &G = graphs();

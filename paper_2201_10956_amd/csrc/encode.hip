@@ -305,23 +305,30 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int64_t n) {
     p[x] = v;
 }
 
-// The scan's tables of n log factorials and a cleared status block.
-__global__ void __launch_bounds__(256) log_tables_kernel(const double *__restrict__ lf64,
-                                                         float *__restrict__ lf32,
-                                                         uint32_t *__restrict__ lfx, int64_t n,
-                                                         double scale, int32_t *__restrict__ status) {
+// See launch_tables.
+__global__ void __launch_bounds__(256) tables_kernel(const double *src_lf64, const int32_t *src_list,
+                                                     int64_t n_list, double *lf64,
+                                                     float *__restrict__ lf32,
+                                                     uint32_t *__restrict__ lfx, int64_t n,
+                                                     double scale, int32_t *list,
+                                                     int32_t *__restrict__ status) {
   if (blockIdx.x == 0 && threadIdx.x < kStatusWords) status[threadIdx.x] = 0;
   const int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (x >= n) return;
-  const double v = lf64[x];
-  lf32[x] = (float)v;
-  lfx[x] = (uint32_t)(unsigned long long)rint(v * scale);
+  if (x < n) {
+    const double v = src_lf64[x];
+    if (src_lf64 != lf64) lf64[x] = v;
+    lf32[x] = (float)v;
+    lfx[x] = (uint32_t)(unsigned long long)rint(v * scale);
+  }
+  if (x < n_list && src_list != list) list[x] = src_list[x];
 }
 
-hipError_t launch_log_tables(const double *lf64, float *lf32, uint32_t *lfx, int64_t n, int shift,
-                             int32_t *status, hipStream_t s) {
-  hipLaunchKernelGGL(log_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, lf64,
-                     lf32, lfx, n, ldexp(1.0, shift), status);
+hipError_t launch_tables(const double *src_lf64, const int32_t *src_list, int64_t n_list, double *lf64,
+                         float *lf32, uint32_t *lfx, int64_t n, int shift, int32_t *list,
+                         int32_t *status, hipStream_t s) {
+  const int64_t m = n > n_list ? n : n_list;
+  hipLaunchKernelGGL(tables_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, src_lf64, src_list,
+                     n_list, lf64, lf32, lfx, n, ldexp(1.0, shift), list, status);
   return hipGetLastError();
 }
 

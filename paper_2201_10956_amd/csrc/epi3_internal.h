@@ -601,10 +601,14 @@ hipError_t launch_encode(const uint8_t *geno, int64_t ld, const int32_t *sample_
 hipError_t launch_pairs(const uint32_t *planes, int32_t Mp, int32_t W0, int32_t W1,
                         int32_t n_classes, int32_t *pairs, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
-// lf32[x] = fl32(lf64[x]) and lfx[x] = round(2^shift lf64[x]) mod 2^32, x < n.
 constexpr int kStatusWords = 64;  // of an encode buffer's status block
-hipError_t launch_log_tables(const double *lf64, float *lf32, uint32_t *lfx, int64_t n, int shift,
-                             int32_t *status, hipStream_t s);
+// lf64 and the sample list to the device (src_lf64, src_list: memory the device
+// can read, or lf64 and list themselves if they are there already), lf32[x] =
+// fl32(lf64[x]), lfx[x] = round(2^shift lf64[x]) mod 2^32, x < n, and a clear
+// status block.
+hipError_t launch_tables(const double *src_lf64, const int32_t *src_list, int64_t n_list, double *lf64,
+                         float *lf32, uint32_t *lfx, int64_t n, int shift, int32_t *list,
+                         int32_t *status, hipStream_t s);
 int64_t host_tiles(int64_t M, int P);
 // Job records, their tile prefixes and a clear tile queue.
 constexpr int kJobsPerLaunch = 24;
@@ -627,6 +631,11 @@ struct SelectSizes {
   bool rest;        // some job may leave its list or plane to the passes after the tail
 };
 hipError_t launch_select(SelJob *sel_dev, int32_t n_jobs, const SelectSizes &z, hipStream_t s);
+// The results of n jobs to memory that the host can read: n states, the n data
+// sets' status words (padded to 8 bytes), hit_bytes (a multiple of 8) of hits.
+constexpr int64_t result_head_bytes(int64_t n) { return n * (int64_t)sizeof(SelState) + (n + 1) / 2 * 8; }
+hipError_t launch_gather_results(const SelState *st, const int32_t *const *status, int32_t n,
+                                 const void *hits, int64_t hit_bytes, void *dst, hipStream_t s);
 // Adds job J to the sizes of a launch.
 inline void add_select_sizes(SelectSizes &z, const SelJob &J) {
   z.max_T = std::max(z.max_T, J.score ? J.T : J.ccap);

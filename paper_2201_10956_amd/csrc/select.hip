@@ -985,6 +985,40 @@ hipError_t launch_select(SelJob *sel_dev, int32_t n_jobs, const SelectSizes &z, 
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------ results ----
+struct StatusPtrs {
+  const int32_t *p[256];
+};
+__global__ void __launch_bounds__(256) gather_results_kernel(const uint2 *st, int64_t n_st, StatusPtrs ptrs,
+                                                             int n_status, int32_t *status_out,
+                                                             const uint2 *hits, int64_t n_hits, uint2 *st_out,
+                                                             uint2 *hits_out) {
+  const int64_t x0 = blockIdx.x * (int64_t)256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+  for (int64_t x = x0; x < n_st; x += step) st_out[x] = st[x];
+  for (int64_t x = x0; x < n_status; x += step) status_out[x] = *ptrs.p[x];
+  for (int64_t x = x0; x < n_hits; x += step) hits_out[x] = hits[x];
+}
+
+hipError_t launch_gather_results(const SelState *st, const int32_t *const *status, int32_t n,
+                                 const void *hits, int64_t hit_bytes, void *dst, hipStream_t s) {
+  static_assert(sizeof(SelState) % 8 == 0, "8-byte units");
+  uint8_t *out = static_cast<uint8_t *>(dst);
+  for (int32_t base = 0; base < n; base += 256) {
+    StatusPtrs ptrs{};
+    const int32_t m = n - base < 256 ? n - base : 256;
+    for (int32_t x = 0; x < m; ++x) ptrs.p[x] = status[base + x];
+    const int64_t units = base == 0 ? hit_bytes / 8 : 0;  // the hits with the first launch
+    const unsigned blocks = (unsigned)std::min<int64_t>(std::max<int64_t>((units + 255) / 256, 1), 256);
+    hipLaunchKernelGGL(gather_results_kernel, dim3(blocks), dim3(256), 0, s,
+                       reinterpret_cast<const uint2 *>(st + base), m * (int64_t)(sizeof(SelState) / 8), ptrs,
+                       (int)m, reinterpret_cast<int32_t *>(out + n * (int64_t)sizeof(SelState)) + base,
+                       static_cast<const uint2 *>(hits), units,
+                       reinterpret_cast<uint2 *>(out + base * (int64_t)sizeof(SelState)),
+                       reinterpret_cast<uint2 *>(out + result_head_bytes(n)));
+  }
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------- test hook ----
 __global__ void __launch_bounds__(256) score_triplets_kernel(
     const uint32_t *__restrict__ planes, const int32_t *__restrict__ pairs,
