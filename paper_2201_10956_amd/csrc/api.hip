@@ -1697,7 +1697,7 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
           HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 16, s));
           out.sample_base = 0;
           return timed(0, s, [&]() {
-            return launch_count_score_perm(W.pjobs + g, 0, n_all, stride, W.queue, fst, fx_table(d),
+            return launch_count_score_perm(W.pjobs + g, Q, 0, n_all, stride, W.queue, fst, fx_table(d),
                                            d.n_samples + 2, fx_scale(d.n_samples), out, s) == hipSuccess
                        ? EPI3_OK
                        : EPI3_E_HIP;

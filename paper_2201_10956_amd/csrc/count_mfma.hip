@@ -164,12 +164,13 @@ __global__ void __launch_bounds__(256) case_pairs_kernel(const uint32_t *__restr
   const int y = blockIdx.x * 64 + lane;
   const int q0 = blockIdx.z * 16;
   if (x >= Mp || (int)blockIdx.x * 64 + 63 < x) return;
+  const int w_end = q0 < Q ? W : 0;  // a group past the last phenotype: zeros
   uint32_t acc[16][4];
 #pragma unroll
   for (int t = 0; t < 16; ++t) acc[t][0] = acc[t][1] = acc[t][2] = acc[t][3] = 0u;
   cptr<uint32_t> pc = as_const(planes);
   const uint2 *pv = reinterpret_cast<const uint2 *>(planes);
-  for (int w = 0; w < W; ++w) {
+  for (int w = 0; w < w_end; ++w) {
     const uint32_t x0 = pc[((int64_t)w * Mp + x) * 2], x1 = pc[((int64_t)w * Mp + x) * 2 + 1];
     const uint2 yv = (y < Mp) ? pv[(int64_t)w * Mp + y] : make_uint2(0u, 0u);
 #pragma unroll
@@ -337,14 +338,21 @@ struct Lookups {
 // are added up two steps after they were issued, so they alternate with the
 // vector instructions (117 per k and wave instead of 170 with 32-bit cells and
 // all lookups of a k at once).  What bounds the kernel is instruction issue:
-// two waves per SIMD (240-254 registers), one counting while the other scores.
+// two waves per SIMD (230 registers), one counting while the other scores.
 // 203 x 1501, 20 phenotypes, score planes: 584 + 713 us in two kernels over the
 // corner scratch -> 1.82 instead of 2.00 ms for the whole call; 1024 x 8192, 64
 // phenotypes, bounded: 271 -> 269 ms.  Tables of k outside (j, M) and of phenotypes
 // past Q are consistent counts too (padding planes are zero), so they are
 // computed where they share a step and only their output is left out.
-template <int FUSE>
-__device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPermT][2],
+//
+// QT = 1 (at most 32 phenotypes: one column tile): both lane halves hold the
+// same phenotypes, so the swap pairs the registers of triplets k and k + 2
+// instead, and half h scores k + 2 h of every four k: no lane idles.  153
+// registers, three waves per SIMD.  With 32 of 64 columns empty, 203 x 1501 x
+// 20 took 1253 us, so 786; 500 x 8192 x 32 33.3 -> 21.4 ms; 400 x 3000 x 16
+// 9.2 -> 4.9 ms.
+template <int FUSE, int QT>
+__device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPermT][QT],
                                             const uint4 *tot16, uint32_t *rows,
                                             SelState *__restrict__ st, const PermOut &out,
                                             float scale, int i, int j, int k0, int64_t slot, int wave, int lane,
@@ -357,26 +365,30 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
   const int kk_hi = M - k0 < kPermKB ? M - k0 : kPermKB;
   // case cells of phenotype q = lane: genotype 0 of SNP k in the low half,
   // genotype 1 in the high half of each register, (a, b) = v % 4
-  uint32_t cc[kPermT][16];
+  uint32_t cc[kPermT][8 * QT];
 #pragma unroll
   for (int tt = 0; tt < kPermT; ++tt)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
+    for (int v = 0; v < 8 * QT; ++v) {
+      const float other = QT == 2 ? acc[tt][QT - 1][v] : acc[tt][0][(v + 8) & 15];
       const auto sw = __builtin_amdgcn_permlane32_swap(
-          __float_as_uint(acc[tt][0][v]), __float_as_uint(acc[tt][1][v]), false, false);
+          __float_as_uint(acc[tt][0][v]), __float_as_uint(other), false, false);
       cc[tt][v] = __builtin_amdgcn_perm(sw[1], sw[0], 0x05040100u);
       asm volatile("" : "+v"(cc[tt][v]));  // packed here: the accumulators end
     }
   typedef unsigned u2e __attribute__((ext_vector_type(2)));
   gptr<u2e> cp = (gptr<u2e>)pj.case_pairs;
   auto cp_row = [&](int x, int y) { return cp + ((int64_t)x * Mp + y) * Qp; };
-  const int q = lane;
+  const int q = lane & (32 * QT - 1);
+  const int hk = QT == 2 ? 0 : 2 * (lane >> 5);  // this lane's k within a step, less 0 or 1
+  constexpr int kStep = 2 * (3 - QT);            // k per step
   // rows k0 .. k0 + 15 lie below the padded stride Mp (k0 + 15 < M + 16), one
   // pair of k ahead, through uniform row pointers advanced per step
   gptr<u2e> pik = cp_row(i, k0), pjk = cp_row(j, k0), pkk = cp_row(k0, k0);
   const int64_t dkk = (int64_t)(Mp + 1) * Qp;
   struct Rows { u2e ik, jk, kk; };
-  Rows next[2] = {{pik[q], pjk[q], pkk[q]}, {pik[Qp + q], pjk[Qp + q], pkk[dkk + q]}};
+  const int oq = hk * Qp + q, okk = hk * (int)dkk + q;
+  Rows next[2] = {{pik[oq], pjk[oq], pkk[okk]}, {pik[Qp + oq], pjk[Qp + oq], pkk[dkk + okk]}};
   const u2e cij = cp_row(i, j)[q], cii = cp_row(i, i)[q], cjj = cp_row(j, j)[q];
   const int n1x4 = pj.n1[q] << 2;
   const float ubq = FUSE == kFuseBounded ? st[q < Q ? q : 0].ub : 0.f;
@@ -422,16 +434,16 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
   asm volatile("" : "+v"(two));
   float *sc = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(rows) + kScoreRows);
 #pragma unroll
-  for (int p = 0; p < kPermKB / 2; ++p) {
+  for (int p = 0; p < kPermKB / kStep; ++p) {
     const Rows cur[2] = {next[0], next[1]};
-    if (p + 1 < kPermKB / 2) {
-      pik += 2 * Qp;
-      pjk += 2 * Qp;
-      pkk += 2 * dkk;
-      next[0] = {pik[q], pjk[q], pkk[q]};
-      next[1] = {pik[Qp + q], pjk[Qp + q], pkk[dkk + q]};
+    if (p + 1 < kPermKB / kStep) {
+      pik += kStep * Qp;
+      pjk += kStep * Qp;
+      pkk += kStep * dkk;
+      next[0] = {pik[oq], pjk[oq], pkk[okk]};
+      next[1] = {pik[Qp + oq], pjk[Qp + oq], pkk[dkk + okk]};
     }
-    if (2 * p + 1 < kk_lo || 2 * p >= kk_hi) continue;  // wave-uniform
+    if (kStep * p + kStep - 1 < kk_lo || kStep * p >= kk_hi) continue;  // wave-uniform
     uint32_t up[2], down[2] = {0u, 0u};
     Lookups in_flight[2];
     auto add_up = [&](int n) {  // the lookups of step n
@@ -444,9 +456,9 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
     };
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int kk = 2 * p + h, tt = kk >> 2, t4 = kk & 3;
+      const int tt = (kStep * p + h) >> 2, t4 = (kStep * p + h) & 3;
       uint32_t ta[28];
-      const uint4 *rk = reinterpret_cast<const uint4 *>(rows + kk * 28);
+      const uint4 *rk = reinterpret_cast<const uint4 *>(rows + (kStep * p + h + hk) * 28);
 #pragma unroll
       for (int x = 0; x < 7; ++x) {
         const uint4 w = rk[x];
@@ -490,13 +502,13 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
     add_up(17);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int kk = 2 * p + h;
-      if (kk < kk_lo || kk >= kk_hi) continue;  // wave-uniform
+      const int kk = kStep * p + h + hk;
+      if (kk < kk_lo || kk >= kk_hi) continue;
       const float k2 = fx_score(up[h] - down[h], scale);
       const uint32_t key = f2key(k2);
       kmin = key < kmin ? key : kmin;
       kmax = key > kmax ? key : kmax;
-      if (FUSE == kFusePlane) sc[kk * 64 + q] = k2;
+      if (FUSE == kFusePlane) sc[kk * 32 * QT + q] = k2;
       if (FUSE == kFuseSample && q < Q)
         out.sample[(int64_t)q * out.sample_T + (out.sample_base + slot) * 64 + wave * kPermKB + kk] = k2;
       if (FUSE == kFuseBounded && q < Q && k2 <= ubq) {
@@ -515,9 +527,9 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-    for (int e0 = 0; e0 < kPermKB * 64; e0 += 64) {
-      const int e = e0 + q, qq = e / kPermKB, kk = e % kPermKB;
-      if (qq < Q && kk >= kk_lo && kk < kk_hi) pj.score[(int64_t)qq * pj.T + base + kk] = sc[kk * 64 + qq];
+    for (int e0 = 0; e0 < kPermKB * 32 * QT; e0 += 64) {
+      const int e = e0 + lane, qq = e / kPermKB, kk = e % kPermKB;
+      if (qq < Q && kk >= kk_lo && kk < kk_hi) pj.score[(int64_t)qq * pj.T + base + kk] = sc[kk * 32 * QT + qq];
     }
   }
 }
@@ -528,7 +540,7 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
 // the corner scratch), with the log-factorial table at LDS address 0;
 // nothing goes to the scratch.  FUSE = 0: corner cells out, finish_perm_kernel
 // after.  The kernels below give the LDS arrays.
-template <bool FP4, int FUSE>
+template <bool FP4, int FUSE, int QT>
 __device__ __forceinline__ void count_perm_body(
     const PermJob *__restrict__ pjp, int64_t tile_begin, int64_t n_tiles, int64_t stride,
     unsigned long long *__restrict__ queue, SelState *__restrict__ st,
@@ -549,12 +561,6 @@ __device__ __forceinline__ void count_perm_body(
     }
   }
   uint32_t kmin = 0xffffffffu, kmax = 0u;  // FUSE: this lane's phenotype's key range
-  const int r = lane & 31, g = lane >> 5;
-  // A row r of a row tile = (triplet ta = r / 8, corner c = (r / 4) % 2,
-  // a = (r / 2) % 2, b = r % 2): the four lanes of a quad share (ta, c) and
-  // differ in (a, b), so each lane loads the k row of a different row tile
-  // and the quad broadcasts it by DPP (one LDS read for the four row tiles)
-  const int ta = r >> 3, rc = (r >> 2) & 1, ra = (r >> 1) & 1, rb = r & 1;
   const int M = pj.M, S = pj.S;
   gptr<uint8_t> gb = (gptr<uint8_t>)pj.bytes;
   gptr<uint8_t> gph = (gptr<uint8_t>)pj.ph;
@@ -591,6 +597,18 @@ __device__ __forceinline__ void count_perm_body(
     // the SIMD's issue), so the matrix cores stay fed while one scores
     if constexpr (FUSE != 0) __builtin_amdgcn_s_setprio(1);
     if (slot >= n_tiles) break;
+    // this tile's lane roles, from a lane number the compiler cannot carry
+    // from tile to tile (it kept every LDS and row offset in registers through
+    // the scoring: 254 and 12 spilled instead of 230 and none)
+    int tid_now = threadIdx.x;
+    asm volatile("" : "+v"(tid_now));
+    const int tid = tid_now, lane = tid & 63, wave = tid >> 6;
+    const int r = lane & 31, g = lane >> 5;
+    // A row r of a row tile = (triplet ta = r / 8, corner c = (r / 4) % 2,
+    // a = (r / 2) % 2, b = r % 2): the four lanes of a quad share (ta, c) and
+    // differ in (a, b), so each lane loads the k row of a different row tile
+    // and the quad broadcasts it by DPP (one LDS read for the four row tiles)
+    const int ta = r >> 3, rc = (r >> 2) & 1, ra = (r >> 1) & 1, rb = r & 1;
     const int64_t t = tile_begin + slot * stride;
     if (j < 0 || t < jlo || t >= jhi) {
       int lo = 0, hi = M - 1;
@@ -619,6 +637,7 @@ __device__ __forceinline__ void count_perm_body(
     constexpr int kPc = kKC / 16;                // pieces per row
     constexpr int kMainU = 96 * kPc / 256;       // main pieces per thread
     constexpr int kPairPieces = kRowsP * kPc;    // pair pieces (<= 256)
+    static_assert(QT == 2 || 32 * kPc == 256, "one piece per thread of 32 rows");
     static_assert(kRowsPH + kRowsXK == 96 && (96 * kPc) % 256 == 0 && kPairPieces <= 256,
                   "staging plan");
     // 32-bit byte offsets of this thread's pieces for chunk 0 (the value
@@ -650,6 +669,7 @@ __device__ __forceinline__ void count_perm_body(
 #pragma unroll
       for (int u = 0; u < kMainU; ++u) {
         const int row = (tid + 256 * u) / kPc;
+        if (QT == 1 && u == 1) continue;  // phenotypes 32 .. 63
         if (row < kRowsPH)
           pf[u] = *reinterpret_cast<gptr<v4i>>(gph + (off[u] + c0));
         else
@@ -665,19 +685,20 @@ __device__ __forceinline__ void count_perm_body(
 #pragma unroll
       for (int u = 0; u < kMainU; ++u) {
         const int c16 = tid + 256 * u;
+        if (QT == 1 && u == 1) continue;
         *reinterpret_cast<v4i *>(dst + lds_row(c16 / kPc) * kRow + (c16 % kPc) * 16) = pf[u];
       }
       if (tid < kPairPieces)
         *reinterpret_cast<v4i *>(dst + (96 + tid / kPc) * kRow + (tid % kPc) * 16) = pa & pb;
     };
 
-    typename Acc::type acc[kPermT][2];
+    typename Acc::type acc[kPermT][QT];
     uint32_t tot[kPermT];
 #pragma unroll
     for (int tt = 0; tt < kPermT; ++tt) {
       tot[tt] = 0u;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[tt][0][v] = acc[tt][1][v] = FUSE ? 8388608 : 0;  // 2^23
+      for (int v = 0; v < 16; ++v) acc[tt][0][v] = acc[tt][QT - 1][v] = FUSE ? 8388608 : 0;  // 2^23
     }
     // FP4: the all-sample corner counts of the tile are one 16 x 16 product
     // per k half: rows = the 16 pair rows (4 pivots x (a, b)), columns = 8 k
@@ -710,12 +731,12 @@ __device__ __forceinline__ void count_perm_body(
     P = *reinterpret_cast<const v4i *>((BB) + o_p + 32 * (STP));                  \
     X = *reinterpret_cast<const v4i *>((BB) + o_x + 32 * (STP));                  \
     B0 = *reinterpret_cast<const v4i *>((BB) + o_b0 + 32 * (STP));                \
-    B1 = *reinterpret_cast<const v4i *>((BB) + o_b1 + 32 * (STP));
+    if constexpr (QT == 2) B1 = *reinterpret_cast<const v4i *>((BB) + o_b1 + 32 * (STP));
 #define EPI3_TILE(TT, P, X, B0, B1)                                                 \
     {                                                                             \
       const v4i a_ = (P) & quad_bcast<TT>(X);                                     \
       acc[TT][0] = Acc::mma(a_, B0, acc[TT][0]);                                  \
-      acc[TT][1] = Acc::mma(a_, B1, acc[TT][1]);                                  \
+      if constexpr (QT == 2) acc[TT][QT - 1] = Acc::mma(a_, B1, acc[TT][QT - 1]); \
       if constexpr (!FP4) tot[TT] = popc4_acc(a_, tot[TT]);                       \
     }
 #define EPI3_SCHED                                                                  \
@@ -779,7 +800,10 @@ __device__ __forceinline__ void count_perm_body(
       // the products above stay before the branch (they would otherwise be
       // sunk to their first use below it)
 #pragma unroll
-      for (int tt = 0; tt < kPermT; ++tt) asm volatile("" : "+v"(acc[tt][0]), "+v"(acc[tt][1]));
+      for (int tt = 0; tt < kPermT; ++tt) {
+        asm volatile("" : "+v"(acc[tt][0]));
+        if constexpr (QT == 2) asm volatile("" : "+v"(acc[tt][QT - 1]));
+      }
       if constexpr (FP4) asm volatile("" : "+v"(tacc));
       if (more) store((ch + 1) & 1);
       __syncthreads();
@@ -824,7 +848,7 @@ __device__ __forceinline__ void count_perm_body(
     if constexpr (FUSE != 0) {
       // the staging buffers are idle until the next tile's first store
       __builtin_amdgcn_s_setprio(0);
-      fused_score<FUSE>(pj, acc, sT16[wave], reinterpret_cast<uint32_t *>(stage + wave * kScorePart), st,
+      fused_score<FUSE, QT>(pj, acc, sT16[wave], reinterpret_cast<uint32_t *>(stage + wave * kScorePart), st,
                         out, scale, i, j, kbase, slot, wave, lane, kmin, kmax);
       continue;
     }
@@ -848,7 +872,7 @@ __device__ __forceinline__ void count_perm_body(
 #pragma unroll
     for (int tt = 0; tt < kPermT; ++tt)
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb)
+      for (int qb = 0; qb < QT; ++qb)
 #pragma unroll
         for (int t4 = 0; t4 < 4; ++t4) {
           const uint32_t c0 = Acc::get(acc[tt][qb], 4 * t4 + 0), c1 = Acc::get(acc[tt][qb], 4 * t4 + 1);
@@ -858,9 +882,10 @@ __device__ __forceinline__ void count_perm_body(
   }
   if constexpr (FUSE != 0) {
     const int Q = pj.Q;
-    if (lane < Q && kmax != 0u) {
-      atomicMin(&sRange[lane][0], kmin);
-      atomicMax(&sRange[lane][1], kmax);
+    const int q = lane & (32 * QT - 1);
+    if (q < Q && kmax != 0u) {
+      atomicMin(&sRange[q][0], kmin);
+      atomicMax(&sRange[q][1], kmax);
     }
     __syncthreads();
     if (tid < 64 && tid < Q && sRange[tid][1] != 0u) {
@@ -881,7 +906,7 @@ __global__ void __launch_bounds__(256, 2) count_mfma_perm_kernel(
   // second half, added by the waves of the first half
   __shared__ float sTot[2][64][4];
   const PermOut none{};
-  count_perm_body<FP4, 0>(pjp, tile_begin, n_tiles, stride, queue, nullptr, nullptr, 0, 1.f, none,
+  count_perm_body<FP4, 0, 2>(pjp, tile_begin, n_tiles, stride, queue, nullptr, nullptr, 0, 1.f, none,
                           stage,
                           sTile, sTot, nullptr, nullptr, nullptr);
 }
@@ -889,8 +914,8 @@ __global__ void __launch_bounds__(256, 2) count_mfma_perm_kernel(
 // Dynamic LDS only, so the log-factorial table starts at LDS address 0 and a
 // lookup is one ds_read at the byte offset: [table][staging][tile slot]
 // [totals exchange][the tile's all-sample cells][key ranges].
-template <int FUSE>
-__global__ void __launch_bounds__(256, 2) count_score_perm_kernel(
+template <int FUSE, int QT>
+__global__ void __launch_bounds__(256, QT == 1 ? 3 : 2) count_score_perm_kernel(
     const PermJob *__restrict__ pjp, int64_t tile_begin, int64_t n_tiles, int64_t stride,
     unsigned long long *__restrict__ queue, SelState *__restrict__ st,
     const uint32_t *__restrict__ lfx, int lf_len, float scale, PermOut out) {
@@ -900,7 +925,7 @@ __global__ void __launch_bounds__(256, 2) count_score_perm_kernel(
   float(*sTot)[64][4] = reinterpret_cast<float(*)[64][4]>(sTile + 2);
   uint4(*sT16)[kPermKB] = reinterpret_cast<uint4(*)[kPermKB]>(sTot + 2);
   uint32_t(*sRange)[2] = reinterpret_cast<uint32_t(*)[2]>(sT16 + 4);
-  count_perm_body<true, FUSE>(pjp, tile_begin, n_tiles, stride, queue, st, lfx, lf_len, scale, out, stage,
+  count_perm_body<true, FUSE, QT>(pjp, tile_begin, n_tiles, stride, queue, st, lfx, lf_len, scale, out, stage,
                               sTile, sTot, sT16, sRange, reinterpret_cast<uint32_t *>(lds));
 }
 
@@ -1167,7 +1192,7 @@ int64_t host_perm_tiles(int64_t M) {
   return n;
 }
 
-template <bool FP4, int FUSE>
+template <bool FP4, int FUSE, int QT>
 static hipError_t launch_count_t(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
                                  int64_t stride, unsigned long long *queue, SelState *st,
                                  const uint32_t *lfx, int32_t lf_len, float scale, const PermOut &out,
@@ -1188,16 +1213,22 @@ static hipError_t launch_count_t(const PermJob *pj_dev, int64_t tile_begin, int6
     hipLaunchKernelGGL(count_mfma_perm_kernel<FP4>, dim3((unsigned)blocks), dim3(256), 0, s, pj_dev,
                        tile_begin, n_tiles, stride, queue);
   } else {
+    auto kern = count_score_perm_kernel<FUSE, QT>;
     const size_t lds = (size_t)perm_score_lds_bytes(lf_len);
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&count_score_perm_kernel<FUSE>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, count_score_perm_kernel<FUSE>, 256, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, lds);
     if (e != hipSuccess) return e;
+    // workgroups that start together count together and score together until
+    // the queue has spread them: with fewer than 32 tiles per CU two per CU are
+    // as good as three or better (64 SNPs 73 against 97 us, 80 214 / 235 for the
+    // whole batch, 128 466 / 459, 203 870 / 786)
+    if (n_tiles < 32ll * n_cu && per_cu > 2) per_cu = 2;
     if (per_cu <= 0) per_cu = 1;
     int64_t blocks = (int64_t)n_cu * per_cu;
     if (blocks > n_tiles) blocks = n_tiles;
-    hipLaunchKernelGGL(count_score_perm_kernel<FUSE>, dim3((unsigned)blocks), dim3(256), lds, s,
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, s,
                        pj_dev, tile_begin, n_tiles, stride, queue, st, lfx, lf_len, scale, out);
   }
   return hipGetLastError();
@@ -1208,9 +1239,9 @@ hipError_t launch_count_mfma_perm(const PermJob *pj_dev, int64_t tile_begin, int
                                   int64_t stride, unsigned long long *queue, bool fp4,
                                   hipStream_t s) {
   const PermOut none{};
-  return fp4 ? launch_count_t<true, 0>(pj_dev, tile_begin, n_tiles, stride, queue, nullptr, nullptr,
+  return fp4 ? launch_count_t<true, 0, 2>(pj_dev, tile_begin, n_tiles, stride, queue, nullptr, nullptr,
                                        0, 1.f, none, s)
-             : launch_count_t<false, 0>(pj_dev, tile_begin, n_tiles, stride, queue, nullptr,
+             : launch_count_t<false, 0, 2>(pj_dev, tile_begin, n_tiles, stride, queue, nullptr,
                                         nullptr, 0, 1.f, none, s);
 }
 
@@ -1218,21 +1249,32 @@ bool perm_fused_ok(int32_t lf_len) {
   return lf_len > 0 && perm_score_lds_bytes(lf_len) <= 80 * 1024;  // two workgroups per CU
 }
 
-hipError_t launch_count_score_perm(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
+template <int QT>
+static hipError_t launch_count_score_q(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
+                                       int64_t stride, unsigned long long *queue, SelState *st,
+                                       const uint32_t *lfx, int32_t lf_len, float scale, const PermOut &out,
+                                       hipStream_t s) {
+  if (out.mode == kPermOutPlane)
+    return launch_count_t<true, kFusePlane, QT>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
+                                                lf_len, scale, out, s);
+  if (out.mode == kPermOutSample)
+    return launch_count_t<true, kFuseSample, QT>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
+                                                 lf_len, scale, out, s);
+  if (out.mode == kPermOutBounded)
+    return launch_count_t<true, kFuseBounded, QT>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
+                                                  lf_len, scale, out, s);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_count_score_perm(const PermJob *pj_dev, int Q, int64_t tile_begin, int64_t n_tiles,
                                    int64_t stride, unsigned long long *queue, SelState *st,
                                    const uint32_t *lfx, int32_t lf_len, float scale, const PermOut &out,
                                    hipStream_t s) {
   if (!perm_fused_ok(lf_len)) return hipErrorInvalidValue;
-  if (out.mode == kPermOutPlane)
-    return launch_count_t<true, kFusePlane>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
-                                            lf_len, scale, out, s);
-  if (out.mode == kPermOutSample)
-    return launch_count_t<true, kPermOutSample>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
-                                                lf_len, scale, out, s);
-  if (out.mode == kPermOutBounded)
-    return launch_count_t<true, kPermOutBounded>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx,
-                                                 lf_len, scale, out, s);
-  return hipErrorInvalidValue;
+  return Q <= 32 ? launch_count_score_q<1>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx, lf_len,
+                                           scale, out, s)
+                 : launch_count_score_q<2>(pj_dev, tile_begin, n_tiles, stride, queue, st, lfx, lf_len,
+                                           scale, out, s);
 }
 
 template <bool LDS, int MODE>

@@ -628,6 +628,7 @@ struct SelectSizes {
   int64_t max_cap;
   int32_t max_k;
   bool sampled, unsampled;  // some job with a plane has SelJob::sample set / clear
+  bool quads;       // jobs of order 4 (all or none)
   bool rest;        // some job may leave its list or plane to the passes after the tail
 };
 hipError_t launch_select(SelJob *sel_dev, int32_t n_jobs, const SelectSizes &z, hipStream_t s);
@@ -641,6 +642,7 @@ inline void add_select_sizes(SelectSizes &z, const SelJob &J) {
   z.max_T = std::max(z.max_T, J.score ? J.T : J.ccap);
   z.max_cap = std::max(z.max_cap, J.cap);
   z.max_k = std::max(z.max_k, J.k);
+  z.quads = z.quads || J.order == 4;
   if (J.score) (J.sample ? z.sampled : z.unsampled) = true;
   // a plane's list holds at most ccap >= min(T, ...) entries; past that the plane is read
   z.rest = z.rest || J.ccap > kTailList || (J.score && J.T > J.ccap && J.T > kTailPlane);
@@ -703,7 +705,7 @@ hipError_t launch_finish_perm(const PermJob *pj_dev, int64_t tile_begin, int64_t
 // Count and score in one kernel (FP4 operands, any output mode, the
 // log-factorial table of lf_len entries in LDS: perm_fused_ok); no scratch.
 bool perm_fused_ok(int32_t lf_len);
-hipError_t launch_count_score_perm(const PermJob *pj_dev, int64_t tile_begin, int64_t n_tiles,
+hipError_t launch_count_score_perm(const PermJob *pj_dev, int Q, int64_t tile_begin, int64_t n_tiles,
                                    int64_t stride, unsigned long long *queue, SelState *st,
                                    const uint32_t *lfx, int32_t lf_len, float scale,
                                    const PermOut &out, hipStream_t s);

@@ -662,6 +662,8 @@ __device__ __forceinline__ void put_record(const SelJob &J, int64_t c, int64_t r
       if (64 * p + lane < rows) R.counts[ROWS * cl + 64 * p + lane] = (uint32_t)lr.r[cl][p];
 }
 
+// QUADS: jobs of order 4, a kernel of its own (twice the registers).
+template <bool QUADS>
 __global__ void __launch_bounds__(256) rescore_kernel(const SelJob *__restrict__ sj) {
   const SelJob &J = sj[blockIdx.y];
   SelState *st = J.st;
@@ -672,7 +674,7 @@ __global__ void __launch_bounds__(256) rescore_kernel(const SelJob *__restrict__
   for (int64_t c = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6); c < n;
        c += waves) {
     const int64_t rank = J.cand[c];
-    if (J.order == 4) {
+    if constexpr (QUADS) {
       int i, j, k, l;
       decode_quad_rank(J.M, rank, i, j, k, l);
       int q[2][81];
@@ -689,28 +691,28 @@ __global__ void __launch_bounds__(256) rescore_kernel(const SelJob *__restrict__
         quad_cells(cnt, J.pairs + cl * MpMp4, J.Mp, i, j, k, l, cl ? J.N1 : J.N0, q[cl]);
       }
       put_record<81>(J, c, rank, i, j, k, l, q, 81);
-      continue;
+    } else {
+      int tab[2][27];
+      if (J.order == 2) {
+        int i, j;
+        decode_pair_rank(J.M, rank, i, j);
+        pair_table(J.planes, J.Mp, J.W0, J.W1, J.N0, J.N1, i, j, tab);
+  #pragma unroll
+        for (int x = 9; x < 27; ++x) tab[0][x] = tab[1][x] = 0;
+        put_record<27>(J, c, rank, i, j, 0, 0, tab, 9);
+        continue;
+      }
+      int i, j, k;
+      decode_rank(J.M, rank, i, j, k);
+      int N0 = J.N0, N1 = J.N1;
+      if (J.n1_dev) {
+        N1 = *J.n1_dev;
+        N0 = J.N0 + J.N1 - N1;
+      }
+      triplet_table(J.planes, J.pairs, J.case_pairs, J.case_stride, J.case_mask, J.layout, J.Mp,
+                    J.W0, J.W1, N0, N1, i, j, k, tab);
+      put_record<27>(J, c, rank, i, j, k, 0, tab, 27);
     }
-    int tab[2][27];
-    if (J.order == 2) {
-      int i, j;
-      decode_pair_rank(J.M, rank, i, j);
-      pair_table(J.planes, J.Mp, J.W0, J.W1, J.N0, J.N1, i, j, tab);
-#pragma unroll
-      for (int x = 9; x < 27; ++x) tab[0][x] = tab[1][x] = 0;
-      put_record<27>(J, c, rank, i, j, 0, 0, tab, 9);
-      continue;
-    }
-    int i, j, k;
-    decode_rank(J.M, rank, i, j, k);
-    int N0 = J.N0, N1 = J.N1;
-    if (J.n1_dev) {
-      N1 = *J.n1_dev;
-      N0 = J.N0 + J.N1 - N1;
-    }
-    triplet_table(J.planes, J.pairs, J.case_pairs, J.case_stride, J.case_mask, J.layout, J.Mp,
-                  J.W0, J.W1, N0, N1, i, j, k, tab);
-    put_record<27>(J, c, rank, i, j, k, 0, tab, 27);
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && (int64_t)st->ncand > J.cap) st->overflow = 1u;
 }
@@ -965,7 +967,8 @@ hipError_t launch_select(SelJob *sel_dev, int32_t n_jobs, const SelectSizes &z, 
   // a wave per candidate; most capacities are far above the candidates found,
   // and a workgroup without one still takes its turn (20 jobs of 1024: 34 us)
   const unsigned cb = (unsigned)std::min<int64_t>((max_cap + 3) / 4, std::max(1024u / nj, 32u));
-  hipLaunchKernelGGL(rescore_kernel, dim3(cb, nj), dim3(256), 0, s, sel_dev);
+  hipLaunchKernelGGL(z.quads ? rescore_kernel<true> : rescore_kernel<false>, dim3(cb, nj), dim3(256), 0, s,
+                     sel_dev);
   const unsigned kb = (unsigned)std::min<int64_t>((max_cap + 63) / 64, std::max(256u / nj, 8u));
   hipLaunchKernelGGL(rank_kernel, dim3(kb, nj), dim3(kRankThreads), 0, s, sel_dev);
   const int64_t P = sort_len(max_cap);  // jobs with sort buffers (each skips the other path)
