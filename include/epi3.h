@@ -201,9 +201,9 @@ int epi3_score_plane(const epi3_dataset *d, int32_t k, int64_t cand_cap, void *w
 /* ---------------------------------------------------------------------------
  * Allocation-free plain scan, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc).  Not a step of the paper's method: the same vector-ALU count
- * kernel and selection as epi3_scan + epi3_topk with EPI3_VARIANT_VALU, whose
- * workspace is a device array of EPI3_STATIC_SCRATCH_BYTES inside the library
+ * hipMalloc).  Not a step of the paper's method: the results of epi3_scan +
+ * epi3_topk with EPI3_VARIANT_VALU bit for bit (counted on the matrix cores
+ * where the rest of the array has room for their buffers), whose workspace is a device array of EPI3_STATIC_SCRATCH_BYTES inside the library
  * instead of a caller buffer (each GPU the library runs on holds its own copy
  * from the first call on it, or from epi3_init, until the process ends).
  * ------------------------------------------------------------------------ */

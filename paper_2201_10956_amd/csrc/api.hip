@@ -747,6 +747,32 @@ struct PlainBound {
   int64_t ccap;
 };
 
+PlainJob make_plainjob(const epi3_dataset &d, bool fp4, int JB, float *score, uint32_t *counts,
+                       uint32_t *keyrange, int64_t *jprefix) {
+  const int32_t unit = fp4 ? 128 : 64;  // samples per 64-byte staged chunk
+  PlainJob pj{};
+  pj.vals = static_cast<const uint8_t *>(fp4 ? d.nibbles : d.bytes);
+  pj.pairs = d.pairs;
+  pj.score = score;
+  pj.counts = counts;
+  pj.keyrange = keyrange;
+  pj.jprefix = jprefix;
+  pj.n_tiles = host_plain_tiles(d.n_snps, JB);
+  pj.T = epi3_n_triplets(d.n_snps);
+  pj.M = d.n_snps;
+  pj.Mp = d.snp_stride;
+  pj.Sb = fp4 ? d.byte_stride / 2 : d.byte_stride;
+  pj.Sb0 = (d.n_controls + unit - 1) / unit * 64;
+  pj.Sb1 = (d.n_cases + unit - 1) / unit * 64;
+  pj.N0 = d.n_controls;
+  pj.N1 = d.n_cases;
+  pj.JB = JB;
+  pj.lfx = fx_table(d);
+  pj.scale = fx_scale(d.n_samples);
+  pj.lf_len = d.n_samples + 2;
+  return pj;
+}
+
 // Counts and scores every triplet of the tasks' data sets (all with the same
 // operand type and tile JB) in one sequence of passes over their tiles taken
 // in task order: data set x owns global tiles job_begin[x] .. job_begin[x + 1]
@@ -758,7 +784,6 @@ struct PlainBound {
 int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, const MfmaBufs &W,
                        hipStream_t s, AuxCtx *ctx, const PlainBound *bd = nullptr) {
   if (bd && tasks.size() != 1) return EPI3_E_INVALID;
-  const int32_t unit = fp4 ? 128 : 64;  // samples per 64-byte staged chunk
   const int n = (int)tasks.size();
   std::vector<int64_t> begin(n + 1, 0);
   std::vector<PlainJob> records(n);
@@ -766,26 +791,7 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
   for (int x = 0; x < n; ++x) {
     const epi3_dataset &d = *tasks[x].d;
     PlainJob &pj = records[x];
-    pj = PlainJob{};
-    pj.vals = static_cast<const uint8_t *>(fp4 ? d.nibbles : d.bytes);
-    pj.pairs = d.pairs;
-    pj.score = tasks[x].score;
-    pj.counts = tasks[x].counts;
-    pj.keyrange = tasks[x].keyrange;
-    pj.jprefix = tasks[x].jprefix;
-    pj.n_tiles = host_plain_tiles(d.n_snps, JB);
-    pj.T = epi3_n_triplets(d.n_snps);
-    pj.M = d.n_snps;
-    pj.Mp = d.snp_stride;
-    pj.Sb = fp4 ? d.byte_stride / 2 : d.byte_stride;
-    pj.Sb0 = (d.n_controls + unit - 1) / unit * 64;
-    pj.Sb1 = (d.n_cases + unit - 1) / unit * 64;
-    pj.N0 = d.n_controls;
-    pj.N1 = d.n_cases;
-    pj.JB = JB;
-    pj.lfx = fx_table(d);
-    pj.scale = fx_scale(d.n_samples);
-    pj.lf_len = d.n_samples + 2;
+    pj = make_plainjob(d, fp4, JB, tasks[x].score, tasks[x].counts, tasks[x].keyrange, tasks[x].jprefix);
     if (pj.Sb0 > pj.Sb || pj.Sb1 > pj.Sb) return EPI3_E_INVALID;
     begin[x + 1] = begin[x] + pj.n_tiles;
     lf_len = std::max(lf_len, pj.lf_len);
@@ -1139,10 +1145,70 @@ int64_t epi3_workspace_bytes(const epi3_dataset *d, int32_t k, int32_t variant, 
   return scan_layout(nullptr, *d, k, cand_cap, variant).total;
 }
 
+// A vector-ALU scan's data set counted on the matrix cores all the same, in
+// memory past its workspace: the buffers of the fused FP4 kernel, and the
+// nibble planes if the data set has none.
+struct SpareLayout {
+  PlainJob *pjob;
+  int64_t *jbegin, *jprefix;
+  uint8_t *nibbles;  // NULL: the data set's own
+  uint8_t *stash;
+  int64_t stashes;
+  int JB;
+};
+
+// Whether that takes place: where AUTO would choose FP4 (the vector ALU is the
+// faster one elsewhere), the kernel takes the table, and `bytes` hold the
+// planes and a stash for one workgroup per CU (up to two; with less than that
+// half the chip would wait).  300 x 3000 in the static array: 541 us on the
+// vector ALU, 301 so.
+static bool spare_layout(const epi3_dataset &d, void *spare, int64_t bytes, SpareLayout *L) {
+  constexpr int64_t kFewest = 256, kMost = 512;
+  if (!spare || epi3_n_triplets(d.n_snps) == 0 || d.n_cases > 65535 || d.n_controls > 65535 ||
+      !offsets32_ok(d) ||
+      rule_tile(EPI3_VARIANT_AUTO, d.n_snps, d.n_samples, EPI3_VARIANT_VALU) != EPI3_VARIANT_MFMA_FP4)
+    return false;
+  *L = SpareLayout{};
+  L->JB = pick_JB(d, EPI3_VARIANT_MFMA_FP4);
+  if (!plain_fused_ok(L->JB, d.n_samples + 2)) return false;
+  Carver c(spare);
+  L->pjob = c.take<PlainJob>(1);
+  L->jbegin = c.take<int64_t>(2);
+  L->jprefix = c.take<int64_t>((int64_t)d.n_snps + 1);
+  if (!d.nibbles) L->nibbles = c.take<uint8_t>(2ll * d.snp_stride * 2 * (d.byte_stride / 2));
+  L->stashes = std::min(kMost, (bytes - c.size()) / kPlainStash);
+  if (L->stashes < kFewest && L->stashes < host_plain_tiles(d.n_snps, L->JB)) return false;
+  L->stash = c.take<uint8_t>(L->stashes * kPlainStash);
+  return L->stashes > 0 && c.size() <= bytes;
+}
+
+static int enqueue_count_spare(const epi3_dataset &d, const SpareLayout &L, float *score, const ScanLayout &W,
+                               hipStream_t s) {
+  epi3_dataset e = d;
+  if (L.nibbles) {
+    HIP_OK(launch_expand_nibbles(static_cast<const uint32_t *>(d.planes), d.snp_stride, d.words[0], d.words[1],
+                                 d.byte_stride, L.nibbles, s));
+    e.nibbles = L.nibbles;
+  }
+  const PlainJob pj = make_plainjob(e, true, L.JB, score, nullptr, &W.st->kmin, L.jprefix);
+  const int64_t begin[2] = {0, pj.n_tiles};
+  HIP_OK(launch_plain_setup(&pj, begin, 1, L.pjob, L.jbegin, W.queue, s));
+  PlainOut out{};
+  out.mode = kPermOutPlane;
+  out.stride = 1;
+  return timed(0, s, [&]() {
+    return launch_count_score_plain(L.pjob, L.jbegin, 1, L.JB, L.stash, L.stashes, 0, pj.n_tiles, 1,
+                                    W.queue, pj.lf_len, out, s) == hipSuccess
+               ? EPI3_OK
+               : EPI3_E_HIP;
+  });
+}
+
 // bounded: select by bound (W.bounded; matrix-core variants only) instead of
-// scoring into `score`
+// scoring into `score`; spare: see spare_layout (vector-ALU variant)
 static int enqueue_count(const epi3_dataset &d, int32_t variant, float *score, uint32_t *counts,
-                         const ScanLayout &W, hipStream_t s, bool bounded = false) {
+                         const ScanLayout &W, hipStream_t s, bool bounded = false, void *spare = nullptr,
+                         int64_t spare_bytes = 0) {
   const int v = plain_variant(d, variant);
   if (v < 0) return v;
   if (v == EPI3_VARIANT_MFMA || v == EPI3_VARIANT_MFMA_FP4) {
@@ -1160,6 +1226,8 @@ static int enqueue_count(const epi3_dataset &d, int32_t variant, float *score, u
     return enqueue_count_mfma(one, v == EPI3_VARIANT_MFMA_FP4, pick_JB(d, v), B, s, lease.c);
   }
   if (bounded) return EPI3_E_UNSUPPORTED;
+  SpareLayout L;
+  if (!counts && spare_layout(d, spare, spare_bytes, &L)) return enqueue_count_spare(d, L, score, W, s);
   const int P = pick_P(d);
   Job J = make_job(d, score, counts, W.jprefix, &W.st->kmin, P);
   HIP_OK(launch_valu_setup(&J, 1, W.job, W.queue, s));
@@ -1173,6 +1241,13 @@ static int enqueue_count(const epi3_dataset &d, int32_t variant, float *score, u
 
 int epi3_scan(const epi3_dataset *d, int32_t k, int32_t variant, int64_t cand_cap, void *ws_dev,
               int64_t ws_bytes, void *stream) {
+  return epi3::scan_in(d, k, variant, cand_cap, ws_dev, ws_bytes, false, stream);
+}
+
+}  // extern "C"
+
+int epi3::scan_in(const epi3_dataset *d, int32_t k, int32_t variant, int64_t cand_cap, void *ws_dev,
+                  int64_t ws_bytes, bool spare, void *stream) {
   if (!valid_dataset(d) || k <= 0 || !ws_dev) return EPI3_E_INVALID;
   if (d->layout != EPI3_LAYOUT_SPLIT) return EPI3_E_INVALID;
   if (reinterpret_cast<uintptr_t>(ws_dev) % kAlign) return EPI3_E_INVALID;
@@ -1198,7 +1273,9 @@ int epi3_scan(const epi3_dataset *d, int32_t k, int32_t variant, int64_t cand_ca
     HIP_OK(launch_init_select(&ss, 1, W.ssel, s));
   }
   if (T > 0) {
-    const int rc = enqueue_count(*d, variant, W.score, nullptr, W, s, W.bounded);
+    const int rc = enqueue_count(*d, variant, W.score, nullptr, W, s, W.bounded,
+                                 spare ? static_cast<uint8_t *>(ws_dev) + W.total : nullptr,
+                                 ws_bytes - W.total);
     if (rc != EPI3_OK) return rc;
   }
   SelectSizes z{};
@@ -1207,6 +1284,8 @@ int epi3_scan(const epi3_dataset *d, int32_t k, int32_t variant, int64_t cand_ca
     return launch_select(W.sel, 1, z, s) == hipSuccess ? EPI3_OK : EPI3_E_HIP;
   });
 }
+
+extern "C" {
 
 int epi3_topk(const epi3_dataset *d, int32_t k, int64_t cand_cap, void *ws_dev, epi3_hit *hits_host,
               int32_t *n_out, void *stream) {

@@ -139,6 +139,22 @@ __global__ void __launch_bounds__(256) encode_kernel(const uint8_t *__restrict__
   }
 }
 
+// Nibble planes of bit planes that were encoded without them: a thread per word
+// of a row (16 bytes out), runs of 16 words by consecutive threads, so the
+// stores are 256-byte runs and the scattered reads stay in L2.  300 x 3000: 3 us
+// for 2.4 MB, against the 415 us of vector-ALU counting it avoids.
+__global__ void __launch_bounds__(256) expand_nibbles_kernel(const uint32_t *__restrict__ planes,
+                                                             int32_t Mp, int32_t W0, int32_t W1, int32_t S,
+                                                             uint32_t *__restrict__ nib) {
+  const int c = blockIdx.z, W = c ? W1 : W0, off = c ? W0 : 0;
+  const int w = blockIdx.y * 16 + (threadIdx.x & 15);
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 4);  // 2 m + genotype
+  if (w >= S / 32) return;
+  const uint32_t b = w < W ? planes[(int64_t)(off + w) * Mp * 2 + row] : 0u;
+  *reinterpret_cast<uint4 *>(nib + ((int64_t)c * Mp * 2 + row) * (S / 8) + 4 * w) =
+      make_uint4(nibbles_of(b, 0), nibbles_of(b, 1), nibbles_of(b, 2), nibbles_of(b, 3));
+}
+
 // Pairwise tables out[c][x][y] = (n00, n01, n10, n11), n_ab = number of
 // samples of class c with genotype a at SNP x and b at SNP y (a, b in {0, 1}).
 // The diagonal holds the per-SNP counts (n_x(0), 0, 0, n_x(1)).
@@ -346,6 +362,14 @@ hipError_t launch_encode(const uint8_t *geno, int64_t ld, const int32_t *sample_
   hipLaunchKernelGGL(kernel, dim3(Mp / kEncSnps, (words + per - 1) / per, n_classes), dim3(256), 0, s,
                      geno, ld, sample_list, M, Mp, W0, W1, S, planes,
                      reinterpret_cast<uint32_t *>(bytes), reinterpret_cast<uint32_t *>(nib), status);
+  return hipGetLastError();
+}
+
+hipError_t launch_expand_nibbles(const uint32_t *planes, int32_t Mp, int32_t W0, int32_t W1, int32_t S,
+                                 uint8_t *nib, hipStream_t s) {
+  if (Mp % 8 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(expand_nibbles_kernel, dim3(Mp / 8, (S / 32 + 15) / 16, 2), dim3(256), 0, s, planes, Mp,
+                     W0, W1, S, reinterpret_cast<uint32_t *>(nib));
   return hipGetLastError();
 }
 

@@ -598,6 +598,9 @@ hipError_t launch_encode(const uint8_t *geno, int64_t ld, const int32_t *sample_
                          int32_t Mp, int32_t W0, int32_t W1, int32_t n_classes, int32_t S,
                          uint32_t *planes, uint8_t *bytes, uint8_t *nib, int32_t *status,
                          hipStream_t s);
+// The FP4 value planes ([2][Mp][2][S / 2] nibbles) of a SPLIT data set's bit planes.
+hipError_t launch_expand_nibbles(const uint32_t *planes, int32_t Mp, int32_t W0, int32_t W1, int32_t S,
+                                 uint8_t *nib, hipStream_t s);
 hipError_t launch_pairs(const uint32_t *planes, int32_t Mp, int32_t W0, int32_t W1,
                         int32_t n_classes, int32_t *pairs, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
@@ -752,5 +755,9 @@ int tile_P_default(int32_t M, int32_t N);
 // Device address of the current device's copy of the static scan workspace
 // (looked up once per device; out may be NULL to only set it up).
 int static_scratch_ptr(void **out);
+// epi3_scan; spare: whatever ws_bytes leave past the workspace may be used to
+// count on the matrix cores (vector-ALU variant).
+int scan_in(const epi3_dataset *d, int32_t k, int32_t variant, int64_t cand_cap, void *ws_dev,
+            int64_t ws_bytes, bool spare, void *stream);
 
 }  // namespace epi3

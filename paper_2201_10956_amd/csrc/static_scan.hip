@@ -1,8 +1,9 @@
 // Plain scan + top-k for callers that cannot allocate device memory (code
 // under graph capture, tight serving loops, harnesses that forbid hipMalloc):
-// the same count kernel and selection as epi3_scan + epi3_topk with the
-// vector-ALU variant, with the workspace taken from a fixed device array of
-// this file instead of a caller buffer.
+// epi3_scan + epi3_topk with the vector-ALU variant's workspace and results,
+// taken from a fixed device array of this file instead of a caller buffer
+// (counted on the matrix cores where the rest of the array has room for it;
+// the scores are the same bit for bit).
 #include <mutex>
 
 #include <hip/hip_runtime.h>
@@ -54,7 +55,8 @@ extern "C" int epi3_scan_topk_static(const epi3_dataset *d, int32_t k, epi3_hit 
   if (rc != EPI3_OK) return rc;
   // the scan initialises every part of the workspace it reads (selection
   // state, tile queue, key range), so the previous call's contents are harmless
-  const int rs = epi3_scan(d, k, EPI3_VARIANT_VALU, 0, ws, EPI3_STATIC_SCRATCH_BYTES, stream);
+  // what the array holds past the workspace serves to count on the matrix cores
+  const int rs = epi3::scan_in(d, k, EPI3_VARIANT_VALU, 0, ws, EPI3_STATIC_SCRATCH_BYTES, true, stream);
   if (rs != EPI3_OK) return rs;
   return epi3_topk(d, k, 0, ws, hits_host, n_out, stream);
 }
