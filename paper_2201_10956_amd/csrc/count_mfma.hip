@@ -554,7 +554,7 @@ __device__ __forceinline__ void count_perm_body(
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   if constexpr (FUSE != 0) {
-    for (int x = tid; x < lf_len; x += 256) sLf[x] = lfx[x];
+    table_to_lds<256>(sLf, lfx, lf_len);
     if (tid < 64) {
       sRange[tid][0] = 0xffffffffu;
       sRange[tid][1] = 0u;
@@ -967,7 +967,7 @@ __global__ void __launch_bounds__(256) finish_perm_kernel(const PermJob *__restr
   FinishPermLds &sh = *reinterpret_cast<FinishPermLds *>(lds + (LDS ? finish_perm_table_bytes(lf_len) : 0));
   if (LDS) {
     uint32_t *tab = reinterpret_cast<uint32_t *>(lds);
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) tab[x] = lfx[x];
+    table_to_lds<256>(tab, lfx, lf_len);
   }
   if (threadIdx.x < 64) {
     sh.range[threadIdx.x][0] = 0xffffffffu;

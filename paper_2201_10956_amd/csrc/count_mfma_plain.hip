@@ -688,7 +688,7 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
         keyrange = MODE == kPermOutSample ? out.range : rflp(pj.keyrange);
         lim = (uint32_t)(pj.lf_len < tab_cap ? pj.lf_len : tab_cap);
         dec.J = -1;
-        for (uint32_t x = tid; x < lim; x += 256) lds[x] = lfx[x];  // barrier below
+        table_to_lds<256>(lds, lfx, (int)lim);  // barrier below
       }
       place(tg - jd.lo);
       fetch(0);
@@ -1035,7 +1035,7 @@ __global__ void __launch_bounds__(256) finish_plain_kernel(const PlainJob *__res
       dec.J = -1;
       if (LDS) {
         __syncthreads();  // the previous job's lookups are done
-        for (int x = threadIdx.x; x < pj.lf_len; x += 256) lds[x] = lfx[x];
+        table_to_lds<256>(lds, lfx, pj.lf_len);
         __syncthreads();
       }
     }

@@ -217,8 +217,7 @@ __global__ void __launch_bounds__(256) count_valu_kernel(const Job *__restrict__
   int j = -1;
   int64_t jlo = 0, jhi = 0;
   if (LDS && !MULTI) {
-    const uint32_t *tab = cj[0].lfx;
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) sLds[x] = tab[x];
+    table_to_lds<256>(sLds, cj[0].lfx, lf_len);
     __syncthreads();
   }
 
@@ -247,9 +246,7 @@ __global__ void __launch_bounds__(256) count_valu_kernel(const Job *__restrict__
       jlo = jhi = 0;
       j = -1;
       if (LDS && MULTI) {  // workgroup-uniform: t is
-        const uint32_t *tab = cj[job].lfx;
-        const int len = cj[job].lf_len;
-        for (int x = threadIdx.x; x < len; x += blockDim.x) sLds[x] = tab[x];
+        table_to_lds<256>(sLds, cj[job].lfx, cj[job].lf_len);
         __syncthreads();
       }
     }

@@ -22,6 +22,27 @@ constexpr int kSampleStride = 32;
 // (the sample must hold comfortably more than k scores).
 inline bool sample_select(int64_t T, int64_t k) { return T >= (1ll << 22) && k * 512 <= T; }
 
+// Copies n words of a log-factorial table (16-byte aligned) to LDS with all
+// threads of the workgroup, four 16-byte loads in flight per thread (one word
+// per step waits for memory once per 256 words: with it a 2048 x 16384 pair
+// scan takes 235 us instead of 228).
+template <int THREADS>
+__device__ __forceinline__ void table_to_lds(uint32_t *dst, const uint32_t *src, int n) {
+  const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
+  uint4 *d4 = reinterpret_cast<uint4 *>(dst);
+  const int n4 = n >> 2;
+  int x = threadIdx.x;
+  for (; x + 3 * THREADS < n4; x += 4 * THREADS) {
+    const uint4 a = s4[x], b = s4[x + THREADS], c = s4[x + 2 * THREADS], d = s4[x + 3 * THREADS];
+    d4[x] = a;
+    d4[x + THREADS] = b;
+    d4[x + 2 * THREADS] = c;
+    d4[x + 3 * THREADS] = d;
+  }
+  for (; x < n4; x += THREADS) d4[x] = s4[x];
+  if ((int)threadIdx.x < n - 4 * n4) dst[4 * n4 + threadIdx.x] = src[4 * n4 + threadIdx.x];
+}
+
 // Pointer into the constant address space: uniform loads through it become
 // scalar (s_load) instructions.  Only used for memory no kernel writes while
 // the reading kernel runs.

@@ -62,7 +62,7 @@ __global__ void __launch_bounds__(256) quad_scores_kernel(
     uint32_t *__restrict__ keyrange) {
   extern __shared__ uint32_t tab[];  // no static LDS: the table starts at LDS address 0
   if (LDS) {
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) tab[x] = lfx[x];
+    table_to_lds<256>(tab, lfx, lf_len);
     __syncthreads();
   }
   const int64_t MpMp4 = (int64_t)Mp * Mp * 4;

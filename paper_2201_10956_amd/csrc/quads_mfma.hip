@@ -329,7 +329,7 @@ __global__ void __launch_bounds__(256) finish_quad_kernel(
   // per-SNP counts of the tile's l range follow it
   extern __shared__ uint32_t qtab[];
   if (LDS) {
-    for (int x = threadIdx.x; x < lf_len; x += blockDim.x) qtab[x] = lfx[x];
+    table_to_lds<256>(qtab, lfx, lf_len);
   }
   int2(*sml)[kQLB] = reinterpret_cast<int2(*)[kQLB]>(
       reinterpret_cast<unsigned char *>(qtab) + (LDS ? (lf_len * 4 + 15) / 16 * 16 : 0));
