@@ -589,6 +589,14 @@ __device__ __forceinline__ uint32_t lo_x4(uint32_t v, uint32_t two) {
       : "v"(two), "v"(v));
   return r;
 }
+// 4 x the high half of v.
+__device__ __forceinline__ uint32_t hi_x4(uint32_t v, uint32_t two) {
+  uint32_t r;
+  asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+      : "=v"(r)
+      : "v"(two), "v"(v));
+  return r;
+}
 // K2 of a table of R rows given as byte offsets (4 x count), in fixed point:
 // sum over rows of L[r + 1] - L[r_0] - L[r_1].  LDS: table at LDS address 0.
 template <int R, bool LDS>

@@ -14,9 +14,9 @@
 namespace epi3 {
 namespace {
 
-// Corner cells of every triplet per class: t3[c * T + rank] = cells
-// 4 a + 2 b + c (a, b, c in {0, 1}) as 8 x 16 bits, two per word, low half
-// first.  Thread per triplet.
+// Corner cells of every triplet: t3[2 rank + x / 4] word x % 4 = the counts of
+// cell x = 4 a + 2 b + c (a, b, c in {0, 1}) in both classes, class 1 in the
+// high half.  Thread per triplet.
 __global__ void __launch_bounds__(256) triplet_corners_kernel(const uint32_t *__restrict__ planes,
                                                               int32_t M, int32_t Mp, int32_t W0,
                                                               int32_t W1, int64_t T,
@@ -26,9 +26,11 @@ __global__ void __launch_bounds__(256) triplet_corners_kernel(const uint32_t *__
        r += (int64_t)gridDim.x * blockDim.x) {
     int i, j, k;
     decode_rank(M, r, i, j, k);
+    uint32_t n[2][8];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      uint32_t n[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int x = 0; x < 8; ++x) n[c][x] = 0u;
       for (int w = c ? W0 : 0; w < (c ? W0 + W1 : W0); ++w) {
         const uint2 *row = pv + (int64_t)w * Mp;
         const uint2 xi = row[i], xj = row[j], xk = row[k];
@@ -38,19 +40,25 @@ __global__ void __launch_bounds__(256) triplet_corners_kernel(const uint32_t *__
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
             const uint32_t ij = X[0][a] & X[1][b];
-            n[4 * a + 2 * b] += __builtin_popcount(ij & X[2][0]);
-            n[4 * a + 2 * b + 1] += __builtin_popcount(ij & X[2][1]);
+            n[c][4 * a + 2 * b] += __builtin_popcount(ij & X[2][0]);
+            n[c][4 * a + 2 * b + 1] += __builtin_popcount(ij & X[2][1]);
           }
       }
-      t3[c * T + r] = make_uint4(n[0] | (n[1] << 16), n[2] | (n[3] << 16), n[4] | (n[5] << 16),
-                                 n[6] | (n[7] << 16));
     }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      t3[2 * r + h] = make_uint4(n[0][4 * h] | (n[1][4 * h] << 16), n[0][4 * h + 1] | (n[1][4 * h + 1] << 16),
+                                 n[0][4 * h + 2] | (n[1][4 * h + 2] << 16),
+                                 n[0][4 * h + 3] | (n[1][4 * h + 3] << 16));
   }
 }
 
-__device__ __forceinline__ void unpack8(uint4 v, uint32_t *n) {
-  n[0] = v.x & 0xffffu; n[1] = v.x >> 16; n[2] = v.y & 0xffffu; n[3] = v.y >> 16;
-  n[4] = v.z & 0xffffu; n[5] = v.z >> 16; n[6] = v.w & 0xffffu; n[7] = v.w >> 16;
+// Class c's corner cells of triplet `rank`.
+__device__ __forceinline__ void unpack8(const uint4 *t3, int64_t rank, int c, uint32_t *n) {
+  const uint4 v = t3[2 * rank], w = t3[2 * rank + 1];
+  const int s = 16 * c;
+  n[0] = (v.x >> s) & 0xffffu; n[1] = (v.y >> s) & 0xffffu; n[2] = (v.z >> s) & 0xffffu; n[3] = (v.w >> s) & 0xffffu;
+  n[4] = (w.x >> s) & 0xffffu; n[5] = (w.y >> s) & 0xffffu; n[6] = (w.z >> s) & 0xffffu; n[7] = (w.w >> s) & 0xffffu;
 }
 
 // T3: sub-triplet corners from the triplet table (else counted per quad).
@@ -58,7 +66,7 @@ template <bool LDS, bool T3>
 __global__ void __launch_bounds__(256) quad_scores_kernel(
     const uint32_t *__restrict__ planes, const int32_t *__restrict__ pairs, int32_t M, int32_t Mp,
     int32_t W0, int32_t W1, int32_t N0, int32_t N1, const uint32_t *__restrict__ lfx, int32_t lf_len,
-    float scale, int64_t Q, const uint4 *__restrict__ t3, int64_t T, float *__restrict__ score,
+    float scale, int64_t Q, const uint4 *__restrict__ t3, float *__restrict__ score,
     uint32_t *__restrict__ keyrange) {
   extern __shared__ uint32_t tab[];  // no static LDS: the table starts at LDS address 0
   if (LDS) {
@@ -77,11 +85,10 @@ __global__ void __launch_bounds__(256) quad_scores_kernel(
       const int w0 = c ? W0 : 0, w1 = c ? W0 + W1 : W0;
       if (T3) {
         quad_corner_counts(planes, Mp, w0, w1, i, j, k, l, cnt);
-        const uint4 *tc = t3 + c * T;
-        unpack8(tc[lex_base(M, i, j) + k], cnt + 16);
-        unpack8(tc[lex_base(M, i, j) + l], cnt + 24);
-        unpack8(tc[lex_base(M, i, k) + l], cnt + 32);
-        unpack8(tc[lex_base(M, j, k) + l], cnt + 40);
+        unpack8(t3, lex_base(M, i, j) + k, c, cnt + 16);
+        unpack8(t3, lex_base(M, i, j) + l, c, cnt + 24);
+        unpack8(t3, lex_base(M, i, k) + l, c, cnt + 32);
+        unpack8(t3, lex_base(M, j, k) + l, c, cnt + 40);
       } else {
         quad_counts(planes, Mp, w0, w1, 1, i, j, k, l, cnt);
       }
@@ -141,7 +148,7 @@ hipError_t launch_quad_scores_t(const epi3_dataset &d, const uint4 *t3, float *s
   hipLaunchKernelGGL((quad_scores_kernel<LDS, T3>), dim3((unsigned)blocks), dim3(256), lds, s,
                      static_cast<const uint32_t *>(d.planes), d.pairs, M, d.snp_stride, d.words[0],
                      d.words[1], d.n_controls, d.n_cases, fx_table(d), lf_len,
-                     fx_scale(d.n_samples), Q, t3, T, score, keyrange);
+                     fx_scale(d.n_samples), Q, t3, score, keyrange);
   return hipGetLastError();
 }
 

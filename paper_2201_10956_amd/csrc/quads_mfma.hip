@@ -310,32 +310,83 @@ __global__ void __launch_bounds__(256, 2) count_mfma_quad_kernel(
   }
 }
 
-// the 8 corner cells of a triplet-table entry, each x 4
-__device__ __forceinline__ void unpack8q(uint4 v, uint32_t *n) {
-  n[0] = (v.x & 0xffffu) << 2; n[1] = (v.x >> 16) << 2; n[2] = (v.y & 0xffffu) << 2; n[3] = (v.y >> 16) << 2;
-  n[4] = (v.z & 0xffffu) << 2; n[5] = (v.z >> 16) << 2; n[6] = (v.w & 0xffffu) << 2; n[7] = (v.w >> 16) << 2;
-}
+// LDS of the finish kernel past the log-factorial table, per tile: the 27 cells
+// of the sub-triplets (i, j, k) (64 of them), cells (a, b, d < 2) of (i, j, l)
+// (128), all as two 16-bit counts (class 1 in the high half), and the ranks'
+// bases.  Rows of 28 and 20 words: 16-byte reads without bank conflicts.
+constexpr int kQTijk = 28, kQTijl = 20;
+struct FinishQuadLds {
+  uint32_t ijk[4 * kQKB][kQTijk];
+  uint32_t ijl[4 * kQLB][kQTijl];
+  int64_t ik[4 * kQKB];    // lexicographic rank of triplet (i, k, l) - l
+  int64_t quad[4 * kQKB];  // and of the quad (i, j, k, l) - l
+};
 
-// Completes both 81-row tables of every quad of the pass's tiles and scores
-// them (workgroup per tile, round robin; thread per quad, consecutive l).
+// Three rows' lookups: L[r + 1], L[r_0], L[r_1].
+struct QuadLookups {
+  uint32_t u[3], d0[3], d1[3];
+};
+
+// Completes the 81-row tables of every quad of the pass's tiles and scores them
+// (workgroup per tile, round robin; thread = l and two of the k, four i each).
+// Both classes are completed at once, two 16-bit counts per register.  The
+// tables of the sub-triplets (i, j, k) and (i, j, l), which many quads share,
+// are completed once per tile into LDS; (i, k, l) and (j, k, l) come from the
+// triplet table (the latter once per four quads).  Rows are taken three at a
+// time and their lookups added two steps later, so vector instructions (about
+// 600 per quad and wave) and lookups (243) alternate: issue is what bounds it.
+// 123 registers, four waves per SIMD.  Against one class at a time in 32 bits
+// with all sub-triplets completed per quad (204 registers, all 243 lookups
+// after the table), whole scans: 256 x 4096 15.0 -> 11.7 ms, 200 x 3000 7.5 ->
+// 5.6 ms, 128 x 1000 1161 -> 853 us.
 template <bool LDS>
-__global__ void __launch_bounds__(256) finish_quad_kernel(
+__global__ void __launch_bounds__(256, 3) finish_quad_kernel(
     const uint2 *__restrict__ corners, const int64_t *__restrict__ pre_p,
     const uint4 *__restrict__ t3, const int32_t *__restrict__ pairs, int M, int Mp, int N0,
-    int N1, int64_t T, int64_t tile_begin, int64_t n_tiles, const uint32_t *__restrict__ lfx,
+    int N1, int64_t tile_begin, int64_t n_tiles, const uint32_t *__restrict__ lfx,
     int lf_len, float scale, float *__restrict__ score, uint32_t *__restrict__ keyrange) {
   // the LDS table starts the kernel's dynamic LDS block, at LDS address 0
-  // (no static LDS), so a lookup is one ds_read at the byte offset; the
-  // per-SNP counts of the tile's l range follow it
-  extern __shared__ uint32_t qtab[];
-  if (LDS) {
-    table_to_lds<256>(qtab, lfx, lf_len);
-  }
-  int2(*sml)[kQLB] = reinterpret_cast<int2(*)[kQLB]>(
-      reinterpret_cast<unsigned char *>(qtab) + (LDS ? (lf_len * 4 + 15) / 16 * 16 : 0));
+  // (no static LDS), so a lookup is one ds_read at the byte offset
+  extern __shared__ __attribute__((aligned(16))) uint32_t qtab[];
+  if (LDS) table_to_lds<256>(qtab, lfx, lf_len);
+  FinishQuadLds &sh = *reinterpret_cast<FinishQuadLds *>(reinterpret_cast<unsigned char *>(qtab) +
+                                                         (LDS ? (lf_len * 4 + 15) / 16 * 16 : 0));
+  auto at = [&](uint32_t off) { return LDS ? fx_at_lds0((int)off) : fx_at(lfx, (int)off); };
   cptr<int64_t> pre = as_const(pre_p);
-  const int64_t MpMp4 = (int64_t)Mp * Mp * 4;
+  const int4 *pr = reinterpret_cast<const int4 *>(pairs);
+  const int64_t MpMp = (int64_t)Mp * Mp;
+  // both classes' entries of a pair
+  auto pair4 = [&](int x, int y, u16x2 v[4]) {
+    const int64_t e = (int64_t)x * Mp + y;
+    const int4 a = pr[e], b = pr[MpMp + e];
+    v[0] = as_u16x2((uint32_t)a.x | ((uint32_t)b.x << 16));
+    v[1] = as_u16x2((uint32_t)a.y | ((uint32_t)b.y << 16));
+    v[2] = as_u16x2((uint32_t)a.z | ((uint32_t)b.z << 16));
+    v[3] = as_u16x2((uint32_t)a.w | ((uint32_t)b.w << 16));
+  };
+  auto corners8 = [&](int64_t rank, u16x2 v[8]) {
+    const uint4 a = t3[2 * rank], b = t3[2 * rank + 1];
+    v[0] = as_u16x2(a.x); v[1] = as_u16x2(a.y); v[2] = as_u16x2(a.z); v[3] = as_u16x2(a.w);
+    v[4] = as_u16x2(b.x); v[5] = as_u16x2(b.y); v[6] = as_u16x2(b.z); v[7] = as_u16x2(b.w);
+  };
+  // the 27 cells of the triplet (x, y, z)
+  auto table27 = [&](int x, int y, int z, u16x2 t[27]) {
+    u16x2 n[8], pxy[4], pxz[4], pyz[4], mx[4], my[4], mz[4], fyz[9];
+    corners8(lex_base(M, x, y) + z, n);
+    pair4(x, y, pxy);
+    pair4(x, z, pxz);
+    pair4(y, z, pyz);
+    pair4(x, x, mx);
+    pair4(y, y, my);
+    pair4(z, z, mz);
+    const u16x2 my2[2] = {my[0], my[3]}, mz2[2] = {mz[0], mz[3]};
+    pair_cells(pyz, my2, mz2, as_u16x2((uint32_t)N0 | ((uint32_t)N1 << 16)), fyz);
+    const u16x2 pxy2[2] = {mx[0] - pxy[0] - pxy[1], mx[3] - pxy[2] - pxy[3]};
+    complete27(n, fyz, pxy, pxy2, pxz, t);
+  };
   uint32_t kmin = 0xffffffffu, kmax = 0u;
+  uint32_t two = 2u;
+  asm volatile("" : "+v"(two));
   int j = -1;
   int64_t jlo = 0, jhi = 0;
   for (int64_t slot = blockIdx.x; slot < n_tiles; slot += gridDim.x) {
@@ -347,53 +398,128 @@ __global__ void __launch_bounds__(256) finish_quad_kernel(
     }
     int ib, kb, lb;
     q_decode(M, j, t - jlo, ib, kb, lb);
-    // per-SNP counts of the tile's 32 l (pair-table diagonals) into LDS: one
-    // conflict-free LDS read per lane instead of a strided global load
     __syncthreads();  // previous tile's readers are done (and the table is in)
-    if (threadIdx.x < 2 * kQLB) {
-      const int c = threadIdx.x / kQLB, ll = threadIdx.x % kQLB;
-      const int l = lb * kQLB + ll < Mp ? lb * kQLB + ll : Mp - 1;
-      const int4 v = reinterpret_cast<const int4 *>(pairs + c * MpMp4)[(int64_t)l * Mp + l];
-      sml[c][ll] = make_int2(v.x << 2, v.w << 2);
+    if (threadIdx.x < 4 * kQKB) {
+      const int x = threadIdx.x, i = 4 * ib + x / kQKB, k = kb * kQKB + x % kQKB;
+      if (i < j && k > j && k < M) {
+        u16x2 c[27];
+        table27(i, j, k, c);
+#pragma unroll
+        for (int y = 0; y < 27; ++y) sh.ijk[x][y] = as_u32(c[y]);
+        sh.ik[x] = lex_base(M, i, k);
+        sh.quad[x] = quad_rank(M, i, j, k, k + 1) - (k + 1);
+      }
+    } else if (threadIdx.x < 4 * kQKB + 4 * kQLB) {
+      const int x = threadIdx.x - 4 * kQKB, i = 4 * ib + x / kQLB, l = lb * kQLB + x % kQLB;
+      if (i < j && l > j && l < M) {
+        u16x2 c[27];
+        table27(i, j, l, c);
+#pragma unroll
+        for (int ab = 0; ab < 9; ++ab) {
+          sh.ijl[x][2 * ab] = as_u32(c[3 * ab]);
+          sh.ijl[x][2 * ab + 1] = as_u32(c[3 * ab + 1]);
+        }
+      }
     }
     __syncthreads();
-    for (int x = threadIdx.x; x < 4 * kQKB * kQLB; x += blockDim.x) {
-      const int ll = x & (kQLB - 1), kk = (x / kQLB) & (kQKB - 1), w = x / (kQLB * kQKB);
-      const int i = 4 * ib + w, k = kb * kQKB + kk, l = lb * kQLB + ll;
-      if (i >= j || k <= j || l <= k || l >= M) continue;
-      int tc[2][81];
+    const int ll = threadIdx.x & (kQLB - 1), l = lb * kQLB + ll;
+    const int ni = j - 4 * ib < 4 ? j - 4 * ib : 4;  // pivots i below j
+    for (int half = 0; half < 2; ++half) {
+      const int kk = (threadIdx.x >> 5) + 8 * half, k = kb * kQKB + kk;
+      if (k <= j || l <= k || l >= M) continue;
+      u16x2 jkl[8], pkl[4];
+      corners8(lex_base(M, j, k) + l, jkl);
+      pair4(k, l, pkl);
+      const uint4 *rec = reinterpret_cast<const uint4 *>(corners + ((slot * 8) * kQKB + kk) * 128 + ll * 4);
+      // one i ahead: the counted cells of both classes, and (i, k, l)
+      uint4 next[4], nikl[2];
+      auto fetch = [&](int w) {
+        const uint4 *r0 = rec + (int64_t)w * (kQKB * 64), *r1 = r0 + 4 * kQKB * 64;
+        next[0] = r0[0];
+        next[1] = r0[1];
+        next[2] = r1[0];
+        next[3] = r1[1];
+        const int64_t e = 2 * (sh.ik[w * kQKB + kk] + l);
+        nikl[0] = t3[e];
+        nikl[1] = t3[e + 1];
+      };
+      fetch(0);
+      for (int w = 0; w < ni; ++w) {
+        const uint4 v[2][2] = {{next[0], next[1]}, {next[2], next[3]}};  // [class][d]
+        const u16x2 ikl[8] = {as_u16x2(nikl[0].x), as_u16x2(nikl[0].y), as_u16x2(nikl[0].z), as_u16x2(nikl[0].w),
+                              as_u16x2(nikl[1].x), as_u16x2(nikl[1].y), as_u16x2(nikl[1].z), as_u16x2(nikl[1].w)};
+        if (w + 1 < ni) fetch(w + 1);
+        // cells (c, d < 2) of the rows (a, b): counted for a, b < 2
+        u16x2 core[9][4];
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const uint4 *rec = reinterpret_cast<const uint4 *>(
-            corners + (((slot * 2 + c) * 4 + w) * kQKB + kk) * 128 + ll * 4);
-        const uint4 v[2] = {rec[0], rec[1]};  // columns (l, d = 0) and (l, d = 1)
-        uint32_t cnt[48];
-        // uint2 (d, c') = (cells (0, 0) | (0, 1) << 16, (1, 0) | (1, 1) << 16) over (a, b)
-#pragma unroll
-        for (int d = 0; d < 2; ++d)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
           for (int cc = 0; cc < 2; ++cc)
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-              const uint32_t wd = a ? (cc ? v[d].w : v[d].y) : (cc ? v[d].z : v[d].x);
-              cnt[8 * a + 2 * cc + d] = (wd & 0xffffu) << 2;
-              cnt[8 * a + 4 + 2 * cc + d] = (wd >> 16) << 2;
+            for (int d = 0; d < 2; ++d) {
+              const uint32_t w0 = a ? (cc ? v[0][d].w : v[0][d].y) : (cc ? v[0][d].z : v[0][d].x);
+              const uint32_t w1 = a ? (cc ? v[1][d].w : v[1][d].y) : (cc ? v[1][d].z : v[1][d].x);
+              core[3 * a][2 * cc + d] = as_u16x2(__builtin_amdgcn_perm(w1, w0, 0x05040100u));
+              core[3 * a + 1][2 * cc + d] = as_u16x2(__builtin_amdgcn_perm(w1, w0, 0x07060302u));
             }
-        const uint4 *tcl = t3 + c * T;
-        unpack8q(tcl[lex_base(M, i, j) + k], cnt + 16);
-        unpack8q(tcl[lex_base(M, i, j) + l], cnt + 24);
-        unpack8q(tcl[lex_base(M, i, k) + l], cnt + 32);
-        unpack8q(tcl[lex_base(M, j, k) + l], cnt + 40);
-        // cells as byte offsets into the table (x 4)
-        const int2 mlv = sml[c][ll];
-        const int ml[2] = {mlv.x, mlv.y};
-        quad_cells<2>(cnt, pairs + c * MpMp4, Mp, i, j, k, l, (c ? N1 : N0) << 2, tc[c], ml);
+        const uint32_t *tijk = sh.ijk[w * kQKB + kk], *tijl = sh.ijl[w * kQLB + ll];
+        uint32_t up = 0u, down = 0u;
+        QuadLookups in_flight[2];
+        auto add_up = [&](int n) {
+          const QuadLookups &f = in_flight[n & 1];
+          up += f.u[0] + f.u[1];
+          up += f.u[2];
+          down += f.d0[0] + f.d1[0];
+          down += f.d0[1] + f.d1[1];
+          down += f.d0[2] + f.d1[2];
+          asm volatile("" : "+v"(up), "+v"(down));  // (keeps the additions of different steps apart)
+        };
+        auto step = [&](int n, u16x2 r0, u16x2 r1, u16x2 r2) {
+          const uint32_t r[3] = {as_u32(r0), as_u32(r1), as_u32(r2)};
+          uint32_t lo[3], hi[3];
+#pragma unroll
+          for (int x = 0; x < 3; ++x) {
+            lo[x] = lo_x4(r[x], two);
+            hi[x] = hi_x4(r[x], two);
+          }
+          if (n >= 2) add_up(n - 2);
+          QuadLookups &f = in_flight[n & 1];
+#pragma unroll
+          for (int x = 0; x < 3; ++x) {
+            f.u[x] = at(lo[x] + hi[x] + 4u);
+            f.d0[x] = at(lo[x]);
+            f.d1[x] = at(hi[x]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        };
+#pragma unroll
+        for (int ab = 0; ab < 9; ++ab) {
+          u16x2 (&q)[4] = core[ab];
+          if (ab == 2 || ab == 5) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) q[x] = ikl[(ab == 2 ? 0 : 4) + x] - core[ab - 2][x] - core[ab - 1][x];
+          } else if (ab == 6 || ab == 7) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) q[x] = jkl[4 * (ab - 6) + x] - core[ab - 6][x] - core[ab - 3][x];
+          } else if (ab == 8) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) q[x] = (pkl[x] - ikl[x] - ikl[4 + x]) - core[6][x] - core[7][x];
+          }
+          const u16x2 e0 = as_u16x2(tijl[2 * ab]) - q[0] - q[2], e1 = as_u16x2(tijl[2 * ab + 1]) - q[1] - q[3];
+          const u16x2 f0 = as_u16x2(tijk[3 * ab]) - q[0] - q[1], f1 = as_u16x2(tijk[3 * ab + 1]) - q[2] - q[3];
+          const u16x2 f2 = as_u16x2(tijk[3 * ab + 2]) - e0 - e1;
+          step(3 * ab, q[0], q[1], q[2]);
+          step(3 * ab + 1, q[3], e0, e1);
+          step(3 * ab + 2, f0, f1, f2);
+        }
+        add_up(25);
+        add_up(26);
+        const float k2 = fx_score(up - down, scale);
+        score[sh.quad[w * kQKB + kk] + l] = k2;
+        const uint32_t key = f2key(k2);
+        kmin = key < kmin ? key : kmin;
+        kmax = key > kmax ? key : kmax;
       }
-      const float k2 = fx_score(fx_sum<81, LDS>(tc[0], tc[1], lfx), scale);
-      score[quad_rank(M, i, j, k, l)] = k2;
-      const uint32_t key = f2key(k2);
-      kmin = key < kmin ? key : kmin;
-      kmax = key > kmax ? key : kmax;
     }
   }
 #pragma unroll
@@ -413,7 +539,7 @@ hipError_t launch_finish_quad_t(const epi3_dataset &d, const uint2 *corners, con
                                 const uint4 *t3, int64_t tile_begin, int64_t n_tiles,
                                 float *score, uint32_t *keyrange, int n_cu, hipStream_t s) {
   const int lf_len = d.n_samples + 2;
-  const int lds = (LDS ? (lf_len * 4 + 15) / 16 * 16 : 0) + 2 * kQLB * (int)sizeof(int2);
+  const int lds = (LDS ? (lf_len * 4 + 15) / 16 * 16 : 0) + (int)sizeof(FinishQuadLds);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&finish_quad_kernel<LDS>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
@@ -424,7 +550,7 @@ hipError_t launch_finish_quad_t(const epi3_dataset &d, const uint2 *corners, con
   if (blocks > n_tiles) blocks = n_tiles;
   hipLaunchKernelGGL(finish_quad_kernel<LDS>, dim3((unsigned)blocks), dim3(256), lds, s, corners,
                      pre, t3, d.pairs, d.n_snps, d.snp_stride, d.n_controls, d.n_cases,
-                     c3(d.n_snps), tile_begin, n_tiles, fx_table(d), lf_len, fx_scale(d.n_samples),
+                     tile_begin, n_tiles, fx_table(d), lf_len, fx_scale(d.n_samples),
                      score, keyrange);
   return hipGetLastError();
 }
