@@ -922,12 +922,24 @@ static int order_scan(const epi3_dataset *d, int order, int32_t k, int64_t cand_
   S.err2 = 2.0 * order_error_bound(order, d->n_samples);
   HIP_OK(launch_init_select(&S, 1, W.sel, s));
   if (T > 0 && W.qmfma) {
+    HIP_OK(launch_triplet_corners(*d, W.t3, s));
+    HIP_OK(launch_quad_prefix(d->n_snps, W.qprefix, s));
+  }
+  if (T > 0 && W.qmfma && quad_fused_ok(*d)) {
+    HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 2, s));
+    rc = timed(0, s, [&]() {
+      return launch_count_score_quad(*d, W.qprefix, W.t3, W.queue, W.qscratch,
+                                     2 * W.pass_tiles * kQuadTileScratch / kQuadStash, W.score, &W.st->kmin,
+                                     s) == hipSuccess
+                 ? EPI3_OK
+                 : EPI3_E_HIP;
+    });
+    if (rc != EPI3_OK) return rc;
+  } else if (T > 0 && W.qmfma) {
     // quads on the matrix cores: pass p of tiles is counted (timed as the
     // count stage) into scratch buffer p % 2 on `s`; its finish kernel (timed
     // as table completion) runs on the library's second stream while `s`
     // counts pass p + 1, and count p + 2 waits for finish p (same buffer)
-    HIP_OK(launch_triplet_corners(*d, W.t3, s));
-    HIP_OK(launch_quad_prefix(d->n_snps, W.qprefix, s));
     AuxLease lease;
     if (lease.rc != EPI3_OK) return lease.rc;
     hipStream_t s2 = lease.c->s2;

@@ -720,6 +720,14 @@ hipError_t launch_count_mfma_quad(const epi3_dataset &d, const int64_t *jprefix,
                                   unsigned long long *queue, int64_t tile_begin, int64_t n_tiles,
                                   void *scratch, hipStream_t s);
 // completes and scores the quads of those tiles (t3: launch_triplet_corners)
+// Counted and scored in one kernel, where the table leaves room for two
+// workgroups per CU (about 12000 samples); stash: kQuadStash bytes per workgroup,
+// at most max_blocks of them; queue: one zeroed counter.
+constexpr int64_t kQuadStash = 64 * 1024;
+bool quad_fused_ok(const epi3_dataset &d);
+hipError_t launch_count_score_quad(const epi3_dataset &d, const int64_t *jprefix, const void *t3,
+                                   unsigned long long *queue, void *stash, int64_t max_blocks, float *score,
+                                   uint32_t *keyrange, hipStream_t s);
 hipError_t launch_finish_quad(const epi3_dataset &d, const void *scratch, const int64_t *jprefix,
                               const void *t3, int64_t tile_begin, int64_t n_tiles, float *score,
                               uint32_t *keyrange, hipStream_t s);
