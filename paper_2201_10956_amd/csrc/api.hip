@@ -396,7 +396,7 @@ OrderLayout order_layout(void *ws, const epi3_dataset &d, int order, int32_t k, 
   if (order == 4 && T > 0 && mfma_supported(d)) {
     L.qmfma = true;
     L.qprefix = c.take<int64_t>((int64_t)d.n_snps + 1);
-    L.queue = c.take<unsigned long long>(4);
+    L.queue = c.take<unsigned long long>(8);
     const int64_t tiles = host_quad_tiles(d.n_snps);
     L.pass_tiles = std::max<int64_t>(
         1, std::min<int64_t>(tiles, pass_bytes(kQuadPassBytes) / kQuadTileScratch));
@@ -926,7 +926,7 @@ static int order_scan(const epi3_dataset *d, int order, int32_t k, int64_t cand_
     HIP_OK(launch_quad_prefix(d->n_snps, W.qprefix, s));
   }
   if (T > 0 && W.qmfma && quad_fused_ok(*d)) {
-    HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 2, s));
+    HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 16, s));
     rc = timed(0, s, [&]() {
       return launch_count_score_quad(*d, W.qprefix, W.t3, W.queue, W.qscratch,
                                      2 * W.pass_tiles * kQuadTileScratch / kQuadStash, W.score, &W.st->kmin,

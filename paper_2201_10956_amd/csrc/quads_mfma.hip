@@ -425,8 +425,7 @@ __device__ __forceinline__ uint32_t score_quad(u16x2 (&core)[9][4], const u16x2 
               f.d0[x] = at(lo[x]);
               f.d1[x] = at(hi[x]);
             }
-            __builtin_amdgcn_sched_barrier(0);
-          };
+                  };
   #pragma unroll
           for (int ab = 0; ab < 9; ++ab) {
             u16x2 (&q)[4] = core[ab];
