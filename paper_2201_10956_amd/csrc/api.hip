@@ -1768,8 +1768,9 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
       HIP_OK(launch_mask_bytes(W.masks + (int64_t)g * kPermGroup, Q, kPermGroup, d.n_samples,
                                d.byte_stride, const_cast<uint8_t *>(pj.ph),
                                const_cast<int32_t *>(pj.n1), fp4, s));
-      HIP_OK(launch_case_pairs(static_cast<const uint32_t *>(d.planes), d.snp_stride, d.words[0],
+      HIP_OK(launch_case_pairs(static_cast<const uint32_t *>(d.planes), d.n_snps, d.snp_stride, d.words[0],
                                W.masks + (int64_t)g * kPermGroup, Q, kPermGroup,
+                               fp4 && perm_fused_ok(d.n_samples + 2) && Q <= 32,
                                const_cast<int32_t *>(pj.case_pairs), s));
       hipStream_t s2 = lease.c->s2;
       hipEvent_t ev_start = lease.c->ev[0], ev_cnt[2] = {lease.c->ev[1], lease.c->ev[2]},

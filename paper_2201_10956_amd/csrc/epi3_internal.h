@@ -696,9 +696,10 @@ hipError_t launch_perm_setup(const PermJob &pj, const PermJob &alt, PermJob *dst
                              bool prefix, hipStream_t s);
 hipError_t launch_mask_bytes(const uint32_t *const *masks_dev, int32_t Q, int32_t Qp, int32_t N,
                              int32_t S, uint8_t *ph, int32_t *n1, bool fp4, hipStream_t s);
-hipError_t launch_case_pairs(const uint32_t *planes, int32_t Mp, int32_t W,
-                             const uint32_t *const *masks_dev, int32_t Q, int32_t Qp, int32_t *out,
-                             hipStream_t s);
+// half: only phenotypes 0 .. 31 of the Qp = 64 are read (Q <= 32).
+hipError_t launch_case_pairs(const uint32_t *planes, int32_t M, int32_t Mp, int32_t W,
+                             const uint32_t *const *masks_dev, int32_t Q, int32_t Qp, bool half,
+                             int32_t *out, hipStream_t s);
 // Pair scan: FP32 K2 of every pair of a SPLIT data set from its pairwise
 // tables, by lexicographic pair rank; key range into keyrange[0..1].
 hipError_t launch_pair_scores(const epi3_dataset &d, float *score, uint32_t *keyrange, hipStream_t s);
