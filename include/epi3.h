@@ -343,8 +343,7 @@ int epi3_pairs_score_plane(const epi3_dataset *d, int32_t k, int64_t cand_cap, v
  * (0/1 FP4 products, exact FP32 accumulation) when the data set has value
  * planes and classes of at most 65535 samples, else by AND + POPCNT over the
  * bit planes (a data set encoded with EPI3_ENCODE_BITS_ONLY); the corner
- * cells of the four sub-triplets are counted by AND + POPCNT once per
- * triplet, and every other cell follows by inclusion-exclusion from those,
+ * cells of the four sub-triplets are counted once per triplet, and every other cell follows by inclusion-exclusion from those,
  * the pairwise tables of epi3_encode and the class size.  Both count paths
  * give the same FP32 scores.  Hits are the k lowest under
  * (K2, i, j, k, l) with the same FP32 screen and FP64 re-score as the other

@@ -245,11 +245,6 @@ __global__ void __launch_bounds__(256, QT == 1 ? 3 : 2) case_pairs_kernel(const 
       }
 }
 
-__device__ __forceinline__ void load_pair(const int32_t *p, int64_t idx, int v[4]) {
-  const int4 x = reinterpret_cast<const int4 *>(p)[idx];
-  v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-}
-
 // Staging geometry: samples are processed in chunks of kKC staged in LDS,
 // each row padded to an odd number of 16-byte units against bank conflicts.
 constexpr int kKC = 128;

@@ -455,12 +455,6 @@ __global__ void __launch_bounds__(256) collect_kernel(const SelJob *__restrict__
 }
 
 // ----------------------------------------------------- FP64 re-score ----
-__device__ __forceinline__ unsigned wave_sum(unsigned v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
 // Sums of sixteen values over the lanes of a wave, in every lane.  Exchange
 // steps halve the values per lane (8 + 4 + 2 + 1 swaps), two more add up the
 // rest: 17 lane exchanges instead of six per value.
