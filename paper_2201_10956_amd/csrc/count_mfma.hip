@@ -586,7 +586,7 @@ __device__ __forceinline__ void fused_score(const PermJob &pj, v16f (&acc)[kPerm
 // the corner scratch), with the log-factorial table at LDS address 0;
 // nothing goes to the scratch.  FUSE = 0: corner cells out, finish_perm_kernel
 // after.  The kernels below give the LDS arrays.
-template <bool FP4, int FUSE, int QT>
+template <bool FP4, int FUSE, int QT, bool FEW>
 __device__ __forceinline__ void count_perm_body(
     const PermJob *__restrict__ pjp, int64_t tile_begin, int64_t n_tiles, int64_t stride,
     unsigned long long *__restrict__ queue, SelState *__restrict__ st,
@@ -598,7 +598,8 @@ __device__ __forceinline__ void count_perm_body(
   typedef PermAcc<FP4> Acc;
   const PermJob pj = *pjp;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63;
+  const bool wave0 = __builtin_amdgcn_readfirstlane(tid >> 6) == 0;
   if constexpr (FUSE != 0) {
     table_to_lds<256>(sLf, lfx, lf_len);
     if (tid < 64) {
@@ -620,12 +621,22 @@ __device__ __forceinline__ void count_perm_body(
   // b mod 8), each with its own counter in queue[0..7]; a workgroup takes the
   // next slot of its XCD's part, and once that part is done those of the
   // other parts in turn.  Consecutive slots share operand rows, which then
-  // stay in one XCD's L2.  Every workgroup ends after at most 8 empty draws.
+  // stay in one XCD's L2.  Every workgroup ends after at most 8 empty draws,
+  // one after the other; FEW: they are looked at together and the first slot
+  // is fixed (TileSlots).
   int xq = 0;
   const int xcd = blockIdx.x & 7;
-  for (;;) {
+  TileSlots<unsigned long long> slots{queue, n_tiles, 0, xcd};
+  for (bool begun = false;; begun = true) {
     __syncthreads();  // previous tile's readers of sTile / stage are done
-    if (tid == 0) {
+    if constexpr (FEW) {
+      if (wave0) {
+        if (begun)
+          slots.find(tid == 0 ? slots.draw() : 0ull, sTile);
+        else
+          slots.first(sTile);
+      }
+    } else if (tid == 0) {
       int64_t sl = -1;
       while (xq < 8) {
         const int y = (xcd + xq) & 7;
@@ -952,7 +963,7 @@ __global__ void __launch_bounds__(256, 2) count_mfma_perm_kernel(
   // second half, added by the waves of the first half
   __shared__ float sTot[2][64][4];
   const PermOut none{};
-  count_perm_body<FP4, 0, 2>(pjp, tile_begin, n_tiles, stride, queue, nullptr, nullptr, 0, 1.f, none,
+  count_perm_body<FP4, 0, 2, false>(pjp, tile_begin, n_tiles, stride, queue, nullptr, nullptr, 0, 1.f, none,
                           stage,
                           sTile, sTot, nullptr, nullptr, nullptr);
 }
@@ -960,7 +971,7 @@ __global__ void __launch_bounds__(256, 2) count_mfma_perm_kernel(
 // Dynamic LDS only, so the log-factorial table starts at LDS address 0 and a
 // lookup is one ds_read at the byte offset: [table][staging][tile slot]
 // [totals exchange][the tile's all-sample cells][key ranges].
-template <int FUSE, int QT>
+template <int FUSE, int QT, bool FEW>
 __global__ void __launch_bounds__(256, QT == 1 ? 3 : 2) count_score_perm_kernel(
     const PermJob *__restrict__ pjp, int64_t tile_begin, int64_t n_tiles, int64_t stride,
     unsigned long long *__restrict__ queue, SelState *__restrict__ st,
@@ -971,7 +982,7 @@ __global__ void __launch_bounds__(256, QT == 1 ? 3 : 2) count_score_perm_kernel(
   float(*sTot)[64][4] = reinterpret_cast<float(*)[64][4]>(sTile + 2);
   uint4(*sT16)[kPermKB] = reinterpret_cast<uint4(*)[kPermKB]>(sTot + 2);
   uint32_t(*sRange)[2] = reinterpret_cast<uint32_t(*)[2]>(sT16 + 4);
-  count_perm_body<true, FUSE, QT>(pjp, tile_begin, n_tiles, stride, queue, st, lfx, lf_len, scale, out, stage,
+  count_perm_body<true, FUSE, QT, FEW>(pjp, tile_begin, n_tiles, stride, queue, st, lfx, lf_len, scale, out, stage,
                               sTile, sTot, sT16, sRange, reinterpret_cast<uint32_t *>(lds));
 }
 
@@ -1265,7 +1276,13 @@ static hipError_t launch_count_t(const PermJob *pj_dev, int64_t tile_begin, int6
     hipLaunchKernelGGL(count_mfma_perm_kernel<FP4>, dim3((unsigned)blocks), dim3(256), 0, s, pj_dev,
                        tile_begin, n_tiles, stride, queue);
   } else {
-    auto kern = count_score_perm_kernel<FUSE, QT>;
+    // Up to 512 tiles per CU the tiles are handed out with a fixed first slot and
+    // one look at the counters at the end (whole batch: 64 x 800 x 8 169 -> 139
+    // us, 100 x 1500 x 40 379 -> 367, 203 x 1501 x 20, 100 tiles per CU, 738 ->
+    // 720; 512 x 4096 x 64, 1400 per CU, 21.1 ms both; 1024 x 8192 x 64, 11000 per
+    // CU, 259.2 -> 260.1 ms, for the registers that it takes).
+    auto kern = n_tiles <= 512ll * n_cu ? count_score_perm_kernel<FUSE, QT, true>
+                                        : count_score_perm_kernel<FUSE, QT, false>;
     const size_t lds = (size_t)perm_score_lds_bytes(lf_len);
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -581,55 +581,11 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
   const int o_b0 = (kRowsI + kRowsJ + 32 * wb + r) * kPRow + 16 * g;
   const int o_b1 = o_b0 + KT * kPRow + kPlanePad;
 
-  // Slots are cut into 8 contiguous parts, one per XCD (workgroup b runs on
-  // XCD b mod 8), each with a counter in queue[0..7]: consecutive tiles share
-  // operand rows, which then stay in one XCD's L2.  Workgroup b starts with
-  // slot b / 8 of its XCD's part; the counter hands out those after the ones
-  // started with.  (A workgroup draws its next tile while it counts, so with
-  // every slot drawn, and no more tiles than workgroups, those launched first
-  // took two tiles each and the last ones none: whole scan 135 -> 121 us at
-  // 157 x 2311, 238 -> 227 at 300 x 3000.  Drawn between the classes and not
-  // ahead of the tile, the next tile goes to a workgroup that gets to it sooner:
-  // 590 -> 584 us at 512 x 4096, 4.28 -> 4.25 ms at 1003 x 6007.)  Once a part
-  // is used up, the others follow in turn.
-  int part = 0;  // the part being drawn from, counted from the own one
-  const int xcd = blockIdx.x & 7;
-  auto draw = [&]() {  // a part holds fewer than 2^32 tiles
-    return atomicAdd(reinterpret_cast<unsigned *>(queue + ((xcd + part) & 7)), 1u);
-  };
-  // Wave 0: the slot of count c of the current part (lane 0's) to sTile, or the
-  // next one of another part, or n_tiles.  Lane d stands for the d-th part from
-  // the own one, so the counters are looked at together: drawing from part
-  // after part costs a round trip to memory each, seven at the end of a scan.
-  // (Lanes, not scalars: eight parts' limits in scalar registers spilled 90 of
-  // them, 2% of the scan at 512 x 4096.)
-  auto find_slot = [&](unsigned c) {
-    int d = lane;
-    asm volatile("" : "+v"(d));
-    const int y = (xcd + d) & 7, rem = (int)(n_tiles & 7);
-    const int64_t lo = n_tiles / 8 * y + (y < rem ? y : rem), size = n_tiles / 8 + (y < rem ? 1 : 0);
-    const int64_t started = (gridDim.x + 7 - y) / 8;  // may be more than the part has
-    c = (unsigned)rfl((int)c);
-    for (;;) {
-      const bool mine = d == part && started + c < size;
-      if (mine) sTile[0] = lo + started + c;
-      if (__ballot(mine) != 0ull) return;
-      unsigned n = 0u;
-      if (d < 8)
-        n = __hip_atomic_load(reinterpret_cast<unsigned *>(queue + y), __ATOMIC_RELAXED,
-                              __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned long long m = __ballot(d < 8 && d > part && started + n < size);
-      if (m == 0ull) {
-        part = 7;
-        if (d == 0) sTile[0] = n_tiles;
-        return;
-      }
-      part = __builtin_ctzll(m);
-      n = 0u;
-      if (d == part) n = draw();
-      c = (unsigned)__builtin_amdgcn_readlane((int)n, part);
-    }
-  };
+  // Consecutive tiles share operand rows: an XCD's slots are contiguous.  The
+  // next tile is drawn between the classes and not ahead of the tile, so that it
+  // goes to a workgroup that gets to it sooner: 590 -> 584 us at 512 x 4096,
+  // 4.28 -> 4.25 ms at 1003 x 6007.
+  TileSlots<unsigned> slots{queue, n_tiles, 0, (int)(blockIdx.x & 7)};
   // (i0, j0, k0) of tile t of the current job
   int i0 = 0, j0 = 0, k0 = 0;
   auto place = [&](int64_t t) {
@@ -685,14 +641,7 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
       }
   };
 
-  if (wave == 0) {
-    const int64_t in_part = n_tiles / 8 + (xcd < (int)(n_tiles & 7) ? 1 : 0);
-    const int64_t lo = n_tiles / 8 * xcd + (xcd < (int)(n_tiles & 7) ? xcd : (int)(n_tiles & 7));
-    if ((int64_t)(blockIdx.x >> 3) < in_part)
-      sTile[0] = lo + (blockIdx.x >> 3);
-    else
-      find_slot(0xffffffffu);
-  }
+  if (wave == 0) slots.first(sTile);
   __syncthreads();
   int64_t slot = rfl64q(sTile[0]);
   bool loaded = false;  // the current tile's origin is set and its first chunk is in pf
@@ -789,7 +738,7 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
       const bool more = ch + 1 < nch;
       if (ch == nch0) {
         keep();
-        if (tid == 0) drawn = draw();
+        if (tid == 0) drawn = slots.draw();
       }
       if (more) fetch(ch + 1);
       const uint8_t *buf = stage + (ch & 1) * kBuf;
@@ -819,9 +768,9 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
 #undef EPI3_PSTEP
     if (nch == nch0) {
       keep();
-      if (tid == 0) drawn = draw();
+      if (tid == 0) drawn = slots.draw();
     }
-    if (wave == 0) find_slot(drawn);
+    if (wave == 0) slots.find(drawn, sTile);
     __syncthreads();  // the staging buffers are idle from here to the next tile
     // a scoring wave issues ahead of the other workgroup's counting waves: its
     // lookups keep the LDS busy, and the products still fit between

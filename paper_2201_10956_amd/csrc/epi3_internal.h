@@ -538,6 +538,82 @@ __device__ __forceinline__ void decode_quad_rank(int64_t M, int64_t rank, int &i
   l = (int)(r2 - (c2(M - 1 - j) - c2(M - k))) + k + 1;
 }
 
+// ---- tile slots of a persistent launch ----
+// Slots are cut into 8 contiguous parts, one per XCD (workgroup b runs on XCD
+// b mod 8), each with a cleared counter in queue[0..7].
+// Workgroup b starts with slot b / 8 of its XCD's part; the counter hands out
+// those after the ones started with.  (A workgroup may draw its next tile while
+// it works on one: with every slot drawn, and no more tiles than workgroups,
+// those launched first took two tiles each and the last ones none: whole scan
+// 135 -> 121 us at 157 x 2311, 238 -> 227 at 300 x 3000.)  Once a part is used
+// up, the others follow in turn.
+// Count: of 32 bits (the low word of each counter) where no part can hold 2^32
+// tiles, else of 64.
+template <typename Count>
+struct TileSlots {
+  unsigned long long *queue;
+  int64_t n_tiles;
+  int part;  // the part being drawn from, counted from the own one
+  int xcd;
+  __device__ __forceinline__ Count *counter(int y) const { return reinterpret_cast<Count *>(queue + y); }
+  __device__ __forceinline__ Count draw() const { return atomicAdd(counter((xcd + part) & 7), (Count)1); }
+  // lane's value of c in every lane
+  static __device__ __forceinline__ Count from_lane(Count c, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)c, lane);
+    if constexpr (sizeof(Count) == 4) return lo;
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)c >> 32), lane);
+    return (Count)((uint64_t)hi << 32 | lo);
+  }
+  // First slot that the counter of part y hands out, and their number.
+  __device__ __forceinline__ void handed_out(int y, int64_t &begin, Count &size) const {
+    const int rem = (int)(n_tiles & 7);
+    const int64_t started = (gridDim.x + 7 - y) / 8;
+    const int64_t n = n_tiles / 8 + (y < rem ? 1 : 0) - started;  // negative: fewer slots than workgroups
+    begin = n_tiles / 8 * y + (y < rem ? y : rem) + started;
+    size = n > 0 ? (Count)n : 0;
+  }
+  // One whole wave: the slot of count c of the current part (lane 0's c) to
+  // *slot, or the next one of another part, or n_tiles.  Lane d stands for the
+  // d-th part from the own one, so the counters are looked at together: drawing
+  // from part after part costs a round trip to memory each, seven at the end of
+  // a scan.  (Lanes, not scalars: eight parts' limits in scalar registers
+  // spilled 90 of them, 2% of the scan at 512 x 4096.)
+  __device__ __forceinline__ void find(Count c, int64_t *slot) {
+    int d = threadIdx.x & 63;
+    asm volatile("" : "+v"(d));
+    const int y = (xcd + d) & 7;
+    int64_t begin;
+    Count size;
+    handed_out(y, begin, size);
+    c = from_lane(c, 0);
+    for (;;) {
+      const bool mine = d == part && c < size;
+      if (mine) *slot = begin + (int64_t)c;
+      if (__ballot(mine) != 0ull) return;
+      Count n = 0;
+      if (d < 8) n = __hip_atomic_load(counter(y), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned long long m = __ballot(d < 8 && d > part && n < size);
+      if (m == 0ull) {
+        part = 7;
+        if (d == 0) *slot = n_tiles;
+        return;
+      }
+      part = __builtin_ctzll(m);
+      if (d == part) n = draw();
+      c = from_lane(n, part);
+    }
+  }
+  // One whole wave: the workgroup's first slot.
+  __device__ __forceinline__ void first(int64_t *slot) {
+    const int rem = (int)(n_tiles & 7);
+    const int64_t size = n_tiles / 8 + (xcd < rem ? 1 : 0), lo = n_tiles / 8 * xcd + (xcd < rem ? xcd : rem);
+    if ((int64_t)(blockIdx.x >> 3) < size)
+      *slot = lo + (blockIdx.x >> 3);
+    else
+      find(~(Count)0, slot);
+  }
+};
+
 // ---- fixed-point scoring ----
 // K2 is summed in 32-bit fixed point: the table holds round(2^s L[n]) modulo
 // 2^32, and the 3 entries of each row are added and subtracted modulo 2^32.

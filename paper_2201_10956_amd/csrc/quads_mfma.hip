@@ -600,9 +600,10 @@ __global__ void __launch_bounds__(256, 2) count_score_quad_kernel(
   uint32_t kmin = 0xffffffffu, kmax = 0u;
   int j = -1;
   int64_t jlo = 0, jhi = 0;
-  if (threadIdx.x == 0) sTile[0] = (int64_t)atomicAdd(queue, 1ull);
-  __syncthreads();
-  int64_t slot = rfl64x(sTile[0]);
+  // Workgroup b starts with tile b; the queue hands out those after them.  (The
+  // next tile is drawn while one is counted: with every tile drawn, and few
+  // tiles per workgroup, those launched first took two and the last ones none.)
+  int64_t slot = blockIdx.x;
   while (slot < n_tiles) {
     __builtin_amdgcn_s_setprio(0);
     // lane roles formed per tile (see the phenotype count kernel)
@@ -759,7 +760,7 @@ __global__ void __launch_bounds__(256, 2) count_score_quad_kernel(
     __syncthreads();  // the staging buffers are idle from here to the next tile
     __builtin_amdgcn_s_setprio(1);  // scoring goes ahead of the other workgroup's counting
     tabs.fill(sh, ib, j, kb, lb);
-    if (tid == 0) sTile[0] = (int64_t)drawn;
+    if (tid == 0) sTile[0] = (int64_t)(drawn + gridDim.x);
     __syncthreads();
     if (i < j) {  // wave-uniform
       int ln = threadIdx.x & 63;

@@ -1,13 +1,14 @@
-"""Tiles handed out by the one-kernel plain scan: each workgroup starts with a
+"""Tiles handed out by the persistent matrix-core kernels: each workgroup starts with a
 slot of its own and counters hand out the rest, so every slot is counted once
 whatever the number of tiles is beside the workgroups (two per compute unit):
 fewer than the eight parts, a remainder over the parts, about one, two and three
 tiles per workgroup.  A missed slot leaves the score plane's fill."""
+import numpy as np
 import pytest
 import torch
 
 from paper_2201_10956_amd import epi3
-from synth import make_dataset
+from synth import make_dataset, make_permutations
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +50,25 @@ def test_jobs_of_one_launch():
     got = epi3.BatchScanner(sets, 5, variant="mfma_fp4").run()
     for ds, h in zip(sets, got):
         assert h.tobytes() == epi3.scan_topk(ds, 5, variant="valu").tobytes()
+
+
+@pytest.mark.parametrize("Q", [3, 33])
+@pytest.mark.parametrize("M", [4, 12, 20, 37, 64, 75])
+def test_phenotype_batches(M, Q):
+    """Tiles of 64 triplets: from one to beyond three per compute unit."""
+    d = make_dataset(M, 131, 0.4, 0.05, M)
+    perms = make_permutations(d.pheno, Q, 5)
+    g = torch.from_numpy(d.geno).cuda()
+    masks = torch.from_numpy(epi3.pack_masks(perms).view(np.int32)).cuda()
+    got = epi3.BatchScanner(epi3.encode(g, d.pheno, layout="masked"), 5, masks=masks).run()
+    for q in (0, Q // 2, Q - 1):
+        want = epi3.scan_topk(epi3.encode(g, perms[q]), 5, variant="valu")
+        assert got[q].tobytes() == want.tobytes()
+
+
+@pytest.mark.parametrize("M", [4, 9, 21, 34, 50])
+def test_quads(M):
+    d = make_dataset(M, 97, 0.4, 0.05, M)
+    g = torch.from_numpy(d.geno).cuda()
+    want = epi3.scan_quads(epi3.encode(g, d.pheno, values=False), 20)  # counted on the vector ALUs
+    assert epi3.scan_quads(epi3.encode(g, d.pheno), 20).tobytes() == want.tobytes()
