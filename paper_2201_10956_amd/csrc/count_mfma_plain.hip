@@ -520,7 +520,7 @@ constexpr int32_t plain_fused_entries() {
 // tile's slot is drawn while this one is counted and its first chunk loaded
 // while this one is scored.
 //
-// Two waves per SIMD (227-231 registers), one of each workgroup, so one can
+// Two waves per SIMD (229-235 registers), one of each workgroup, so one can
 // count while the other scores.  A lone wave issues one vector instruction
 // per 8 cycles and one lookup per 12 (measured with independent chains; two
 // waves on a SIMD share 2.7 cycles per vector instruction), so with one

@@ -602,7 +602,8 @@ __global__ void __launch_bounds__(256, 2) count_score_quad_kernel(
   int64_t jlo = 0, jhi = 0;
   // Workgroup b starts with tile b; the queue hands out those after them.  (The
   // next tile is drawn while one is counted: with every tile drawn, and few
-  // tiles per workgroup, those launched first took two and the last ones none.)
+  // tiles per workgroup, those launched first took two and the last ones none:
+  // 48 SNPs x 1000 samples 208 -> 197 us per scan, 256 x 4096 unchanged.)
   int64_t slot = blockIdx.x;
   while (slot < n_tiles) {
     __builtin_amdgcn_s_setprio(0);
