@@ -479,9 +479,12 @@ __device__ __forceinline__ void add_up(const Lookups &l, uint32_t &up, uint32_t 
 // Correction of a sum whose table in LDS ends after `lim` entries (it is
 // complete at `lfx`).  An entry past those is needed only by a row of more
 // than half of the samples, so by one row at most: `top`, the row with the
-// largest count.  Its three lookups are replaced (what the LDS held at those
-// addresses is subtracted again; nothing writes LDS meanwhile, and the
-// addresses stay inside the workgroup's block).
+// largest count.  Its three lookups are replaced: what the LDS held at those
+// addresses is subtracted again, so those words must not change between the
+// two readings.  They lie in the staging buffers before their last
+// kPairBytes (fused_ok_t), and from the barrier that ends the counts to the
+// one that ends the scoring only the pair entries are written there, by each
+// wave in its own time: they take the last kPairBytes.
 __device__ __forceinline__ uint32_t fix_top(uint32_t sum, uint32_t top, const uint32_t *lfx,
                                             uint32_t lim) {
   const uint32_t r = top >> 16, r0 = top & 0xffffu;
@@ -506,6 +509,23 @@ template <int JB>
 constexpr int32_t plain_fused_entries() {
   return ((kLdsTableBytes - plain_stage_bytes<JB>() - 16) / 16) * 4;
 }
+// The four waves' pair entries while they score, at the end of the staging
+// buffers: a cut table's lookups run past the table into those (fix_top).
+constexpr int kPairBytes = 4 * 64 * 16;
+// Longest table: the first entries in LDS, with a cover of 7/10 of it.
+template <int JB>
+constexpr int32_t plain_fused_longest() {
+  return plain_fused_entries<JB>() * 10 / 7;
+}
+// Whether the lookups of a table of lf_len entries, cut to those that fit,
+// end before the pair entries.
+template <int JB>
+constexpr bool plain_lookups_ok(int32_t lf_len) {
+  return (int64_t)lf_len * 4 <=
+         (int64_t)plain_fused_entries<JB>() * 4 + plain_stage_bytes<JB>() - kPairBytes;
+}
+static_assert(plain_lookups_ok<8>(plain_fused_longest<8>()) && plain_lookups_ok<4>(plain_fused_longest<4>()),
+              "no lookup reaches words that a wave writes while another scores");
 
 // Counts and scores the tiles in one kernel (FP4).  Both classes' samples are
 // one sequence of chunks.  The accumulators start at 2^23, so an FP32 sum's
@@ -516,7 +536,7 @@ constexpr int32_t plain_fused_entries() {
 // corner cells of its 16 triplets: half (g) of the 16 i, 2 j, one k.  Tables
 // are completed for both classes at once, two 16-bit counts per register, from
 // the pair table (j, k) completed once per j, (i, k) loaded once per i, and
-// (i, j) of the wave's 32 pairs kept in the idle staging buffer.  The next
+// (i, j) of the wave's 32 pairs kept at the end of the idle staging buffers.  The next
 // tile's slot is drawn while this one is counted and its first chunk loaded
 // while this one is scored.
 //
@@ -550,7 +570,7 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
   constexpr int NBP = KT / 32;  // 32-wide k blocks; the 4 waves are (JB / 2) x NBP
   constexpr int kSteps = kPKC / 32;
   static_assert((JB / 2) * NBP == 4, "four waves per tile");
-  static_assert(2 * kBuf == plain_stage_bytes<JB>(), "LDS layout");
+  static_assert(2 * kBuf == plain_stage_bytes<JB>() && 2 * kBuf % 16 == 0, "LDS layout");
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   uint8_t *stage = reinterpret_cast<uint8_t *>(lds + tab_cap);
   int64_t *sTile = reinterpret_cast<int64_t *>(stage + 2 * kBuf);
@@ -834,8 +854,8 @@ __global__ void __launch_bounds__(256, 2) count_score_plain_kernel(
     uint4 q_n[2] = {stash[ln], (stash + 64)[ln]};
     // lane = pair (si0 + lane / 2, jb + lane % 2): its four counted cells, the
     // two (a, 2) cells and its lexicographic base, 32 bytes each, in this
-    // wave's part of the buffer
-    uint4 *pij_s = reinterpret_cast<uint4 *>(stage) + wave * 64;
+    // wave's part of the buffers' end
+    uint4 *pij_s = reinterpret_cast<uint4 *>(stage + 2 * kBuf - kPairBytes) + wave * 64;
     if (ln < 32) {
       u16x2 p[4], m[4];
       const int i = si0 + (ln >> 1);
@@ -1194,12 +1214,10 @@ static hipError_t launch_fused_t(const PlainJob *jobs, const int64_t *job_begin,
 // entries there: at most one row of a triplet's table can need another as
 // long as those cover half of the samples, and the cover of 7/10 taken here
 // makes such rows rare.  16-bit counts.  The lookups that a longer table
-// would need stay inside the workgroup's LDS block.
+// would need end before the words that the waves write while scoring.
 template <int JB>
 static bool fused_ok_t(int32_t lf_len) {
-  const int32_t cap = plain_fused_entries<JB>();
-  return lf_len - 2 <= 65535 && (int64_t)lf_len * 7 <= (int64_t)cap * 10 &&
-         (int64_t)lf_len * 4 <= (int64_t)cap * 4 + plain_stage_bytes<JB>();
+  return lf_len - 2 <= 65535 && lf_len <= plain_fused_longest<JB>() && plain_lookups_ok<JB>(lf_len);
 }
 
 bool plain_fused_ok(int JB, int32_t lf_len) {
