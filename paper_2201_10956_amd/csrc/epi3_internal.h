@@ -647,9 +647,15 @@ inline const uint32_t *fx_table(const epi3_dataset &d) {
 // Sum of the table's rows -> FP32 score.
 __device__ __forceinline__ float fx_score(uint32_t sum, float scale) { return (float)sum * scale; }
 
-// Table entry at byte offset b (b = 4 n for L[n]).
+// Table entry at byte offset b >= 0 (b = 4 n for L[n]) of a table in global memory.
+// The pointer is cast to that address space: jobs' tables come from records, and
+// a lookup through a generic pointer is a flat load with a 64-bit address of its
+// own, 81 of them per triplet (vector-ALU scans of 512 x 21000: one wave per SIMD
+// at 355 registers 17.4 ms, two at 225 so 9.45 ms).
 __device__ __forceinline__ uint32_t fx_at(const uint32_t *L, int b) {
-  return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(L) + b);
+  typedef const __attribute__((address_space(1))) char *gbytes;
+  typedef const __attribute__((address_space(1))) uint32_t *gwords;
+  return *(gwords)((gbytes)L + (uint32_t)b);
 }
 // The same for a table at LDS address 0 (the start of the dynamic LDS block
 // of a kernel that declares no static LDS): the byte offset is the address,
@@ -687,6 +693,9 @@ __device__ __forceinline__ uint32_t fx_sum(const int *t0, const int *t1, const u
     } else {
       up += fx_at(L, b0 + b1 + 4);
       down += fx_at(L, b0) + fx_at(L, b1);
+      // (quads: the lookups stay near their additions, 202 registers instead of 252:
+      // 64 x 140000 9.45 -> 9.29 ms; 27 rows are faster without, 512 x 21000 9.88 / 9.45)
+      if (R > 27) asm volatile("" : "+v"(up), "+v"(down));
     }
   }
   return up - down;
