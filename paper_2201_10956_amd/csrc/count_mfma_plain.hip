@@ -1023,6 +1023,11 @@ __global__ void __launch_bounds__(256) finish_plain_kernel(const PlainJob *__res
   const float ub = MODE == kPermOutBounded ? out.st->ub : 0.f;
   const int kl = threadIdx.x % KT, jl = threadIdx.x / KT;
   for (int64_t slot = blockIdx.x; slot < n_tiles; slot += gridDim.x) {
+    // Tables out: the waves stay together.  Each writes 216-byte tables a few bytes
+    // at a time, and where they drift apart by a tile the parts of neighbouring
+    // tables no longer meet in L2 (512 x 4096, whole call: 2.88 ms with this barrier;
+    // without it 3.10 to 3.31 ms with one to three workgroups per CU).
+    if (COUNTS) __syncthreads();
     const int64_t tg = tile_begin + slot * out.stride;
     if (jd.find(job_begin, n_jobs, tg)) {
       if (keyrange) flush_range(kmin, kmax, keyrange);
