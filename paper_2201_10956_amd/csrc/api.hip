@@ -269,6 +269,19 @@ int plain_variant(const epi3_dataset &d, int32_t variant) {
   return variant;
 }
 
+// The same for a scan that writes its tables: there the matrix cores count and
+// complete in two kernels, so AUTO leaves small data sets to the vector ALUs, on
+// which the one-kernel scan beats them (whole calls, matrix cores / vector ALUs:
+// 64 x 2048 155 / 79 us, 100 x 1000 160 / 109, 255 x 300 505 / 432, 512 x 1000 2.68
+// / 2.15 ms; from the other side 200 x 4000 265 / 361 us, 128 x 12000 205 / 338, 255
+// x 16000 656 / 1626, 512 x 4096 2.88 / 4.45 ms).
+int tables_variant(const epi3_dataset &d, int32_t variant) {
+  const int v = plain_variant(d, variant);
+  const bool large = d.n_samples >= 16384 || (d.n_snps >= 128 && d.n_samples >= 4000) ||
+                     (d.n_snps >= 256 && d.n_samples >= 1024);
+  return variant == EPI3_VARIANT_AUTO && v > EPI3_VARIANT_AUTO && !large ? (int)EPI3_VARIANT_VALU : v;
+}
+
 int pick_JB(const epi3_dataset &d, int32_t v) { return rule_tile(v, d.n_snps, d.n_samples, 4); }
 
 ScanLayout scan_layout(void *ws, const epi3_dataset &d, int32_t k, int64_t cand_cap,
@@ -1340,7 +1353,7 @@ int epi3_scan_tables(const epi3_dataset *d, int32_t variant, uint32_t *counts_de
                      void *ws_dev, int64_t ws_bytes, void *stream) {
   if (!valid_dataset(d) || !k2_dev || !ws_dev) return EPI3_E_INVALID;
   if (d->layout != EPI3_LAYOUT_SPLIT) return EPI3_E_INVALID;
-  const int v = plain_variant(*d, variant);
+  const int v = counts_dev ? tables_variant(*d, variant) : plain_variant(*d, variant);
   if (v < 0) return v;
   ScanLayout W = scan_layout(ws_dev, *d, 1, 0, variant);
   if (ws_bytes < W.total) return EPI3_E_WORKSPACE;
@@ -1349,7 +1362,7 @@ int epi3_scan_tables(const epi3_dataset *d, int32_t variant, uint32_t *counts_de
   if (T == 0) return EPI3_OK;
   HIP_OK(launch_fill_u32(&W.st->kmin, 0xffffffffu, 1, s));
   HIP_OK(launch_fill_u32(&W.st->kmax, 0u, 1, s));
-  return enqueue_count(*d, variant, k2_dev, counts_dev ? counts_dev : nullptr, W, s);
+  return enqueue_count(*d, v, k2_dev, counts_dev ? counts_dev : nullptr, W, s);
 }
 
 int64_t epi3_pairs_workspace_bytes(const epi3_dataset *d, int32_t k, int64_t cand_cap) {
