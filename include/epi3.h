@@ -412,14 +412,16 @@ double epi3_k2_error_bound(int32_t n_samples);
 int64_t epi3_n_triplets(int32_t n_snps);
 
 /* Optional set-up on the current device: creates the library's second
- * stream and events of the matrix-core paths and the stream batched scans
- * are captured on, and looks up the device address of the static workspace
- * of epi3_scan_topk_static, which the first call that needs them would
- * otherwise do.  Returns EPI3_E_HIP if the runtime refuses. */
+ * stream and events of the matrix-core paths, the stream batched scans are
+ * captured on and a block of pinned host memory, and looks up the device
+ * address of the static workspace of epi3_scan_topk_static, which the first
+ * call that needs them would otherwise do.  Returns EPI3_E_HIP if the runtime refuses. */
 int epi3_init(void);
 
-/* Release cached graphs and the library's idle streams and events.  Must not
- * run while another call of the library is in progress. */
+/* Release cached graphs, the library's idle streams and events and its idle
+ * pinned host memory (at most 8 blocks of 1 MB, and 8 that calls with an error
+ * left behind, for which it waits for their devices).  Must not run while
+ * another call of the library is in progress. */
 void epi3_release(void);
 
 /* Kernel timing for measurement: while enabled, the library records a HIP

@@ -562,16 +562,26 @@ struct AuxLease {
 // transfers of a call then cost one kernel instead of a staged copy each (a
 // pageable copy takes 8-15 us of host time whatever its size).  A call holds a
 // block of its own until its stream has finished with it.  At most kStagingIdle
-// blocks stay idle; epi3_release gives them back.  A block whose stream did not
-// finish (an error) is never used again.  Where nothing may be allocated
+// blocks stay idle; epi3_release gives them back.  A block whose stream could not
+// be waited for (an error) is not used again; once kStagingLost are lost that way,
+// calls use plain copies until epi3_release has waited for the devices and given
+// them back.  Where nothing may be allocated
 // (epi3_topk, which epi3_scan_topk_static ends in), only an idle block is taken:
 // every encode leaves one, and epi3_init.
 constexpr int64_t kStagingBytes = 1 << 20;
-constexpr size_t kStagingIdle = 8;
+constexpr size_t kStagingIdle = 8, kStagingLost = 8;
 struct StagingPool {
+  struct Lost {
+    uint8_t *host;
+    int dev;  // whose stream used it
+  };
   std::mutex mu;
   std::vector<uint8_t *> idle;
-  StagingPool() { idle.reserve(kStagingIdle); }
+  std::vector<Lost> lost;
+  StagingPool() {
+    idle.reserve(kStagingIdle);
+    lost.reserve(kStagingLost);
+  }
 };
 StagingPool &staging_pool() {
   static StagingPool p;
@@ -586,6 +596,7 @@ class StagingLease {
     {
       StagingPool &p = staging_pool();
       std::lock_guard<std::mutex> g(p.mu);
+      if (p.lost.size() >= kStagingLost) return;
       if (!p.idle.empty()) {
         host = p.idle.back();
         p.idle.pop_back();
@@ -606,10 +617,16 @@ class StagingLease {
     dev = static_cast<uint8_t *>(d);
   }
   ~StagingLease() {
-    if (!host || busy) return;
+    if (!host) return;
     StagingPool &p = staging_pool();
     {
       std::lock_guard<std::mutex> g(p.mu);
+      if (busy) {
+        // (calls that were under way at the limit: not given back at all)
+        int dev = -1;
+        if (p.lost.size() < kStagingLost && hipGetDevice(&dev) == hipSuccess) p.lost.push_back({host, dev});
+        return;
+      }
       if (p.idle.size() < kStagingIdle) {
         p.idle.push_back(host);
         return;
@@ -2054,6 +2071,16 @@ void epi3_release(void) {
     std::lock_guard<std::mutex> lk(p.mu);
     for (uint8_t *m : p.idle) (void)hipHostFree(m);
     p.idle.clear();
+    int dev = -1;
+    if (!p.lost.empty() && hipGetDevice(&dev) == hipSuccess) {
+      std::vector<StagingPool::Lost> kept;
+      for (const StagingPool::Lost &l : p.lost) {
+        if (hipSetDevice(l.dev) == hipSuccess && hipDeviceSynchronize() == hipSuccess) (void)hipHostFree(l.host);
+        else kept.push_back(l);
+      }
+      p.lost.assign(kept.begin(), kept.end());
+      (void)hipSetDevice(dev);
+    }
   }
   GraphCache &G = graphs();
   std::lock_guard<std::mutex> lk(G.mu);
