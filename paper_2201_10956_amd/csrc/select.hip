@@ -826,10 +826,13 @@ __global__ void __launch_bounds__(256) sort_init_kernel(const SelJob *__restrict
 
 // One compare-exchange stage (block size k, distance j >= kSortLocal) over
 // global memory: thread t handles the pair (lo, lo + j).
+// The launches follow the job with the most entries (a batch's jobs differ where
+// their triplets are fewer than the capacity): a job is sorted after the stages of
+// k = sortP, and later ones would reach past its entries.
 __global__ void __launch_bounds__(256) sort_global_kernel(const SelJob *__restrict__ sj, int64_t k,
                                                           int64_t j) {
   const SelJob &J = sj[blockIdx.y];
-  if (J.sortP == 0 || J.st->done != 1u) return;
+  if (k > J.sortP || J.st->done != 1u) return;
   for (int64_t t = blockIdx.x * 256 + threadIdx.x; t < J.sortP / 2; t += (int64_t)gridDim.x * 256) {
     const int64_t lo = ((t & ~(j - 1)) << 1) | (t & (j - 1)), hi = lo + j;
     const bool asc = (lo & k) == 0;
@@ -848,7 +851,7 @@ constexpr int kSortLocal = 2048;
 __global__ void __launch_bounds__(1024) sort_local_kernel(const SelJob *__restrict__ sj, int64_t k,
                                                           int full) {
   const SelJob &J = sj[blockIdx.y];
-  if (J.sortP == 0 || J.st->done != 1u) return;
+  if (J.sortP == 0 || k > J.sortP || J.st->done != 1u) return;
   __shared__ uint64_t lk[kSortLocal];
   __shared__ uint32_t li[kSortLocal];
   for (int64_t base = (int64_t)blockIdx.x * kSortLocal; base < J.sortP;
