@@ -533,20 +533,25 @@ AuxCtx *aux_make(int *rc) {
   }
   return c;
 }
+// Taken by the paths that need one: counts and scores in one kernel need no second
+// stream, and making one takes 3 ms.
 struct AuxLease {
   AuxCtx *c = nullptr;
-  int rc = EPI3_OK;
-  AuxLease() {
+  AuxLease() = default;
+  int take() {
+    if (c) return EPI3_OK;
     AuxPool &p = aux_pool();
     {
       std::lock_guard<std::mutex> g(p.mu);
       if (!p.idle.empty()) {
         c = p.idle.back();
         p.idle.pop_back();
-        return;
+        return EPI3_OK;
       }
     }
+    int rc = EPI3_OK;
     c = aux_make(&rc);
+    return rc;
   }
   ~AuxLease() {
     if (!c) return;
@@ -812,7 +817,7 @@ PlainJob make_plainjob(const epi3_dataset &d, bool fp4, int JB, float *score, ui
 // smallest score + 2 e(N) as the bound, then the full pass appending only the
 // scores under the bound to the list (no score plane).
 int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, const MfmaBufs &W,
-                       hipStream_t s, AuxCtx *ctx, const PlainBound *bd = nullptr) {
+                       hipStream_t s, AuxLease &lease, const PlainBound *bd = nullptr) {
   if (bd && tasks.size() != 1) return EPI3_E_INVALID;
   const int n = (int)tasks.size();
   std::vector<int64_t> begin(n + 1, 0);
@@ -837,9 +842,6 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
   // the second stream while `s` counts pass p + 1.  Count p + 2 waits for
   // finish p (same buffer).  The slots of a pass are the tiles n0 + q of a
   // sequence of n_all tiles 0, stride, 2 stride, ...
-  hipStream_t s2 = ctx->s2;
-  hipEvent_t ev_start = ctx->ev[0], ev_cnt[2] = {ctx->ev[1], ctx->ev[2]},
-             ev_fin[2] = {ctx->ev[3], ctx->ev[4]};
   const bool fused = fp4 && !counts && plain_fused_ok(JB, lf_len);
   auto passes = [&](int64_t n_all, int64_t stride, PlainOut out) -> int {
     if (fused) {
@@ -857,6 +859,11 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
                    : EPI3_E_HIP;
       });
     }
+    int rc = lease.take();
+    if (rc != EPI3_OK) return rc;
+    hipStream_t s2 = lease.c->s2;
+    hipEvent_t ev_start = lease.c->ev[0], ev_cnt[2] = {lease.c->ev[1], lease.c->ev[2]},
+               ev_fin[2] = {lease.c->ev[3], lease.c->ev[4]};
     HIP_OK(hipEventRecord(ev_start, s));
     HIP_OK(hipStreamWaitEvent(s2, ev_start, 0));
     int p = 0;
@@ -865,7 +872,7 @@ int enqueue_count_mfma(const std::vector<MfmaTask> &tasks, bool fp4, int JB, con
       const int b = p & 1;
       if (p >= 2) HIP_OK(hipStreamWaitEvent(s, ev_fin[b], 0));
       HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 2, s));
-      int rc = timed(0, s, [&]() {
+      rc = timed(0, s, [&]() {
         return launch_count_mfma_plain(W.pjobs, W.job_begin, n, JB, fp4, buf[b], n0 * stride, nn,
                                        stride, W.queue, s) == hipSuccess
                    ? EPI3_OK
@@ -971,7 +978,8 @@ static int order_scan(const epi3_dataset *d, int order, int32_t k, int64_t cand_
     // as table completion) runs on the library's second stream while `s`
     // counts pass p + 1, and count p + 2 waits for finish p (same buffer)
     AuxLease lease;
-    if (lease.rc != EPI3_OK) return lease.rc;
+    rc = lease.take();
+    if (rc != EPI3_OK) return rc;
     hipStream_t s2 = lease.c->s2;
     hipEvent_t ev_start = lease.c->ev[0], ev_cnt[2] = {lease.c->ev[1], lease.c->ev[2]},
                ev_fin[2] = {lease.c->ev[3], lease.c->ev[4]};
@@ -1257,15 +1265,14 @@ static int enqueue_count(const epi3_dataset &d, int32_t variant, float *score, u
     if (!W.scratch) return EPI3_E_WORKSPACE;
     const MfmaBufs B{W.scratch, W.pass_tiles, W.pjob, W.jbegin, W.queue};
     AuxLease lease;
-    if (lease.rc != EPI3_OK) return lease.rc;
     const std::vector<MfmaTask> one{{&d, score, counts, W.jprefix, &W.st->kmin}};
     if (bounded) {
       const PlainBound bd{W.sample_stride, W.sample_tiles, W.sample, W.ssel, W.sel,
                           W.sst,           W.st,           W.ckey,   W.crank, W.ccap};
-      return enqueue_count_mfma(one, v == EPI3_VARIANT_MFMA_FP4, pick_JB(d, v), B, s, lease.c,
+      return enqueue_count_mfma(one, v == EPI3_VARIANT_MFMA_FP4, pick_JB(d, v), B, s, lease,
                                 &bd);
     }
-    return enqueue_count_mfma(one, v == EPI3_VARIANT_MFMA_FP4, pick_JB(d, v), B, s, lease.c);
+    return enqueue_count_mfma(one, v == EPI3_VARIANT_MFMA_FP4, pick_JB(d, v), B, s, lease);
   }
   if (bounded) return EPI3_E_UNSUPPORTED;
   SpareLayout L;
@@ -1656,8 +1663,7 @@ BatchLayout batch_layout(void *ws, const epi3_job *jobs, int32_t n, int64_t cand
 int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32_t variant,
                     hipStream_t s) {
   const bool fp4 = variant != EPI3_VARIANT_MFMA;  // MASKED: AUTO and MFMA_FP4 use FP4
-  AuxLease lease;  // second stream and events of the matrix-core passes
-  if (lease.rc != EPI3_OK) return lease.rc;
+  AuxLease lease;  // second stream and events of matrix-core passes in two kernels
   // selection state first: the count kernels write each job's key range into it
   std::vector<SelJob> sj(n);
   for (int x = 0; x < n; ++x) {
@@ -1704,7 +1710,7 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
       const MfmaBufs B{W.plain_scratch, W.plain_pass_tiles, W.pjobs_plain + rec,
                        W.plain_begin + beg, W.queue};
       const int rc = enqueue_count_mfma(tasks, kv.first.first == EPI3_VARIANT_MFMA_FP4,
-                                        kv.first.second, B, s, lease.c);
+                                        kv.first.second, B, s, lease);
       if (rc != EPI3_OK) return rc;
       rec += (int64_t)xs.size();
       beg += (int64_t)xs.size() + 1;
@@ -1802,9 +1808,6 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
                                W.masks + (int64_t)g * kPermGroup, Q, kPermGroup,
                                fp4 && perm_fused_ok(d.n_samples + 2) && Q <= 32,
                                const_cast<int32_t *>(pj.case_pairs), s));
-      hipStream_t s2 = lease.c->s2;
-      hipEvent_t ev_start = lease.c->ev[0], ev_cnt[2] = {lease.c->ev[1], lease.c->ev[2]},
-                 ev_fin[2] = {lease.c->ev[3], lease.c->ev[4]};
       const PermJob *pdev[2] = {W.pjobs + g, W.pjobs_alt + g};
       // Passes over the tiles n * stride, n < n_all: pass p counts into scratch
       // buffer p % 2 on `s`; its finish kernel runs on the second stream while
@@ -1826,6 +1829,11 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
           });
         }
         if (!W.perm_scratch) return EPI3_E_INVALID;  // the layout and the passes disagree
+        int rc = lease.take();
+        if (rc != EPI3_OK) return rc;
+        hipStream_t s2 = lease.c->s2;
+        hipEvent_t ev_start = lease.c->ev[0], ev_cnt[2] = {lease.c->ev[1], lease.c->ev[2]},
+                   ev_fin[2] = {lease.c->ev[3], lease.c->ev[4]};
         HIP_OK(hipEventRecord(ev_start, s));
         HIP_OK(hipStreamWaitEvent(s2, ev_start, 0));
         int p = 0;
@@ -1834,7 +1842,7 @@ int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32
           const int b = p & 1;
           if (p >= 2) HIP_OK(hipStreamWaitEvent(s, ev_fin[b], 0));
           HIP_OK(launch_fill_u32(reinterpret_cast<uint32_t *>(W.queue), 0u, 16, s));
-          int rc = timed(0, s, [&]() {
+          rc = timed(0, s, [&]() {
             return launch_count_mfma_perm(pdev[b], n0 * stride, nn, stride, W.queue, fp4, s) ==
                            hipSuccess
                        ? EPI3_OK
@@ -2046,7 +2054,8 @@ int epi3_scan_batched(const epi3_job *jobs, int32_t n_jobs, int32_t variant, int
 int epi3_init(void) {
   {
     AuxLease lease;  // one idle context in the pool from now on
-    if (lease.rc != EPI3_OK) return lease.rc;
+    const int rc = lease.take();
+    if (rc != EPI3_OK) return rc;
     StagingLease staging(0, true);  // and one block of pinned memory
   }
   {
