@@ -1659,11 +1659,12 @@ BatchLayout batch_layout(void *ws, const epi3_job *jobs, int32_t n, int64_t cand
   return L;
 }
 
-// Enqueues the whole batched scan (no host synchronisation inside).
+// Enqueues the whole batched scan (no host synchronisation inside).  lease: second
+// stream and events of matrix-core passes in two kernels; held until a capture of
+// `s` has ended, since the stream it forks to records into it until then.
 int enqueue_batched(const epi3_job *jobs, int32_t n, const BatchLayout &W, int32_t variant,
-                    hipStream_t s) {
+                    hipStream_t s, AuxLease &lease) {
   const bool fp4 = variant != EPI3_VARIANT_MFMA;  // MASKED: AUTO and MFMA_FP4 use FP4
-  AuxLease lease;  // second stream and events of matrix-core passes in two kernels
   // selection state first: the count kernels write each job's key range into it
   std::vector<SelJob> sj(n);
   for (int x = 0; x < n; ++x) {
@@ -1997,7 +1998,8 @@ int epi3_scan_batched(const epi3_job *jobs, int32_t n_jobs, int32_t variant, int
   hipGraphExec_t exec = nullptr;
   if (timing_on()) {
     // measurement mode: run the same sequence eagerly so each kernel is timed
-    rc = timed(2, s, [&]() { return enqueue_batched(jobs, n_jobs, W, variant, s); });
+    AuxLease lease;
+    rc = timed(2, s, [&]() { return enqueue_batched(jobs, n_jobs, W, variant, s, lease); });
     if (rc != EPI3_OK) return rc;
   } else {
     std::lock_guard<std::mutex> lk(G.mu);
@@ -2007,8 +2009,9 @@ int epi3_scan_batched(const epi3_job *jobs, int32_t n_jobs, int32_t variant, int
       exec = it->second;
     } else {
       if (!G.capture) HIP_OK(hipStreamCreateWithFlags(&G.capture, hipStreamNonBlocking));
+      AuxLease lease;
       HIP_OK(hipStreamBeginCapture(G.capture, hipStreamCaptureModeRelaxed));
-      rc = enqueue_batched(jobs, n_jobs, W, variant, G.capture);
+      rc = enqueue_batched(jobs, n_jobs, W, variant, G.capture, lease);
       hipGraph_t graph = nullptr;
       const hipError_t e = hipStreamEndCapture(G.capture, &graph);
       if (rc != EPI3_OK || e != hipSuccess) {
