@@ -108,7 +108,9 @@ typedef struct {
                              (low nibble first) [class][snp_stride][2][byte_stride / 2] */
     int32_t *pairs;       /* device: pairwise tables [class][snp_stride][snp_stride][4] */
     double *lf64;         /* device: log factorials L[0..N+1] in FP64 */
-    float *lf32;          /* device: the same rounded to FP32 */
+    float *lf32;          /* device: the same rounded to FP32.  The fixed-point table that the
+                             scans score with follows it in the buffer, so the arrays stay
+                             where epi3_encode put them */
     int32_t *status;      /* device: status word (bit 0: bad genotype byte) */
 } epi3_dataset;
 
@@ -203,9 +205,10 @@ int epi3_score_plane(const epi3_dataset *d, int32_t k, int64_t cand_cap, void *w
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc).  Not a step of the paper's method: the results of epi3_scan +
  * epi3_topk with EPI3_VARIANT_VALU bit for bit (counted on the matrix cores
- * where the rest of the array has room for their buffers), whose workspace is a device array of EPI3_STATIC_SCRATCH_BYTES inside the library
- * instead of a caller buffer (each GPU the library runs on holds its own copy
- * from the first call on it, or from epi3_init, until the process ends).
+ * where the rest of the array has room for their buffers), whose workspace is
+ * a device array of EPI3_STATIC_SCRATCH_BYTES inside the library instead of a
+ * caller buffer (each GPU the library runs on holds its own copy from the
+ * first call on it, or from epi3_init, until the process ends).
  * ------------------------------------------------------------------------ */
 
 /* Size of the library's static workspace: the FP32 score plane of the data
@@ -343,8 +346,9 @@ int epi3_pairs_score_plane(const epi3_dataset *d, int32_t k, int64_t cand_cap, v
  * (0/1 FP4 products, exact FP32 accumulation) when the data set has value
  * planes and classes of at most 65535 samples, else by AND + POPCNT over the
  * bit planes (a data set encoded with EPI3_ENCODE_BITS_ONLY); the corner
- * cells of the four sub-triplets are counted once per triplet, and every other cell follows by inclusion-exclusion from those,
- * the pairwise tables of epi3_encode and the class size.  Both count paths
+ * cells of the four sub-triplets are counted once per triplet, and every
+ * other cell follows by inclusion-exclusion from those, the pairwise tables
+ * of epi3_encode and the class size.  Both count paths
  * give the same FP32 scores.  Hits are the k lowest under
  * (K2, i, j, k, l) with the same FP32 screen and FP64 re-score as the other
  * orders.  The score plane holds C(M,4) floats, so M is limited by memory
@@ -395,6 +399,7 @@ int epi3_quads_score_plane(const epi3_dataset *d, int32_t k, int64_t cand_cap, v
 /* Run the count kernel of `variant` over every triplet of a SPLIT data set and
  * write each triplet's table and FP32 K2 in lexicographic (i, j, k) order:
  * counts_dev [C(M,3)][2][27] uint32 (may be NULL), k2_dev [C(M,3)] float.
+ * AUTO: with tables, small data sets count on the vector ALUs, which are faster there.
  * ws_dev: a workspace of epi3_workspace_bytes(d, 1, variant, 0) bytes.  Asynchronous. */
 int epi3_scan_tables(const epi3_dataset *d, int32_t variant, uint32_t *counts_dev,
                      float *k2_dev, void *ws_dev, int64_t ws_bytes, void *stream);

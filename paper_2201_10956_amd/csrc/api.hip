@@ -1068,11 +1068,14 @@ const char *epi3_version(void) { return "epi3 0.1 (gfx950)"; }
 int64_t epi3_n_triplets(int32_t n_snps) { return c3(n_snps); }
 
 double epi3_k2_error_bound(int32_t n_samples) {
-  // Per row the FP32 evaluation of L[r+1] - (L[r0] + L[r1]) with table entries
-  // rounded to FP32 errs by at most 4u L[r+1] (u = 2^-24; L is superadditive so
-  // L[r0] + L[r1] <= L[r+1]); summing 27 rows adds at most 26u sum_rows L[r+1];
-  // and sum_rows L[r+1] <= L[N + 27].  32u L[N + 27] covers both plus the
-  // second-order terms and the FP64 evaluation's own rounding.
+  // A score is the exact sum of 3 x 27 table entries, each within 2^-(s+1) of L
+  // (fx_shift), rounded once to FP32: it errs by at most 41 x 2^-s + 2^-24 K2.
+  // The bound kept here is that of an FP32 evaluation of the rows, which covers
+  // it (0.27 against 1e-3 at 16384 samples): per row L[r+1] - (L[r0] + L[r1]) with
+  // entries rounded to FP32 errs by at most 4u L[r+1] (u = 2^-24; L is
+  // superadditive so L[r0] + L[r1] <= L[r+1]); summing 27 rows adds at most 26u
+  // sum_rows L[r+1]; and sum_rows L[r+1] <= L[N + 27].  32u L[N + 27] covers both
+  // plus the second-order terms and the FP64 evaluation's own rounding.
   if (n_samples < 0) return 0.0;
   return 32.0 * ldexp(1.0, -24) * log_factorial_at((int64_t)n_samples + 27);
 }

@@ -1217,9 +1217,14 @@ static hipError_t launch_fused_t(const PlainJob *jobs, const int64_t *job_begin,
 
 // Tables longer than the LDS holds beside the staging keep their first
 // entries there: at most one row of a triplet's table can need another as
-// long as those cover half of the samples, and the cover of 7/10 taken here
-// makes such rows rare.  16-bit counts.  The lookups that a longer table
-// would need end before the words that the waves write while scoring.
+// long as those cover half of the samples; the cover of 7/10 taken here keeps
+// the lookups clear of what the waves write.  The corrected rows cost little,
+// also where nearly every triplet has one (rare alleles): 2048 x 16384 with
+// minor allele frequencies of 0.01 to 0.5, 0.01 to 0.05 and 0.001 to 0.01 67.7,
+// 66.1 and 65.8 ms (two kernels with the whole table: 85.7, 82.4, 82.0), 512 x
+// 12400 1.13, 1.09, 1.09 ms (1.51, 1.45, 1.45).  16-bit counts.  The lookups
+// that a longer table would need end before the words that the waves write
+// while scoring.
 template <int JB>
 static bool fused_ok_t(int32_t lf_len) {
   return lf_len - 2 <= 65535 && lf_len <= plain_fused_longest<JB>() && plain_lookups_ok<JB>(lf_len);

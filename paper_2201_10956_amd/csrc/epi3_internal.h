@@ -59,13 +59,13 @@ __host__ __device__ __forceinline__ int64_t c3(int64_t x) {
   return x < 3 ? 0 : x * (x - 1) / 2 * (x - 2) / 3;
 }
 
-// Lexicographic rank of i < j < k < M among all triplets.
 // Lexicographic rank of the pair (i, j), i < j < M.
 __host__ __device__ __forceinline__ int64_t pair_rank(int64_t M, int64_t i, int64_t j) {
   return c2(M) - c2(M - i) + (j - i - 1);
 }
+// Lexicographic rank of i < j < k < M among all triplets, less k.
 __host__ __device__ __forceinline__ int64_t lex_base(int64_t M, int64_t i, int64_t j) {
-  return c3(M) - c3(M - i) + c2(M - 1 - i) - c2(M - j) - j - 1;  // + k gives the rank
+  return c3(M) - c3(M - i) + c2(M - 1 - i) - c2(M - j) - j - 1;
 }
 
 // Order-preserving map of a float to an unsigned key (and back).
@@ -805,7 +805,6 @@ hipError_t launch_quad_prefix(int32_t M, int64_t *jprefix, hipStream_t s);
 hipError_t launch_count_mfma_quad(const epi3_dataset &d, const int64_t *jprefix,
                                   unsigned long long *queue, int64_t tile_begin, int64_t n_tiles,
                                   void *scratch, hipStream_t s);
-// completes and scores the quads of those tiles (t3: launch_triplet_corners)
 // Counted and scored in one kernel, where the table leaves room for two
 // workgroups per CU (about 12000 samples); stash: kQuadStash bytes per workgroup,
 // at most max_blocks of them; queue: one zeroed counter.
@@ -814,6 +813,8 @@ bool quad_fused_ok(const epi3_dataset &d);
 hipError_t launch_count_score_quad(const epi3_dataset &d, const int64_t *jprefix, const void *t3,
                                    unsigned long long *queue, void *stash, int64_t max_blocks, float *score,
                                    uint32_t *keyrange, hipStream_t s);
+// Completes and scores the quads of launch_count_mfma_quad's tiles (t3:
+// launch_triplet_corners).
 hipError_t launch_finish_quad(const epi3_dataset &d, const void *scratch, const int64_t *jprefix,
                               const void *t3, int64_t tile_begin, int64_t n_tiles, float *score,
                               uint32_t *keyrange, hipStream_t s);

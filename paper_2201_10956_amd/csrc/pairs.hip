@@ -3,8 +3,7 @@
 // Eq. 1 holds for any number of interacting SNPs (I = 3^k rows); for pairs
 // the table has 9 rows per class.  Its four cells with both genotypes in
 // {0, 1} are the pairwise tables that encoding counts for the triplet scan
-// (AND + POPCNT of the two SNPs' planes over the class's words), and the
-// other five follow from the per-SNP counts (the diagonal of the pairwise
+// (products of the SNPs' planes over the class's samples), and the other five follow from the per-SNP counts (the diagonal of the pairwise
 // tables) and the class size.  So scoring a pair is table completion and 27
 // lookups; the counting itself happened at encoding.
 #include "epi3_internal.h"

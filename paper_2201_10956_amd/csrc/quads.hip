@@ -1,11 +1,13 @@
 // Fourth-order scan: K2 of every quad of SNPs.
 //
 // Eq. 1 holds for any number of interacting SNPs; for quads the table has
-// 3^4 = 81 rows per class.  Per class and quad the 16 cells with all four
+// 3^4 = 81 rows per class.  The 8 corner cells of each of a quad's four
+// sub-triplets come from a table counted once per triplet beforehand on the
+// matrix cores (triplet_corners_kernel; they do not depend on the fourth SNP;
+// classes of more than 65535 samples: counted per quad).  Data sets without
+// value planes are scored here: per class and quad the 16 cells with all four
 // genotypes in {0, 1} are counted by AND + POPCNT over the class's words (the
-// paper's table filling, Alg. 2, with one more SNP); the 8 corner cells of
-// each of the four sub-triplets come from a table counted once per triplet
-// beforehand (they do not depend on the fourth SNP), and the rest follow by
+// paper's table filling, Alg. 2, with one more SNP), and the rest follow by
 // inclusion-exclusion (quad_cells).  One thread per quad, quads by
 // lexicographic rank, so the lanes of a wave share (i, j, k) and read
 // consecutive l.

@@ -459,10 +459,14 @@ __device__ __forceinline__ uint32_t score_quad(u16x2 (&core)[9][4], const u16x2 
 // triplet table (the latter once per four quads).  Rows are taken three at a
 // time and their lookups added two steps later, so vector instructions (about
 // 600 per quad and wave) and lookups (243) alternate: issue is what bounds it.
-// 123 registers, four waves per SIMD.  Against one class at a time in 32 bits
-// with all sub-triplets completed per quad (204 registers, all 243 lookups
-// after the table), whole scans: 256 x 4096 15.0 -> 11.7 ms, 200 x 3000 7.5 ->
-// 5.6 ms, 128 x 1000 1161 -> 853 us.
+// It serves data sets above about 11900 samples, whose table and the 18.6 KB of
+// shared tables leave two workgroups to a CU (123 registers would allow four
+// waves per SIMD), one from about 16000 samples, and four again above 20478,
+// where the table stays in global memory.  Against one class at a time in 32
+// bits with all sub-triplets completed per quad (204 registers, all 243 lookups
+// after the table, two workgroups per CU up to 20478 samples), whole scans: 128
+// x 12500 2.71 -> 2.17 ms, 128 x 16384 3.19 -> 3.00, 128 x 18000 3.43 -> 3.14, 200
+// x 18000 19.6 -> 16.0, 128 x 30000 6.57 -> 5.76 ms.
 template <bool LDS>
 __global__ void __launch_bounds__(256, 3) finish_quad_kernel(
     const uint2 *__restrict__ corners, const int64_t *__restrict__ pre_p,
