@@ -1023,11 +1023,6 @@ __global__ void __launch_bounds__(256) finish_plain_kernel(const PlainJob *__res
   const float ub = MODE == kPermOutBounded ? out.st->ub : 0.f;
   const int kl = threadIdx.x % KT, jl = threadIdx.x / KT;
   for (int64_t slot = blockIdx.x; slot < n_tiles; slot += gridDim.x) {
-    // Tables out: the waves stay together.  Each writes 216-byte tables a few bytes
-    // at a time, and where they drift apart by a tile the parts of neighbouring
-    // tables no longer meet in L2 (512 x 4096, whole call: 2.88 ms with this barrier;
-    // without it 3.10 to 3.31 ms with one to three workgroups per CU).
-    if (COUNTS) __syncthreads();
     const int64_t tg = tile_begin + slot * out.stride;
     if (jd.find(job_begin, n_jobs, tg)) {
       if (keyrange) flush_range(kmin, kmax, keyrange);
@@ -1062,20 +1057,33 @@ __global__ void __launch_bounds__(256) finish_plain_kernel(const PlainJob *__res
     i0 = __builtin_amdgcn_readfirstlane(i0);
     gptr<u4e> cor = (gptr<u4e>)(corners + slot * 2 * (int64_t)kTile);
     const int j = j0 + jl, k = k0 + kl;
-    if (j >= k || k >= M) continue;
+    const bool pair = j < k && k < M;
+    if (!COUNTS && !pair) continue;
     int fjk[2][9];
+    if (pair) {  // (tiles of 128 k reach past the padded stride)
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const uint32_t cb = (uint32_t)c * MpMp;
-      const i4e c4 = pr[cb + (uint32_t)j * Mp + k];
-      const i4e jj = pr[cb + (uint32_t)j * Mp + j], kk = pr[cb + (uint32_t)k * Mp + k];
-      const int pjk[4] = {c4.x << 2, c4.y << 2, c4.z << 2, c4.w << 2};
-      const int mj[2] = {jj.x << 2, jj.w << 2}, mk[2] = {kk.x << 2, kk.w << 2};
-      pair_cells(pjk, mj, mk, Nx4[c], fjk[c]);
+      for (int c = 0; c < 2; ++c) {
+        const uint32_t cb = (uint32_t)c * MpMp;
+        const i4e c4 = pr[cb + (uint32_t)j * Mp + k];
+        const i4e jj = pr[cb + (uint32_t)j * Mp + j], kk = pr[cb + (uint32_t)k * Mp + k];
+        const int pjk[4] = {c4.x << 2, c4.y << 2, c4.z << 2, c4.w << 2};
+        const int mj[2] = {jj.x << 2, jj.w << 2}, mk[2] = {kk.x << 2, kk.w << 2};
+        pair_cells(pjk, mj, mk, Nx4[c], fjk[c]);
+      }
     }
     for (int il = 0; il < kPI; ++il) {
       const int i = i0 + il;
-      if (i >= j) break;
+      if (COUNTS) {
+        // Tables out: the waves stay together.  Each writes 216-byte tables a few
+        // bytes at a time, and where they drift apart the parts of neighbouring
+        // tables no longer meet in L2 (512 x 4096, whole call: 3.10 to 3.31 ms without
+        // a barrier, with one to three workgroups per CU, 2.88 with one per tile, 2.58
+        // with one per two i).
+        if (il % 2 == 0) __syncthreads();
+        if (!pair || i >= j) continue;
+      } else if (i >= j) {
+        break;
+      }
       const int x = il * 256 + threadIdx.x;
       int tab[2][27];
 #pragma unroll
