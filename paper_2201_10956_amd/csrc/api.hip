@@ -271,10 +271,13 @@ int plain_variant(const epi3_dataset &d, int32_t variant) {
 
 // The same for a scan that writes its tables: there the matrix cores count and
 // complete in two kernels, so AUTO leaves small data sets to the vector ALUs, on
-// which the one-kernel scan beats them (whole calls, matrix cores / vector ALUs:
-// 64 x 2048 155 / 79 us, 100 x 1000 160 / 109, 255 x 300 505 / 432, 512 x 1000 2.68
-// / 2.15 ms; from the other side 200 x 4000 265 / 361 us, 128 x 12000 205 / 338, 255
-// x 16000 656 / 1626, 512 x 4096 2.88 / 4.45 ms).
+// which the one-kernel scan beats them (whole calls, FP4 matrix cores / vector ALUs:
+// 64 x 2048 155 / 75 us, 100 x 1000 159 / 103, 255 x 300 450 / 426, 512 x 1000 2.36
+// / 2.04 ms; from the other side 200 x 4000 268 / 349 us, 128 x 12000 203 / 320, 255
+// x 16000 599 / 1597, 512 x 2048 2.39 / 2.80 ms, 512 x 4096 2.53 / 4.48).  From 256
+// SNPs the two meet at about 1500 (512 x 1500 2.37 / 2.37 ms) to 2000 samples (256 x
+// 2048 468 / 458 us): between 1024 and there the line costs up to a third (256 x 1024
+// 457 / 340 us, 512 x 1024 2.36 / 2.06 ms).
 int tables_variant(const epi3_dataset &d, int32_t variant) {
   const int v = plain_variant(d, variant);
   const bool large = d.n_samples >= 16384 || (d.n_snps >= 128 && d.n_samples >= 4000) ||
